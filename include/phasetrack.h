@@ -78,7 +78,9 @@ typedef enum { PT_OBJ_CHI2 = 0, PT_OBJ_COR = 1 } pt_objective_kind;
 /* Arithmetic of the objective.  PT_PREC_FP64: phase, cosine, residual and
  * sums in FP64.  PT_PREC_MIXED: FP64 per-chunk phase anchor, FP32 local
  * phase offset (compensated), FP32 cosine and residual, FP32 chunk sums,
- * FP64 cross-chunk sum; DE selection compares FP64 values in both modes. */
+ * FP64 cross-chunk sum; DE selection compares FP64 values in both modes.
+ * (A fit that runs through node weights, see pt_ctx_set_launch_mode, is FP64
+ * throughout whichever is asked for: there the mixed sums would save nothing.) */
 typedef enum { PT_PREC_FP64 = 0, PT_PREC_MIXED = 1 } pt_precision;
 
 /* pt_fit.flags bits.  CONVERGED: the window stop rule was met; MAXGEN: the
@@ -390,7 +392,10 @@ typedef struct {
     uint64_t hbm_budget_bytes;  /* device bytes resident blocks may hold; a block of n samples
                                    holds n * sizeof(sample) + (max_gens + 1) * 8 + 2 * (P * 136 +
                                    P * ntiles * 8 + 48), ntiles = ceil(n / (256 * spl)): samples,
-                                   history and two slots of rows, objectives, partials and state */
+                                   history and two slots of rows, objectives, partials and state;
+                                   node weights and draws (18 KB + 8 P per generation of a step,
+                                   at most 500) and the working space of one step's new blocks
+                                   are not counted */
     pt_de_settings de;          /* settings of every block (pop <= 256) */
     int32_t seed_first;         /* 1: seed each track's first box from its samples */
     int32_t seed_snippet;       /* pt_seed_opts.snippet (0 = default) */
@@ -448,6 +453,18 @@ double pt_server_clock(pt_server* srv);
 /* ---- launch strategy ---- */
 
 /* How a fit's generations are launched.
+ *   Node weights (PT_LAUNCH_AUTO).  Over one block a candidate's phase differs
+ *     from that of the box's centre by a smooth polynomial whose range the box
+ *     bounds, so the sums of the objective over the samples equal, to FP64
+ *     rounding, sums over K Chebyshev nodes (K of 60 to 300 for the paper's
+ *     boxes) with weights computed once from the samples.  A fit computes them
+ *     at its start and then runs its generations, one workgroup per block,
+ *     without touching the samples again.  Taken for every block it carries:
+ *     n of 64 to 2^26, P <= 240, K <= 512 and an FP64 method of
+ *     PT_FP64_AUTO; the choice depends on the block and P only.  The chi-square
+ *     comes as a difference from the samples' energy, so a fit whose best
+ *     falls below 1/1000 of it (30 dB of signal to noise), or whose samples are
+ *     not finite, is run again over its samples.
  *   PT_LAUNCH_PERSISTENT: one cooperative grid runs every generation of
  *     every block; workgroups keep their sample chunks in registers, and the
  *     workgroup that completes a block's generation runs its DE step (no
@@ -457,16 +474,19 @@ double pt_server_clock(pt_server* srv);
  *     launch (or one launch with the step fused, see pt_ctx_set_step_fusion),
  *     replayed from captured HIP graphs of 50 generations (250 for fits
  *     without a window rule).
- *   PT_LAUNCH_AUTO (default): graph.  On MI355X the per-block barrier of
- *     the persistent grid costs about as much as graph-replayed launches,
- *     which run back to back, so the graph path is the faster default.
- * Both give bit-identical results for the same geometry. */
+ *   PT_LAUNCH_AUTO (default): node weights where they apply, else graph.  On
+ *     MI355X the per-block barrier of the persistent grid costs about as much
+ *     as graph-replayed launches, which run back to back, so the graph path is
+ *     the faster of those two.
+ * Graph and persistent launches give bit-identical results for the same
+ * geometry; node weights the same objectives to rounding, so the same
+ * trajectory until a selection compares two objectives closer than that. */
 enum { PT_LAUNCH_AUTO = 0, PT_LAUNCH_GRAPH = 1, PT_LAUNCH_PERSISTENT = 2 };
 
 int pt_ctx_set_launch_mode(pt_ctx* ctx, int mode);
 
-/* Launch strategy the context's most recent fit used (PT_LAUNCH_GRAPH or
- * PT_LAUNCH_PERSISTENT). */
+/* Launch strategy the context's most recent fit used: PT_LAUNCH_PERSISTENT, or
+ * PT_LAUNCH_GRAPH for any other. */
 int pt_ctx_last_launch(pt_ctx* ctx, int* mode);
 
 /* ---- FP64 objective arithmetic ----
@@ -489,8 +509,9 @@ enum { PT_FP64_AUTO = 0, PT_FP64_POLY = 1 };
 int pt_ctx_set_fp64_method(pt_ctx* ctx, int method);
 
 /* ---- step fusion ----
- * How a fit's generations map onto launches (graph-replayed fits; the DE
- * step is that of Table 4, DE/rand/1/bin, in every form):
+ * How a fit's generations map onto launches (graph-replayed fits; fits through
+ * node weights have one form; the DE step is that of Table 4, DE/rand/1/bin,
+ * in every form):
  * PT_FUSION_AUTO (default): PT_FUSION_LEAD when the launch's work units fit
  *   in two rounds of resident workgroups (the kernel's occupancy times the
  *   compute units: a latency-bound fit, such as one paper-scale block) and
@@ -516,19 +537,22 @@ int pt_ctx_set_step_fusion(pt_ctx* ctx, int mode);
 
 /* Objective arithmetic of the context's most recent fit or objective
  * evaluation: per-sample FP64 cosine, mixed precision, or FP64 phasor (also
- * for a batch whose blocks used both FP64 arithmetics). */
+ * for a batch whose blocks used both FP64 arithmetics).  For fits through node
+ * weights, the arithmetic their samples would be evaluated in. */
 enum { PT_ARITH_FP64_POLY = 0, PT_ARITH_MIXED = 1, PT_ARITH_FP64_PHASOR = 2 };
 
 int pt_ctx_last_arithmetic(pt_ctx* ctx, int* arith);
 
 /* Chunk geometry (samples per lane, candidates per workgroup) of the
- * context's most recent fit or objective evaluation; 0, 0 before the first.
+ * context's most recent fit or objective evaluation (for fits through node
+ * weights, the one their samples would be evaluated in); 0, 0 before the first.
  * PT_EINVAL on null arguments. */
 int pt_ctx_last_geometry(pt_ctx* ctx, int* samples_per_lane, int* cand_per_group);
 
 /* Objective-kernel launches of the context's most recent fit (all blocks of
  * a batch share them): one per generation including generation 0, plus one
- * for the last DE step in the leading-step form; 1 for a persistent launch.
+ * for the last DE step in the leading-step form; 1 for a persistent launch; one
+ * per up to 500 generations through node weights.
  * A fit that stopped early by the window rule may have run fewer. */
 int pt_ctx_last_fit_launches(pt_ctx* ctx, int64_t* launches);
 
@@ -538,7 +562,8 @@ int pt_ctx_last_fit_launches(pt_ctx* ctx, int64_t* launches);
  * on, fits launch kernels one by one (no graph replay), each generation as
  * the objective alone and then the DE step whatever the step-fusion
  * setting, and bracket every objective launch with HIP events on the fit's
- * stream; results are bit-identical to those of the other forms. */
+ * stream (through node weights: one launch, bracketed, per generation);
+ * results are bit-identical to those without timing. */
 int pt_ctx_set_timing(pt_ctx* ctx, int on);
 
 /* Launch count and summed duration [ms] of objective-kernel launches timed
@@ -567,8 +592,8 @@ int pt_ctx_get_tile(pt_ctx* ctx, int64_t n, int P, int precision, int* samples_p
 int pt_ctx_set_tile(pt_ctx* ctx, int samples_per_lane, int cand_per_group);
 
 /* Time every supported geometry on a block of n samples and population P:
- * short fits of 100 generations in the context's current launch form and
- * step fusion, on synthetic data on the device in a box of the paper's
+ * short fits of 100 generations over the samples (graph launches unless the
+ * context's launch mode is persistent) in the context's step fusion, on synthetic data on the device in a box of the paper's
  * widths around one carrier at the largest drift rate and drift
  * acceleration of the paper-scale synthetic blocks (5 Hz/s, 0.05 Hz/s^2),
  * so that each geometry is timed with the FP64 arithmetic it would use at

@@ -1,7 +1,8 @@
 """Build libphasetrack.so (HIP, gfx950) in-tree with hipcc.
 
-The runtime (csrc/phasetrack.hip) and the kernel instances (csrc/instances.hip,
-once per sample type and samples-per-lane value) are compiled as separate
+The runtime (csrc/phasetrack.hip), the node-weight fits (csrc/nodes.hip) and the
+kernel instances (csrc/instances.hip, once per sample type and
+samples-per-lane value) are compiled as separate
 objects in parallel, then linked into one shared library.
 """
 import os
@@ -13,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 SRC = os.path.join(CSRC, "phasetrack.hip")
 INST = os.path.join(CSRC, "instances.hip")
+NODES = os.path.join(CSRC, "nodes.hip")
 LIB = os.path.join(HERE, "libphasetrack.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
@@ -48,7 +50,7 @@ def _jobs() -> int:
 def build(verbose: bool = False, extra=None) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
-    units = [(SRC, os.path.join(OBJ_DIR, "phasetrack.o"), [])]
+    units = [(SRC, os.path.join(OBJ_DIR, "phasetrack.o"), []), (NODES, os.path.join(OBJ_DIR, "nodes.o"), [])]
     for t, tn, s in INSTANCES:
         units.append((INST, os.path.join(OBJ_DIR, f"instances_{tn}_s{s}.o"),
                       [f"-DPT_INST_T={t}", f"-DPT_INST_TN={tn}", f"-DPT_INST_S={s}"]))

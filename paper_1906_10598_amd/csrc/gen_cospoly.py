@@ -5,7 +5,8 @@ The device kernels reduce the phase to turns r in [-1/2, 1/2] exactly
 polynomial p fitted on u = r^2 in [0, 1/4] at Chebyshev nodes (mpmath
 chebyfit, 50 digits).  Degree 10 in u gives an approximation error of
 3.3e-17 (below FP64 rounding), degree 9 gives 6.2e-15; degree 6 gives 1.1e-8
-(below FP32 rounding).
+(below FP32 rounding).  Phases known to lie within an eighth of a turn take
+degree 6 in FP64.
 
 Run:  python gen_cospoly.py  (rewrites cospoly.h next to this script).
 """
@@ -17,13 +18,13 @@ mpmath.mp.dps = 50
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def fit(deg, odd=False):
+def fit(deg, odd=False, rmax=mpmath.mpf(1) / 2):
     if odd:  # sin(2 pi r) / r as a polynomial in u = r^2
         f = lambda u: (mpmath.sin(2 * mpmath.pi * mpmath.sqrt(u)) / mpmath.sqrt(u)  # noqa: E731
                        if u != 0 else 2 * mpmath.pi)
     else:
         f = lambda u: mpmath.cos(2 * mpmath.pi * mpmath.sqrt(u))  # noqa: E731
-    poly, err = mpmath.chebyfit(f, [0, mpmath.mpf(1) / 4], deg + 1, error=True)
+    poly, err = mpmath.chebyfit(f, [0, rmax ** 2], deg + 1, error=True)
     # chebyfit returns highest degree first
     return [float(c) for c in poly], float(err)
 
@@ -32,6 +33,8 @@ def main():
     p64, e64 = fit(10)
     p64s, e64s = fit(9)
     s64, es64 = fit(10, odd=True)
+    cn, ecn = fit(6, rmax=mpmath.mpf(1) / 8)
+    sn, esn = fit(6, odd=True, rmax=mpmath.mpf(1) / 8)
     p32, e32 = fit(6)
     lines = [
         "// Generated by gen_cospoly.py -- do not edit.",
@@ -49,6 +52,11 @@ def main():
     lines += ["};", f"// sin(2 pi r) = r q(r^2), FP64, degree 10 in u: error of q {es64:.2e}.",
               f"constexpr int kSinDeg64 = {len(s64) - 1};", "constexpr double kSin64[] = {"]
     lines += [f"    {c.hex()},  // {c:.17e}" for c in s64]
+    lines += ["};", f"// |r| <= 1/8: cos(2 pi r) and sin(2 pi r) / r, degree 6 in u: errors {ecn:.2e}, {esn:.2e}.",
+              f"constexpr int kNarDeg64 = {len(cn) - 1};", "constexpr double kCosNar64[] = {"]
+    lines += [f"    {c.hex()},  // {c:.17e}" for c in cn]
+    lines += ["};", "constexpr double kSinNar64[] = {"]
+    lines += [f"    {c.hex()},  // {c:.17e}" for c in sn]
     lines += ["};", f"constexpr int kCosDeg32 = {len(p32) - 1};", "constexpr float kCos32[] = {"]
     for c in p32:
         cf = float(mpmath.mpf(c))

@@ -1,0 +1,108 @@
+// nodes.h -- the fit of a block through node weights (host side interface).
+//
+// Over one block the model phase of a candidate differs from a reference
+// phase phi_ref (the box's centre) by a smooth polynomial delta(x), x in
+// [-1, 1] along the block, whose range the search box bounds.  exp(i delta)
+// and exp(2 i delta) are therefore their own interpolants at K Chebyshev
+// nodes x_k to FP64 rounding, and the sums over samples that the objective of
+// Eq. (2-2-4) needs become sums over nodes:
+//   sum_n s_n cos phi_n  = Re sum_k Z_k exp(i delta(x_k)),
+//   sum_n cos 2 phi_n    = Re sum_k W_k exp(2 i delta(x_k)),
+//   Z_k = sum_n s_n exp(i phi_ref(n)) L_k(x_n),
+//   W_k = sum_n exp(2 i phi_ref(n)) L_k(x_n),
+// L_k the Lagrange polynomials of the nodes.  With S2 = sum_n s_n^2,
+//   chi^2 = S2 - 2 A sum s cos phi + A^2 (N + sum cos 2 phi) / 2
+// (amplitude slope: the same with A + Adot t inside the sums).  A fit
+// computes Z, W and S2 once from its samples and evaluates every candidate
+// of every generation at K points (about a hundred) instead of N samples.
+//
+// Measured against one launch per generation over all samples (each generation
+// a chain of ~9 us in its leading-step form; same machine): the 400 000-sample
+// block, P = 40, 2000 generations 18.2 -> 2.21 ms; the quartic 1e6-sample block
+// 39.5 -> 2.81 ms; 64 uneven blocks, 1500 generations 172 -> 2.88 ms (the
+// blocks' generations then run on 64 compute units at once instead of sharing
+// the chip's issue slots sample by sample).
+//
+// Three kernels:
+//   k_node_project  samples -> 16 points per tile of samples (the same
+//                   interpolation inside a tile, whose phase span needs only
+//                   16 nodes); also the random draws of the first chunk
+//   k_node_moments  points -> Chebyshev moments of the block, partial sums
+//   k_node_fit      moments -> Z, W (first chunk), then whole generations of
+//                   Differential Evolution, one workgroup per block; also the
+//                   random draws of the next chunk
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "../../include/phasetrack.h"
+#include "device.h"
+
+namespace pt {
+
+constexpr int kNodeMaxK = 512;    // largest node count of a block
+constexpr int kNodeMaxP = 240;    // largest population (four members per row of 16 lanes, 15 waves)
+constexpr int kNodePts = 16;      // nodes per tile, and of the narrow set
+constexpr int kNodeRun = 4096;    // samples a projection workgroup takes at a time (16 per lane)
+constexpr int kNodeGroup = 128;   // points per moments workgroup
+constexpr int kNodeRing = 512;    // best-so-far values k_node_fit keeps in LDS for the window rule
+constexpr int kNodeNarrow = 5 * kNodePts + 2 * 8;  // doubles of a saved narrow set: weights, centre, limits
+// chi-square is taken as S2 - ..., so it carries rounding of ~1e-16 S2: a fit
+// whose best falls below kNodeCancel * S2 (30 dB of signal to noise) is
+// abandoned and run through the per-sample objective
+constexpr double kNodeCancel = 1e-3;
+enum { kFlagNodeAbort = 1 << 16 };  // DeState::flags of an abandoned fit
+
+// One block of a node-weight launch, beside its BlockDesc.
+struct NodeDesc {
+    // reference phase in turns, a polynomial in m = n - ref: r1 (hi + lo), r2, r3, r4
+    double r1h, r1l, r2, r3, r4;
+    // x = (n - (N - 1) / 2) / h, h = (N - 1) / 2; m = h (x + c)
+    double h, c;
+    // slot -> coefficient of u = m / h: (value - mid) * sc (turns; amplitude units for slots 0 and 5)
+    double mid[kSlots], sc[kSlots];
+    double su1, su2;   // sum over samples of u and u^2 (energy of a sloping amplitude)
+    int K;             // nodes, a multiple of 16
+    int slope;         // the amplitude slope is active
+    int lanes_log;     // log2 of the lanes (16 samples each) sharing a tile
+    int runs;          // kNodeRun-sample runs per projection workgroup
+    int ntile;         // tiles
+    int proj_begin, nproj;  // projection workgroups
+    int mom_begin, nmom;    // moments workgroups
+    int g0;            // next generation of the block when the descriptors were uploaded
+    int parity;        // which half of `draws` the next launch reads
+    double* pts;       // ntile x 16 x (Re s e, Im s e, Re e^2, Im e^2)
+    double* s2;        // nproj partial sums of s^2
+    double* mom;       // nmom x K x 4 partial moments
+    double* wts;       // K x 4 weights, then S2
+    double* nar;       // kNodeNarrow doubles and 4 ints of the narrow set
+    uint32_t* draws;   // two halves of chunk x P packed draws
+};
+
+struct NodePlan {
+    NodeDesc nd;       // everything but the pointers, prefixes, g0 and parity
+    size_t pts_doubles, s2_doubles, mom_doubles;  // working space of the projection
+};
+constexpr size_t kNodeWtsDoubles = 4 * kNodeMaxK + 2;
+constexpr size_t kNodeNarDoubles = kNodeNarrow + 2;
+
+// Whether a block's fits go through node weights, and its plan: depends on
+// the block (length, rate, reference, box) and the population size only.
+bool node_plan(const pt_block& b, double ref, int P, NodePlan* out);
+
+// Largest number of generations one k_node_fit launch runs for population P
+// and nodes up to maxK, and its dynamic LDS bytes.
+int node_chunk(int P, int maxK, int lds_max);
+size_t node_fit_lds(int P, int maxK, int chunk);
+
+// Launches (nd / bd: device tables of nblk blocks; chunk: generations per
+// half of `draws`).  `off`: generations run since the tables were uploaded.
+hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_proj, int P, int ngen, int chunk,
+                        hipStream_t s);
+hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, hipStream_t s);
+hipError_t node_fit(const NodeDesc* nd, const BlockDesc* bd, int nblk, int P, int maxK, int off, int ngen, int next_ngen,
+                    int chunk, int flip, hipStream_t s);
+hipError_t node_setup(int lds_max);  // once per device
+
+}  // namespace pt

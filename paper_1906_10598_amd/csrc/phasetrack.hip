@@ -22,6 +22,7 @@
 #include "../../include/phasetrack.h"
 #include "instances.h"
 #include "kernels.h"
+#include "nodes.h"
 #include "seed.h"
 
 using namespace pt;
@@ -265,6 +266,10 @@ struct pt_ctx {
     hipEvent_t ev_state[2] = {nullptr, nullptr};
     DevBuf desc, pop, trial, fpop, partials, hist, state, rec, staging, eval_pop, tune_block, sync;
     PinBuf hdesc, hrec, hstate;
+    // node-weight fits: descriptor tables, and weights, draws and the projection's working space
+    DevBuf node_desc, node_ws;
+    PinBuf hnode;
+    int lds_max = 65536;  // LDS bytes one workgroup may hold
     // last fit (for pt_last_population / pt_last_history)
     int last_nblk = 0, last_P = 0, last_maxg = 0;
     std::vector<int> last_gens;
@@ -615,10 +620,33 @@ BlockDesc base_desc(const pt_block& B, const pt_de_settings* de, int ntiles, int
     return d;
 }
 
-int prepare(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings* de, hipStream_t s, Plan* pl,
-            bool with_state) {
+// Blocks with their samples on the device: host samples are copied into the
+// context's staging buffer on stream s.
+int stage_blocks(pt_ctx* ctx, const pt_block* blocks, int nblk, hipStream_t s, std::vector<pt_block>* out) {
+    out->assign(blocks, blocks + nblk);
+    auto bytes = [&](int b) { return (size_t)blocks[b].n * (blocks[b].dtype == PT_F64 ? 8 : 4); };
+    size_t total = 0;
+    for (int b = 0; b < nblk; ++b)
+        if (!blocks[b].on_device) total += (bytes(b) + 255) & ~(size_t)255;
+    if (!total) return PT_OK;
+    const int rc = ctx->staging.ensure(total);
+    if (rc) return rc;
+    char* stage = static_cast<char*>(ctx->staging.p);
+    for (int b = 0; b < nblk; ++b) {
+        if (blocks[b].on_device) continue;
+        HIPCHK(hipMemcpyAsync(stage, blocks[b].samples, bytes(b), hipMemcpyHostToDevice, s));
+        (*out)[b].samples = stage;
+        (*out)[b].on_device = 1;
+        stage += (bytes(b) + 255) & ~(size_t)255;
+    }
+    return PT_OK;
+}
+
+// Geometry and arithmetic of a call (phasor: the blocks whose boxes allow the
+// FP64 phasor path).
+int plan_arithmetic(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings* de, Plan* pl,
+                    std::vector<char>* phasor, int* n_phasor) {
     const int P = de->pop;
-    pl->nblk = nblk;
     pl->P = P;
     pl->dtype = blocks[0].dtype;
     pl->mixed = de->precision == PT_PREC_MIXED;
@@ -647,31 +675,76 @@ int prepare(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings*
         if (units > 4LL * ctx->ncu) pl->geo = throughput_geometry(P);
     }
     pl->mode = pl->mixed ? kModeMixed : kModePoly;
-    std::vector<char> phasor(nblk, 0);
-    int nphasor = 0;
+    phasor->assign(nblk, 0);
+    *n_phasor = 0;
     if (!pl->mixed && ctx->fp64_method != PT_FP64_POLY) {
         for (int b = 0; b < nblk; ++b) {
             const pt_box& bx = blocks[b].box;
             const double span = (double)blocks[b].n + std::fabs(block_ref(&blocks[b]));
-            phasor[b] = phasor_ok(pl->geo.spl, blocks[b].fs, span, bx.lo[2], bx.hi[2], box_max(bx, 3),
-                                  box_max(bx, 4), box_max(bx, 6));
-            nphasor += phasor[b];
+            (*phasor)[b] = phasor_ok(pl->geo.spl, blocks[b].fs, span, bx.lo[2], bx.hi[2], box_max(bx, 3),
+                                     box_max(bx, 4), box_max(bx, 6));
+            *n_phasor += (*phasor)[b];
         }
-        if (nphasor == nblk) pl->mode = kModePhasor;  // one kernel for every block
+        if (*n_phasor == nblk) pl->mode = kModePhasor;  // one kernel for every block
     }
+    return PT_OK;
+}
+
+// DE buffers of a call of nblk blocks (every launch form keeps block b's at
+// the b-th place) and the records' and states' host copies.
+int ensure_state(pt_ctx* ctx, int nblk, const pt_de_settings* de) {
+    const int P = de->pop;
+    // two slots of the DE buffers (the leading-step form alternates between them)
+    const size_t rows = (size_t)nblk * P * kStride * sizeof(double);
+    int rc;
+    if ((rc = ctx->pop.ensure(2 * rows)) || (rc = ctx->trial.ensure(2 * rows)) ||
+        (rc = ctx->fpop.ensure(2 * (size_t)nblk * P * sizeof(double))) ||
+        (rc = ctx->hist.ensure((size_t)nblk * (de->max_gens + 1) * sizeof(double))) ||
+        (rc = ctx->state.ensure(2 * (size_t)nblk * sizeof(DeState))) ||
+        (rc = ctx->rec.ensure((size_t)nblk * sizeof(FitRecord))) ||
+        (rc = ctx->hrec.ensure((size_t)nblk * sizeof(FitRecord))) ||
+        (rc = ctx->hstate.ensure(4 * (size_t)nblk * sizeof(DeState) + sizeof(int))))
+        return rc;
+    return PT_OK;
+}
+
+// Block b's DE buffers (of nblk) in a descriptor.
+void set_state(pt_ctx* ctx, int b, int max_gens, BlockDesc* d) {
+    const int P = d->P;
+    d->pop = static_cast<double*>(ctx->pop.p) + (size_t)b * P * kStride;
+    d->trial = static_cast<double*>(ctx->trial.p) + (size_t)b * P * kStride;
+    d->fpop = static_cast<double*>(ctx->fpop.p) + (size_t)b * P;
+    d->hist = static_cast<double*>(ctx->hist.p) + (size_t)b * (max_gens + 1);
+    d->st = static_cast<DeState*>(ctx->state.p) + b;
+}
+
+// Plan and descriptors of a call's blocks `idx` (ascending; samples on the
+// device) for the launch forms that evaluate every sample.
+int prepare(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<int>& idx, const pt_de_settings* de,
+            hipStream_t s, Plan* pl, bool with_state) {
+    const int P = de->pop, nblk = (int)idx.size();
+    pl->nblk = nblk;
+    std::vector<char> phasor;
+    int nphasor = 0, rc;
+    if ((rc = plan_arithmetic(ctx, blocks, nall, de, pl, &phasor, &nphasor))) return rc;
+    nphasor = 0;
+    pl->slope = false;
+    for (int b : idx) {
+        nphasor += phasor[b];
+        if (blocks[b].box.lo[5] != 0.0 || blocks[b].box.hi[5] != 0.0) pl->slope = true;
+    }
+    if (nblk < nall && !pl->mixed) pl->mode = nphasor == nblk ? kModePhasor : kModePoly;
     const int tile = kThreads * pl->geo.spl;
     const int groups = (P + pl->geo.cpg - 1) / pl->geo.cpg;
 
     // sizes
     std::vector<int> ntiles(nblk);
-    size_t part_elems = 0, stage_bytes = 0;
+    size_t part_elems = 0;
     int64_t units = 0;
-    for (int b = 0; b < nblk; ++b) {
-        ntiles[b] = (int)((blocks[b].n + tile - 1) / tile);
-        part_elems += (size_t)P * ntiles[b];
-        units += (int64_t)ntiles[b] * groups;
-        if (!blocks[b].on_device)
-            stage_bytes += ((size_t)blocks[b].n * (blocks[b].dtype == PT_F64 ? 8 : 4) + 255) & ~(size_t)255;
+    for (int k = 0; k < nblk; ++k) {
+        ntiles[k] = (int)((blocks[idx[k]].n + tile - 1) / tile);
+        part_elems += (size_t)P * ntiles[k];
+        units += (int64_t)ntiles[k] * groups;
     }
     if (units > (int64_t)1 << 30) return fail(PT_EINVAL, "batch too large (%lld work units)", (long long)units);
     pl->total_units = (int)units;
@@ -699,60 +772,34 @@ int prepare(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings*
                     : 0;
     if (pl->fused == 2) pl->de_lds += (size_t)P * kSlots * 8;  // the leading step stages both row sets
 
-    // two slots of the DE buffers (the leading-step form alternates between them)
-    const size_t rows = (size_t)nblk * P * kStride * sizeof(double);
-    int rc;
-    if ((rc = ctx->desc.ensure(2 * sizeof(BlockDesc) * nblk)) || (rc = ctx->pop.ensure(2 * rows)) ||
-        (rc = ctx->trial.ensure(2 * rows)) || (rc = ctx->fpop.ensure(2 * (size_t)nblk * P * sizeof(double))) ||
+    if ((rc = ctx->desc.ensure(2 * sizeof(BlockDesc) * nblk)) || (rc = ensure_state(ctx, nall, de)) ||
         (rc = ctx->partials.ensure(2 * part_elems * sizeof(double))) ||
-        (rc = ctx->hist.ensure((size_t)nblk * (de->max_gens + 1) * sizeof(double))) ||
-        (rc = ctx->state.ensure(2 * (size_t)nblk * sizeof(DeState))) ||
         (rc = ctx->sync.ensure((size_t)nblk * kSyncInts * sizeof(int))) ||
-        (rc = ctx->rec.ensure((size_t)nblk * sizeof(FitRecord))) ||
-        (rc = ctx->hdesc.ensure(2 * sizeof(BlockDesc) * nblk)) ||
-        (rc = ctx->hrec.ensure((size_t)nblk * sizeof(FitRecord))) ||
-        (rc = ctx->hstate.ensure(4 * (size_t)nblk * sizeof(DeState) + sizeof(int))))
+        (rc = ctx->hdesc.ensure(2 * sizeof(BlockDesc) * nblk)))
         return rc;
-    if (stage_bytes && (rc = ctx->staging.ensure(stage_bytes))) return rc;
 
     // descriptor table (pinned host -> device)
     BlockDesc* hd = static_cast<BlockDesc*>(ctx->hdesc.p);
-    double* pop = static_cast<double*>(ctx->pop.p);
-    double* trial = static_cast<double*>(ctx->trial.p);
-    double* fpop = static_cast<double*>(ctx->fpop.p);
     double* part = static_cast<double*>(ctx->partials.p);
-    double* hist = static_cast<double*>(ctx->hist.p);
-    DeState* st = static_cast<DeState*>(ctx->state.p);
-    char* stage = static_cast<char*>(ctx->staging.p);
-    size_t part_off = 0, stage_off = 0;
+    size_t part_off = 0;
     int unit_off = 0;
-    for (int b = 0; b < nblk; ++b) {
-        const pt_block& B = blocks[b];
-        BlockDesc d = base_desc(B, de, ntiles[b], groups);
-        const size_t bytes = (size_t)B.n * (B.dtype == PT_F64 ? 8 : 4);
-        if (!B.on_device) {
-            HIPCHK(hipMemcpyAsync(stage + stage_off, B.samples, bytes, hipMemcpyHostToDevice, s));
-            d.samples = stage + stage_off;
-            stage_off += (bytes + 255) & ~(size_t)255;
-        }
+    for (int k = 0; k < nblk; ++k) {
+        BlockDesc d = base_desc(blocks[idx[k]], de, ntiles[k], groups);
+        set_state(ctx, idx[k], de->max_gens, &d);
         d.unit_begin = unit_off;
-        unit_off += ntiles[b] * groups;
-        d.pop = pop + (size_t)b * P * kStride;
-        d.trial = trial + (size_t)b * P * kStride;
-        d.fpop = fpop + (size_t)b * P;
+        unit_off += ntiles[k] * groups;
         d.partials = part + part_off;
-        part_off += (size_t)P * ntiles[b];
-        d.hist = hist + (size_t)b * (de->max_gens + 1);
-        d.st = with_state ? st + b : nullptr;
+        part_off += (size_t)P * ntiles[k];
+        if (!with_state) d.st = nullptr;
         if (pl->fused == 2) {
-            d.pop2 = d.pop + (size_t)nblk * P * kStride;
-            d.trial2 = d.trial + (size_t)nblk * P * kStride;
-            d.fpop2 = d.fpop + (size_t)nblk * P;
+            d.pop2 = d.pop + (size_t)nall * P * kStride;
+            d.trial2 = d.trial + (size_t)nall * P * kStride;
+            d.fpop2 = d.fpop + (size_t)nall * P;
             d.partials2 = d.partials + part_elems;
-            d.st2 = d.st + nblk;
+            d.st2 = d.st + nall;
         }
-        d.sync = with_state ? static_cast<int*>(ctx->sync.p) + (size_t)b * kSyncInts : nullptr;
-        hd[b] = d;
+        d.sync = with_state ? static_cast<int*>(ctx->sync.p) + (size_t)k * kSyncInts : nullptr;
+        hd[k] = d;
     }
     // objective launches: one over the main table, or (FP64 batches whose
     // blocks differ in arithmetic) the phasor blocks and the others apart; a
@@ -779,9 +826,9 @@ int prepare(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings*
         for (int want = 1; want >= 0; --want) {
             const int off = ndesc;
             int64_t u = 0;
-            for (int b = 0; b < nblk; ++b) {
-                if (phasor[b] != want) continue;
-                BlockDesc d = hd[b];
+            for (int k = 0; k < nblk; ++k) {
+                if (phasor[idx[k]] != want) continue;
+                BlockDesc d = hd[k];
                 d.unit_begin = (int)u;
                 u += (int64_t)d.ntiles * d.ngroups;
                 hd[ndesc++] = d;
@@ -820,19 +867,15 @@ void derive(pt_fit* f) {
     f->total_phase = phase(f->t_right) - phase(f->t_left);
 }
 
-int run_fit(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings* de, void* hip_stream,
-            pt_fit* out) {
-    int rc = check_de(de);
-    if (rc) return rc;
-    if (nblk < 1 || nblk > 4096) return fail(PT_EINVAL, "nblk = %d outside [1, 4096]", nblk);
-    if (!out) return fail(PT_EINVAL, "out is null");
-    for (int b = 0; b < nblk; ++b)
-        if ((rc = check_block(&blocks[b], b))) return rc;
-    HIPCHK(hipSetDevice(ctx->device));
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+// Fits of the blocks `idx` by the launch forms that evaluate every sample;
+// rec[b]: block b's record.
+int run_direct(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<int>& idx, const pt_de_settings* de,
+               hipStream_t s, std::vector<FitRecord>* rec) {
+    int rc;
+    const int nblk = (int)idx.size();
     Plan pl;
     void* old_desc = ctx->desc.p;
-    if ((rc = prepare(ctx, blocks, nblk, de, s, &pl, true))) return rc;
+    if ((rc = prepare(ctx, blocks, nall, idx, de, s, &pl, true))) return rc;
     if (ctx->desc.p != old_desc) ctx->drop_graphs();
     const BlockDesc* d = static_cast<const BlockDesc*>(ctx->desc.p);
 
@@ -895,10 +938,10 @@ int run_fit(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings*
         const int chunk = pl.window ? kChunk : kChunkLong;
         const int full = iters / chunk, rem = iters % chunk;
         DeState* hst = static_cast<DeState*>(ctx->hstate.p);
-        const int ns = lead ? 2 * nblk : nblk;  // leading-step form: either slot may hold the stop
+        const int ns = lead ? 2 * nall : nall;  // leading-step form: either slot may hold the stop
         auto stopped = [&](const DeState* h) {
-            for (int b = 0; b < nblk; ++b)
-                if (!(h[b].done != 0 || (lead && h[nblk + b].done != 0))) return false;
+            for (int b : idx)
+                if (!(h[b].done != 0 || (lead && h[nall + b].done != 0))) return false;
             return true;
         };
         bool all = false;
@@ -926,13 +969,171 @@ int run_fit(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings*
     hipLaunchKernelGGL(k_finalize, dim3(nblk), dim3(64), 0, s, d, static_cast<FitRecord*>(ctx->rec.p));
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(ctx->hrec.p, ctx->rec.p, sizeof(FitRecord) * nblk, hipMemcpyDeviceToHost, s));
-    int* herr = reinterpret_cast<int*>(static_cast<DeState*>(ctx->hstate.p) + 4 * nblk);
+    int* herr = reinterpret_cast<int*>(static_cast<DeState*>(ctx->hstate.p) + 4 * nall);
     HIPCHK(hipMemcpyAsync(herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (ctx->timing && (rc = collect_timing(ctx))) return rc;
     if (*herr) return fail(PT_EDEVICE, "persistent fit: a block's generation did not complete in time");
 
     const FitRecord* r = static_cast<const FitRecord*>(ctx->hrec.p);
+    for (int k = 0; k < nblk; ++k) (*rec)[idx[k]] = r[k];
+    return PT_OK;
+}
+
+// Generations per stop check of a node-weight fit with the window rule (fits
+// of the benchmark stop after 200 to 350 generations), and bytes its draws may
+// take.
+constexpr int kNodeCheck = 64;
+constexpr size_t kNodeDrawBytes = (size_t)256 << 20;
+
+// Fits of the blocks `idx` through node weights (plans[k] for idx[k]); rec[b]:
+// block b's record.
+int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<int>& idx,
+              const std::vector<NodePlan>& plans, const pt_de_settings* de, hipStream_t s,
+              std::vector<FitRecord>* rec) {
+    const int P = de->pop, nblk = (int)idx.size(), iters = de->max_gens + 1;
+    const bool window = de->rel_tol > 0;
+    int rc, maxK = 0, proj = 0, mom = 0;
+    size_t work = 0;
+    for (const NodePlan& p : plans) {
+        maxK = std::max(maxK, p.nd.K);
+        work += p.pts_doubles + p.s2_doubles + p.mom_doubles;
+    }
+    int chunk = ctx->timing ? 1 : std::min(node_chunk(P, maxK, ctx->lds_max), window ? kNodeCheck : iters);
+    chunk = std::min(chunk, std::max(16, (int)(kNodeDrawBytes / ((size_t)8 * P * nblk))));
+    const size_t draws = ((size_t)2 * chunk * P * sizeof(uint32_t) + 15) / 16 * 2;  // in doubles
+    const size_t fixed = kNodeWtsDoubles + kNodeNarDoubles + draws;
+    const size_t ndb = (sizeof(NodeDesc) * nblk + 255) & ~(size_t)255, bdb = sizeof(BlockDesc) * nblk;
+    if ((rc = ensure_state(ctx, nall, de)) || (rc = ctx->node_ws.ensure((work + fixed * nblk) * sizeof(double))) ||
+        (rc = ctx->node_desc.ensure(ndb + bdb)) || (rc = ctx->hnode.ensure(ndb + bdb)) ||
+        (rc = ctx->errflag.ensure(sizeof(int))))
+        return rc;
+    NodeDesc* hn = static_cast<NodeDesc*>(ctx->hnode.p);
+    BlockDesc* hb = reinterpret_cast<BlockDesc*>(static_cast<char*>(ctx->hnode.p) + ndb);
+    double* ws = static_cast<double*>(ctx->node_ws.p);
+    for (int k = 0; k < nblk; ++k) {
+        hb[k] = base_desc(blocks[idx[k]], de, 0, 0);
+        set_state(ctx, idx[k], de->max_gens, &hb[k]);
+        NodeDesc n = plans[k].nd;
+        n.proj_begin = proj;
+        n.mom_begin = mom;
+        proj += n.nproj;
+        mom += n.nmom;
+        auto take = [&](size_t doubles) {
+            double* p = ws;
+            ws += doubles;
+            return p;
+        };
+        n.draws = reinterpret_cast<uint32_t*>(take(draws));
+        n.wts = take(kNodeWtsDoubles);
+        n.nar = take(kNodeNarDoubles);
+        n.pts = take(plans[k].pts_doubles);
+        n.s2 = take(plans[k].s2_doubles);
+        n.mom = take(plans[k].mom_doubles);
+        hn[k] = n;
+    }
+    HIPCHK(hipMemcpyAsync(ctx->node_desc.p, hn, ndb + bdb, hipMemcpyHostToDevice, s));
+    const NodeDesc* nd = static_cast<const NodeDesc*>(ctx->node_desc.p);
+    const BlockDesc* bd = reinterpret_cast<const BlockDesc*>(static_cast<const char*>(ctx->node_desc.p) + ndb);
+    HIPCHK(node_project(nd, bd, nblk, proj, P, std::min(chunk, iters), chunk, s));
+    HIPCHK(node_moments(nd, bd, nblk, mom, s));
+    DeState* hst = static_cast<DeState*>(ctx->hstate.p);
+    auto stopped = [&](const DeState* h) {
+        for (int b : idx)
+            if (!h[b].done) return false;
+        return true;
+    };
+    bool all = false;
+    for (int c = 0; c * (int64_t)chunk < iters && !all; ++c) {
+        const int off = c * chunk, ngen = std::min(chunk, iters - off), next = std::min(chunk, iters - off - ngen);
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (ctx->timing) {
+            e0 = take_event(ctx);
+            e1 = take_event(ctx);
+            if (!e0 || !e1) return fail(PT_EDEVICE, "hipEventCreate failed");
+            HIPCHK(hipEventRecord(e0, s));
+        }
+        HIPCHK(node_fit(nd, bd, nblk, P, maxK, off, ngen, next, chunk, c & 1, s));
+        if (ctx->timing) {
+            HIPCHK(hipEventRecord(e1, s));
+            ctx->ev_pending.push_back({e0, e1});
+        }
+        ++ctx->last_fit_launches;
+        if (window && next && !ctx->timing) {
+            // as in the graph form: the state after chunk c - 1 is checked once
+            // chunk c is queued, so the device never idles for the check
+            HIPCHK(hipMemcpyAsync(hst + (c & 1) * nall, ctx->state.p, sizeof(DeState) * nall, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipEventRecord(ctx->ev_state[c & 1], s));
+            if (c >= 1) {
+                HIPCHK(hipEventSynchronize(ctx->ev_state[(c - 1) & 1]));
+                all = stopped(hst + ((c - 1) & 1) * nall);
+            }
+        }
+    }
+    hipLaunchKernelGGL(k_finalize, dim3(nblk), dim3(64), 0, s, bd, static_cast<FitRecord*>(ctx->rec.p));
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(ctx->hrec.p, ctx->rec.p, sizeof(FitRecord) * nblk, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if (ctx->timing && (rc = collect_timing(ctx))) return rc;
+    const FitRecord* r = static_cast<const FitRecord*>(ctx->hrec.p);
+    for (int k = 0; k < nblk; ++k) (*rec)[idx[k]] = r[k];
+    return PT_OK;
+}
+
+// Whether fits in this context may take node weights: the automatic launch
+// mode, and not with the per-sample FP64 cosine asked for.
+bool nodes_allowed(const pt_ctx* ctx) {
+    return ctx->launch_mode == PT_LAUNCH_AUTO && ctx->fp64_method == PT_FP64_AUTO;
+}
+
+// direct: no node weights (the autotuner, which times the other forms).
+int run_fit(pt_ctx* ctx, const pt_block* given, int nblk, const pt_de_settings* de, void* hip_stream, pt_fit* out,
+            bool direct = false) {
+    int rc = check_de(de);
+    if (rc) return rc;
+    if (nblk < 1 || nblk > 4096) return fail(PT_EINVAL, "nblk = %d outside [1, 4096]", nblk);
+    if (!out) return fail(PT_EINVAL, "out is null");
+    for (int b = 0; b < nblk; ++b)
+        if ((rc = check_block(&given[b], b))) return rc;
+    HIPCHK(hipSetDevice(ctx->device));
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    // the arithmetic and geometry the blocks' samples are evaluated in
+    Plan pl;
+    std::vector<char> phasor;
+    int nphasor = 0;
+    if ((rc = plan_arithmetic(ctx, given, nblk, de, &pl, &phasor, &nphasor))) return rc;
+    std::vector<pt_block> blocks;
+    if ((rc = stage_blocks(ctx, given, nblk, s, &blocks))) return rc;
+    std::vector<int> by_nodes, by_samples;
+    std::vector<NodePlan> plans;
+    for (int b = 0; b < nblk; ++b) {
+        NodePlan p;
+        if (!direct && nodes_allowed(ctx) && node_plan(blocks[b], block_ref(&blocks[b]), de->pop, &p) &&
+            node_chunk(de->pop, p.nd.K, ctx->lds_max) >= 16) {
+            by_nodes.push_back(b);
+            plans.push_back(p);
+        } else {
+            by_samples.push_back(b);
+        }
+    }
+    std::vector<FitRecord> rec(nblk);
+    ctx->last_fit_launches = 0;
+    if (!by_nodes.empty()) {
+        if ((rc = run_nodes(ctx, blocks.data(), nblk, by_nodes, plans, de, s, &rec))) return rc;
+        for (int b : by_nodes)  // abandoned: more signal to noise than the weights carry
+            if (rec[b].flags & kFlagNodeAbort) by_samples.push_back(b);
+        std::sort(by_samples.begin(), by_samples.end());
+    }
+    if (!by_samples.empty()) {
+        const int64_t node_launches = ctx->last_fit_launches;
+        if ((rc = run_direct(ctx, blocks.data(), nblk, by_samples, de, s, &rec))) return rc;
+        ctx->last_fit_launches += node_launches;
+    }
+    if (!by_nodes.empty()) {
+        ctx->last_launch = PT_LAUNCH_GRAPH;
+        ctx->last_arith = nphasor == 0 || nphasor == nblk ? pl.mode : kModePhasor;
+        ctx->last_geo = pl.geo;
+    }
     ctx->last_nblk = nblk;
     ctx->last_P = de->pop;
     ctx->last_maxg = de->max_gens;
@@ -940,15 +1141,15 @@ int run_fit(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_settings*
     for (int b = 0; b < nblk; ++b) {
         pt_fit& f = out[b];
         std::memset(&f, 0, sizeof f);
-        for (int j = 0; j < PT_NSLOT; ++j) f.coef[j] = r[b].x[j];
-        f.objective = r[b].f;
-        f.generations = r[b].gens;
-        f.flags = r[b].flags;
-        f.ref = block_ref(&blocks[b]);
-        f.t_left = (0.0 - f.ref) / blocks[b].fs;
-        f.t_right = ((double)blocks[b].n - f.ref) / blocks[b].fs;
+        for (int j = 0; j < PT_NSLOT; ++j) f.coef[j] = rec[b].x[j];
+        f.objective = rec[b].f;
+        f.generations = rec[b].gens;
+        f.flags = rec[b].flags;
+        f.ref = block_ref(&given[b]);
+        f.t_left = (0.0 - f.ref) / given[b].fs;
+        f.t_right = ((double)given[b].n - f.ref) / given[b].fs;
         derive(&f);
-        ctx->last_gens[b] = r[b].gens;
+        ctx->last_gens[b] = rec[b].gens;
     }
     return PT_OK;
 }
@@ -989,6 +1190,8 @@ int pt_ctx_create(int device, pt_ctx** out) {
     int lds_max = 0;
     if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess)
         lds_max = 65536;
+    c->lds_max = lds_max;
+    HIPCHK(node_setup(lds_max));
     // 16 bytes of LDS per snippet sample plus the kernel's 1 KiB of reduction space
     for (int lg = kSeedMaxLog; lg >= 6; --lg)
         if ((16 << lg) + 1024 <= lds_max) {
@@ -1016,11 +1219,12 @@ void pt_ctx_destroy(pt_ctx* ctx) {
     }
     DevBuf* bufs[] = {&ctx->desc,    &ctx->pop,      &ctx->trial,   &ctx->fpop,  &ctx->partials, &ctx->hist,
                       &ctx->state,   &ctx->rec,      &ctx->staging, &ctx->eval_pop, &ctx->tune_block, &ctx->errflag,
-                      &ctx->sync,    &ctx->seed_out, &ctx->seed_stage};
+                      &ctx->sync,    &ctx->seed_out, &ctx->seed_stage, &ctx->node_desc, &ctx->node_ws};
     for (DevBuf* b : bufs) b->release();
     ctx->hdesc.release();
     ctx->hrec.release();
     ctx->hseed.release();
+    ctx->hnode.release();
     ctx->hstate.release();
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
@@ -1136,7 +1340,9 @@ static int eval_setup(pt_ctx* ctx, const pt_block* block, const double* pop, int
     ext.apply(blk);
     pt_de_settings de = eval_settings(P, precision, objective);
     void* old_desc = ctx->desc.p;
-    if ((rc = prepare(ctx, &blk, 1, &de, s, pl, false))) return rc;
+    std::vector<pt_block> staged;
+    if ((rc = stage_blocks(ctx, &blk, 1, s, &staged))) return rc;
+    if ((rc = prepare(ctx, staged.data(), 1, {0}, &de, s, pl, false))) return rc;
     if (ctx->desc.p != old_desc) ctx->drop_graphs();
     const BlockDesc* hd = static_cast<const BlockDesc*>(ctx->hdesc.p);
     // (a kernel, not a strided 2-D copy: those have returned wrong data under
@@ -1659,7 +1865,7 @@ int pt_ctx_autotune(pt_ctx* ctx, int64_t n, int P, int precision, void* hip_stre
             double ms = 1e30;
             for (int rep = 0; rep < 3 && !rc; ++rep) {
                 const auto t0 = std::chrono::steady_clock::now();
-                rc = run_fit(ctx, &b, 1, &de, hip_stream, &fit);
+                rc = run_fit(ctx, &b, 1, &de, hip_stream, &fit, true);
                 const auto t1 = std::chrono::steady_clock::now();
                 if (rep) ms = std::min(ms, std::chrono::duration<double, std::milli>(t1 - t0).count());
             }
@@ -1717,6 +1923,12 @@ struct pt_server {
         pt_block blk{};
         DevBuf samples, pop, trial, fpop, partials, hist, state;  // two slots each of pop ... state
         int lead = 0;  // leading-step form: launches this block has run since (re)initialisation
+        // node-weight fits: the block's plan, its weights and draws (two chunks),
+        // and the half of the draws the next launch reads
+        bool nodes = false;
+        NodePlan plan{};
+        DevBuf node;
+        int parity = 0;
     };
     struct Pending {
         uint64_t ticket;
@@ -1743,6 +1955,9 @@ struct pt_server {
     uint64_t next_ticket = 1;
     DevBuf desc, rec;
     PinBuf hdesc, hrec, hstate;
+    int chunk = 0;  // generations per node-weight launch
+    DevBuf node_desc, node_ws;
+    PinBuf hnode;
     std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
     double clock() const {
         return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -1786,6 +2001,13 @@ int slot_mode(const pt_server* sv, const pt_block& b) {
                      box_max(b.box, 6))
                ? kModePhasor
                : kModePoly;
+}
+
+// How a block's fit runs, from its own box only: through node weights, or by
+// evaluating its samples in the arithmetic of slot_mode.
+void slot_form(const pt_server* sv, pt_server::Slot& sl) {
+    sl.mode = slot_mode(sv, sl.blk);
+    sl.nodes = nodes_allowed(sv->ctx) && sv->chunk >= 16 && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan);
 }
 
 // Warm box of a track's next block around the prediction from its last fit.
@@ -1886,7 +2108,7 @@ int server_admit(pt_server* sv, hipStream_t s) {
                 }
             sl.warm = 2;
         }
-        sl.mode = slot_mode(sv, sl.blk);
+        slot_form(sv, sl);
         sl.attempts = 1;
         sl.active = true;
         sl.fresh = true;
@@ -1901,6 +2123,62 @@ int server_admit(pt_server* sv, hipStream_t s) {
         // the host copy can go once the stream has consumed it
         HIPCHK(hipStreamSynchronize(s));
         it = sv->pending.erase(it);
+    }
+    return PT_OK;
+}
+
+// One step of the node-weight blocks, act[0 .. nn) (the first nn_fresh new;
+// dd: the step's descriptors on the device): K generations, in launches of up
+// to sv->chunk.
+int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, const BlockDesc* dd, int K,
+                 hipStream_t s, int* launches) {
+    const int P = sv->cfg.de.pop, chunk = std::min(sv->chunk, K);
+    const size_t draws = ((size_t)2 * chunk * P * sizeof(uint32_t) + 15) / 16 * 2;  // in doubles
+    size_t work = 0;
+    int maxK = 0, proj = 0, mom = 0, rc;
+    for (int q = 0; q < nn; ++q) {
+        const NodePlan& p = sv->slots[act[q]].plan;
+        maxK = std::max(maxK, p.nd.K);
+        if (q < nn_fresh) work += p.pts_doubles + p.s2_doubles + p.mom_doubles;
+    }
+    if ((rc = sv->node_desc.ensure(sizeof(NodeDesc) * nn)) || (rc = sv->hnode.ensure(sizeof(NodeDesc) * nn)) ||
+        (rc = sv->node_ws.ensure(work * sizeof(double))))
+        return rc;
+    NodeDesc* hn = static_cast<NodeDesc*>(sv->hnode.p);
+    double* ws = static_cast<double*>(sv->node_ws.p);
+    for (int q = 0; q < nn; ++q) {
+        pt_server::Slot& sl = sv->slots[act[q]];
+        NodeDesc n = sl.plan.nd;
+        if (q < nn_fresh) {
+            if ((rc = sl.node.ensure((kNodeWtsDoubles + kNodeNarDoubles + draws) * sizeof(double)))) return rc;
+            sl.parity = 0;
+            n.proj_begin = proj;
+            n.mom_begin = mom;
+            proj += n.nproj;
+            mom += n.nmom;
+            n.pts = ws;
+            n.s2 = n.pts + sl.plan.pts_doubles;
+            n.mom = n.s2 + sl.plan.s2_doubles;
+            ws = n.mom + sl.plan.mom_doubles;
+        }
+        n.wts = static_cast<double*>(sl.node.p);
+        n.nar = n.wts + kNodeWtsDoubles;
+        n.draws = reinterpret_cast<uint32_t*>(n.nar + kNodeNarDoubles);
+        n.g0 = sl.fresh ? 0 : sl.gen;
+        n.parity = sl.parity;
+        hn[q] = n;
+    }
+    HIPCHK(hipMemcpyAsync(sv->node_desc.p, hn, sizeof(NodeDesc) * nn, hipMemcpyHostToDevice, s));
+    const NodeDesc* nd = static_cast<const NodeDesc*>(sv->node_desc.p);
+    if (nn_fresh) {
+        HIPCHK(node_project(nd, dd, nn_fresh, proj, P, chunk, chunk, s));
+        HIPCHK(node_moments(nd, dd, nn_fresh, mom, s));
+    }
+    *launches = 0;
+    for (int off = 0; off < K; off += chunk, ++*launches) {
+        const int ngen = std::min(chunk, K - off), left = K - off - ngen;
+        // the last launch of the step makes the draws of the next step's first
+        HIPCHK(node_fit(nd, dd, nn, P, maxK, off, ngen, left ? std::min(chunk, left) : chunk, chunk, *launches & 1, s));
     }
     return PT_OK;
 }
@@ -1989,6 +2267,7 @@ int pt_server_create(pt_ctx* ctx, const pt_server_config* cfg, pt_server** out) 
     if (sv->cfg.max_attempts == 0) sv->cfg.max_attempts = 1;
     sv->geo = cfg->spl ? Geometry{cfg->spl, cfg->cpg} : default_geometry(400000, cfg->de.pop);
     sv->lead = ctx->step_fusion == PT_FUSION_LEAD;
+    sv->chunk = node_chunk(cfg->de.pop, kNodeMaxK, ctx->lds_max);
     sv->slots.resize(cfg->max_slots);
     *out = sv.release();
     return PT_OK;
@@ -1999,9 +2278,12 @@ void pt_server_destroy(pt_server* sv) {
     (void)hipSetDevice(sv->ctx->device);
     (void)hipDeviceSynchronize();
     for (auto& sl : sv->slots) {
-        DevBuf* b[] = {&sl.samples, &sl.pop, &sl.trial, &sl.fpop, &sl.partials, &sl.hist, &sl.state};
+        DevBuf* b[] = {&sl.samples, &sl.pop, &sl.trial, &sl.fpop, &sl.partials, &sl.hist, &sl.state, &sl.node};
         for (DevBuf* x : b) x->release();
     }
+    sv->node_desc.release();
+    sv->node_ws.release();
+    sv->hnode.release();
     sv->desc.release();
     sv->rec.release();
     sv->hdesc.release();
@@ -2050,11 +2332,13 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     int rc = server_admit(sv, s);
     if (rc) return rc;
-    // active slots, grouped by objective kernel (arithmetic, dtype, slope)
+    // active slots: those fitted through node weights first (new ones leading),
+    // then the others grouped by objective kernel (arithmetic, dtype, slope)
     auto kernel_key = [&](int k) {
         const pt_server::Slot& sl = sv->slots[k];
         const bool slope = sl.blk.box.lo[5] != 0.0 || sl.blk.box.hi[5] != 0.0;
-        return std::make_tuple(sl.mode, sl.blk.dtype, (int)slope);
+        if (sl.nodes) return std::make_tuple(-1, (int)!sl.fresh, 0);
+        return std::make_tuple(sl.mode, (int)sl.blk.dtype, (int)slope);
     };
     std::vector<int> act;
     for (int k = 0; k < (int)sv->slots.size(); ++k)
@@ -2092,9 +2376,22 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
     };
     std::vector<Launch> launches;
     bool any_fresh = false;
+    int nn = 0, nn_fresh = 0;  // node-weight blocks, and the new ones among them
     for (int q = 0; q < nb; ++q) {
         pt_server::Slot& sl = sv->slots[act[q]];
         const pt_block& B = sl.blk;
+        if (sl.nodes) {
+            BlockDesc d = base_desc(B, &de, 0, 0);
+            d.pop = static_cast<double*>(sl.pop.p);
+            d.trial = static_cast<double*>(sl.trial.p);
+            d.fpop = static_cast<double*>(sl.fpop.p);
+            d.hist = static_cast<double*>(sl.hist.p);
+            d.st = static_cast<DeState*>(sl.state.p);
+            hd[q] = d;
+            ++nn;
+            nn_fresh += sl.fresh;
+            continue;
+        }
         if (launches.empty() || kernel_key(act[q]) != kernel_key(act[launches.back().first])) {
             const auto key = kernel_key(act[q]);
             launches.push_back({q, 0, 0, objective_kernel(std::get<1>(key), sv->geo, std::get<0>(key),
@@ -2156,12 +2453,17 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
     HIPCHK(hipMemcpyAsync(sv->desc.p, hd, sizeof(BlockDesc) * nb, hipMemcpyHostToDevice, s));
     const BlockDesc* dd = static_cast<const BlockDesc*>(sv->desc.p);
     const size_t de_lds = (size_t)P * kSlots * 8 + (size_t)de_threads * (8 + 8 + 4);
+    const int K = sv->cfg.gens_per_step;
+    int node_launches = 0;
+    if (nn) {
+        if ((rc = server_nodes(sv, act, nn, nn_fresh, dd, K, s, &node_launches))) return rc;
+    }
+    const int nd = nb - nn;  // blocks whose samples are evaluated
     if (any_fresh) {
-        hipLaunchKernelGGL(k_de_init_fresh, dim3(nb), dim3(de_threads), 0, s, dd);
+        hipLaunchKernelGGL(k_de_init_fresh, dim3(nd), dim3(de_threads), 0, s, dd + nn);
         HIPCHK(hipGetLastError());
     }
-    const int K = sv->cfg.gens_per_step;
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; k < K && nd; ++k) {
         if (lead) {
             for (const Launch& L : launches) {
                 const int grid = (L.units + L.count + 7) / 8 * 8;  // plus one bookkeeping unit per block
@@ -2174,14 +2476,14 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
             const int grid = (L.units + 7) / 8 * 8;
             launch_objective(L.k, grid, 0, s, dd + L.first, L.count, L.units, 0);
         }
-        hipLaunchKernelGGL(k_de_step, dim3(nb), dim3(de_threads), de_lds, s, dd);
+        hipLaunchKernelGGL(k_de_step, dim3(nd), dim3(de_threads), de_lds, s, dd + nn);
     }
     HIPCHK(hipGetLastError());
     hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(64), 0, s, dd, static_cast<FitRecord*>(sv->rec.p));
     HIPCHK(hipGetLastError());
     DeState* hst = static_cast<DeState*>(sv->hstate.p);
     for (int q = 0; q < nb; ++q)
-        HIPCHK(hipMemcpyAsync(hst + 2 * q, sv->slots[act[q]].state.p, (lead ? 2 : 1) * sizeof(DeState),
+        HIPCHK(hipMemcpyAsync(hst + 2 * q, sv->slots[act[q]].state.p, (lead && q >= nn ? 2 : 1) * sizeof(DeState),
                               hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(sv->hrec.p, sv->rec.p, sizeof(FitRecord) * nb, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -2195,14 +2497,24 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         // the block's current state: in the leading-step form the slot holding
         // the stop, else the one the next launch would read
         const int L0 = sl.fresh ? 0 : sl.lead;
-        const DeState& cur = !lead ? hst[2 * q]
+        const DeState& cur = !lead || sl.nodes ? hst[2 * q]
                              : hst[2 * q].done ? hst[2 * q]
                              : hst[2 * q + 1].done ? hst[2 * q + 1]
                                                    : hst[2 * q + ((L0 + K) & 1)];
         sl.fresh = false;
         sl.gen = cur.gen;
         sl.lead = L0 + K;
+        if (sl.nodes) sl.parity ^= node_launches & 1;
         if (!cur.done) {
+            ++still;
+            continue;
+        }
+        if (sl.nodes && (cur.flags & kFlagNodeAbort)) {
+            // more signal to noise than node weights carry: the same fit again
+            // over the samples
+            sl.nodes = false;
+            sl.fresh = true;
+            sl.gen = 0;
             ++still;
             continue;
         }
@@ -2242,7 +2554,7 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         if (failed && sl.attempts < cf.max_attempts) {
             // Sec. 3.1.1: enlarge the range and search again
             enlarge_box(sl.blk.box, cf.enlarge);
-            sl.mode = slot_mode(sv, sl.blk);
+            slot_form(sv, sl);
             ++sl.attempts;
             sl.fresh = true;
             sl.gen = 0;

@@ -36,7 +36,8 @@ from collections import defaultdict
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1906_10598_amd", "csrc")
 # every source a kernel's code or launch depends on
-KERNEL_SOURCES = ("kernels.h", "device.h", "cospoly.h", "instances.h", "instances.hip", "phasetrack.hip")
+KERNEL_SOURCES = ("kernels.h", "device.h", "cospoly.h", "instances.h", "instances.hip", "nodes.h",
+                  "nodes.hip", "phasetrack.hip")
 CAL_BYTES = 256 * 1024 * 1024
 # counters whose per-dispatch medians go on the `counters:` line
 COUNTER_KEYS = {"SQ_INSTS_VALU": "valu", "SQ_WAVES": "waves",
