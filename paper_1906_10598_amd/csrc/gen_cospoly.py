@@ -5,8 +5,8 @@ The device kernels reduce the phase to turns r in [-1/2, 1/2] exactly
 polynomial p fitted on u = r^2 in [0, 1/4] at Chebyshev nodes (mpmath
 chebyfit, 50 digits).  Degree 10 in u gives an approximation error of
 3.3e-17 (below FP64 rounding), degree 9 gives 6.2e-15; degree 6 gives 1.1e-8
-(below FP32 rounding).  Phases known to lie within an eighth of a turn take
-degree 6 in FP64.
+(below FP32 rounding).  Phases known to lie within 1/8 or 1/48 of a
+turn take degree 6 or 4 in FP64.
 
 Run:  python gen_cospoly.py  (rewrites cospoly.h next to this script).
 """
@@ -35,6 +35,8 @@ def main():
     s64, es64 = fit(10, odd=True)
     cn, ecn = fit(6, rmax=mpmath.mpf(1) / 8)
     sn, esn = fit(6, odd=True, rmax=mpmath.mpf(1) / 8)
+    c8, ec8 = fit(4, rmax=mpmath.mpf(1) / 48)
+    s8, es8 = fit(4, odd=True, rmax=mpmath.mpf(1) / 48)
     p32, e32 = fit(6)
     lines = [
         "// Generated by gen_cospoly.py -- do not edit.",
@@ -57,6 +59,11 @@ def main():
     lines += [f"    {c.hex()},  // {c:.17e}" for c in cn]
     lines += ["};", "constexpr double kSinNar64[] = {"]
     lines += [f"    {c.hex()},  // {c:.17e}" for c in sn]
+    lines += ["};", f"// |r| <= 1/48, degree 4 in u: errors {ec8:.2e}, {es8:.2e}.",
+              f"constexpr int kNar8Deg64 = {len(c8) - 1};", "constexpr double kCosNar8[] = {"]
+    lines += [f"    {c.hex()},  // {c:.17e}" for c in c8]
+    lines += ["};", "constexpr double kSinNar8[] = {"]
+    lines += [f"    {c.hex()},  // {c:.17e}" for c in s8]
     lines += ["};", f"constexpr int kCosDeg32 = {len(p32) - 1};", "constexpr float kCos32[] = {"]
     for c in p32:
         cf = float(mpmath.mpf(c))

@@ -18,8 +18,8 @@
 //
 // Measured against one launch per generation over all samples (each generation
 // a chain of ~9 us in its leading-step form; same machine): the 400 000-sample
-// block, P = 40, 2000 generations 18.2 -> 2.21 ms; the quartic 1e6-sample block
-// 39.5 -> 2.81 ms; 64 uneven blocks, 1500 generations 172 -> 2.88 ms (the
+// block, P = 40, 2000 generations 18.1 -> 1.99 ms; the quartic 1e6-sample block
+// 39.4 -> 2.33 ms; 64 uneven blocks, 1500 generations 205 -> 2.02 ms (the
 // blocks' generations then run on 64 compute units at once instead of sharing
 // the chip's issue slots sample by sample).
 //
@@ -42,12 +42,15 @@
 namespace pt {
 
 constexpr int kNodeMaxK = 512;    // largest node count of a block
-constexpr int kNodeMaxP = 240;    // largest population (four members per row of 16 lanes, 15 waves)
-constexpr int kNodePts = 16;      // nodes per tile, and of the narrow set
+constexpr int kNodeMaxP = 240;    // largest population (two members per octet of lanes, 15 waves)
+constexpr int kNodePts = 16;      // nodes per tile
 constexpr int kNodeRun = 4096;    // samples a projection workgroup takes at a time (16 per lane)
 constexpr int kNodeGroup = 128;   // points per moments workgroup
 constexpr int kNodeRing = 512;    // best-so-far values k_node_fit keeps in LDS for the window rule
-constexpr int kNodeNarrow = 5 * kNodePts + 2 * 8;  // doubles of a saved narrow set: weights, centre, limits
+constexpr int kNodeLevelHead = 48;  // doubles before a saved re-expanded set's weights
+// largest |delta| (turns) of the sets of 16 and 8 nodes: the range of their
+// sine and cosine polynomials
+constexpr double kNodeTurns16 = 1.0 / 8, kNodeTurns8 = 1.0 / 48;
 // chi-square is taken as S2 - ..., so it carries rounding of ~1e-16 S2: a fit
 // whose best falls below kNodeCancel * S2 (30 dB of signal to noise) is
 // abandoned and run through the per-sample objective
@@ -76,8 +79,8 @@ struct NodeDesc {
     double* s2;        // nproj partial sums of s^2
     double* mom;       // nmom x K x 4 partial moments
     double* wts;       // K x 4 weights, then S2
-    double* nar;       // kNodeNarrow doubles and 4 ints of the narrow set
-    uint32_t* draws;   // two halves of chunk x P packed draws
+    double* nar;       // the re-expanded set between launches
+    uint64_t* draws;   // two halves of chunk x P packed draws
 };
 
 struct NodePlan {
@@ -85,7 +88,7 @@ struct NodePlan {
     size_t pts_doubles, s2_doubles, mom_doubles;  // working space of the projection
 };
 constexpr size_t kNodeWtsDoubles = 4 * kNodeMaxK + 2;
-constexpr size_t kNodeNarDoubles = kNodeNarrow + 2;
+constexpr size_t kNodeNarDoubles = kNodeLevelHead + 5 * (kNodeMaxK / 8 * 5);
 
 // Whether a block's fits go through node weights, and its plan: depends on
 // the block (length, rate, reference, box) and the population size only.
@@ -102,7 +105,7 @@ hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int t
                         hipStream_t s);
 hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, hipStream_t s);
 hipError_t node_fit(const NodeDesc* nd, const BlockDesc* bd, int nblk, int P, int maxK, int off, int ngen, int next_ngen,
-                    int chunk, int flip, hipStream_t s);
+                    int chunk, int flip, bool cor, hipStream_t s);
 hipError_t node_setup(int lds_max);  // once per device
 
 }  // namespace pt

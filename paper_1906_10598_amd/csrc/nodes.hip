@@ -4,8 +4,15 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.h"
+
+// Every operation here rounds as written: a fit runs the same objective through
+// several inlined copies (full and re-expanded sets, first and later
+// generations), which must agree bit for bit, and a sum over lanes must come
+// out the same in all of them (a product fused into its first step would not).
+#pragma clang fp contract(off)
 
 namespace pt {
 namespace {
@@ -35,12 +42,27 @@ __device__ __forceinline__ void row_sums(double (&v)[N]) {
     sum_step<3>(v);
 }
 
-// Lane L of each row of 16, in every lane of the row.
-template <int L>
-__device__ __forceinline__ double row_bcast(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + L, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + L, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
+// Lane J of each octet (lanes 8 q .. 8 q + 7), in every lane of the octet: a
+// broadcast over the row of 16, then over its upper half.
+template <int J>
+__device__ __forceinline__ double oct_bcast(double v) {
+    const long long x = __double_as_longlong(v);
+    long long a = __builtin_amdgcn_mov_dpp(x, 0x150 + J, 0xF, 0xF, false);
+    a = __builtin_amdgcn_update_dpp(a, x, 0x158 + J, 0xF, 0xC, false);
+    return __longlong_as_double(a);
+}
+
+// Sum over the octet, in every lane of it (pairs, quads, the two quads).
+__device__ __forceinline__ double oct_sum(double v) {
+    auto moved = [](double x, auto ctrl) {
+        constexpr int c = decltype(ctrl)::value;
+        return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), c, 0xF, 0xF, false),
+                                __builtin_amdgcn_mov_dpp(__double2loint(x), c, 0xF, 0xF, false));
+    };
+    v += moved(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
+    v += moved(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
+    v += moved(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    return v;
 }
 
 template <bool MAX>
@@ -70,13 +92,16 @@ __device__ __forceinline__ int node_block_of(const NodeDesc* nd, int nblk, int w
     return lo;
 }
 
-// Packed draws of one member: r1, r2, r3 in bytes 0-2, the slots the binomial
-// crossover takes from the mutant in byte 3.
-__device__ __forceinline__ uint32_t node_pack(const BlockDesc* d, const Draws& w) {
+// Packed draws of one member: the byte offsets of rows r1, r2 and r3 in 16 bits
+// each, then the slots the binomial crossover takes from the mutant.
+__device__ __forceinline__ uint64_t node_pack(const BlockDesc* d, const Draws& w) {
     uint32_t m = 0;
     for (int a = 0; a < d->D; ++a)
         if ((w.cross >> a) & 1u) m |= 1u << d->act[a];
-    return (uint32_t)w.r1 | ((uint32_t)w.r2 << 8) | ((uint32_t)w.r3 << 16) | (m << 24);
+    constexpr int kRow = kStride * sizeof(double);
+    static_assert(kNodeMaxP * kRow <= 65536, "row offsets fit 16 bits");
+    return (uint64_t)((uint32_t)(w.r1 * kRow) | ((uint32_t)(w.r2 * kRow) << 16)) |
+           ((uint64_t)((uint32_t)(w.r3 * kRow) | (m << 16)) << 32);
 }
 
 // The draws of generations g .. g + ngen - 1 of every member, by workgroups
@@ -275,52 +300,71 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
 // ---------------------------------------------------------------------------
 // The fit: one workgroup per block runs `ngen` generations.
 //
-// Member m belongs to a row of 16 lanes (waves 0 .. W - 1, four rows each, NM
-// members per row): lanes 0-6 of the row hold the member's slots, build its
-// trial from the rows of the previous generation in LDS and turn it into the
-// coefficients of delta; all 16 lanes then evaluate delta, exp(i delta) and
-// the weighted sums at the nodes k = lane, lane + 16, ... and the row adds up
-// by DPP moves, so selection needs no exchange between waves.  One barrier
-// per generation separates writing the selected rows from reading them (two
-// copies alternate).  Wave W keeps the books one generation behind: best
-// member, history, stop rule.
+// Member m belongs to an octet of lanes (waves 0 .. W - 1, eight octets each, NM
+// members per octet): lane j < 7 holds the member's slot j, builds its trial
+// coordinate from the rows of the previous generation in LDS and turns it into
+// a coefficient of delta; all eight lanes then evaluate delta, exp(i delta) and
+// the weighted sums at the nodes k = lane, lane + 8, ... and add up by DPP
+// moves, so selection needs no exchange between octets.  One barrier per
+// generation separates writing the selected rows from reading them (two copies
+// alternate).  Wave W keeps the books one generation behind: best member,
+// history, stop rule.
 //
-// Once the population has drawn together so far that every trial stays
-// within an eighth of a turn of the best member's phase, the weights are
-// re-expanded about that member's phase on 16 nodes (relevel): one node per
-// lane, held in registers, no phase reduction, a shorter sine and cosine.  A
-// trial outside the re-expansion's limits is evaluated on the full set.
+// As the population draws together fewer nodes do: every 16th generation the
+// bookkeeping wave measures its spread, and when markedly fewer nodes would
+// carry any trial it asks for the weights to be re-expanded about the best
+// member's phase (relevel), first on any smaller number of nodes, at last on 16
+// and then 8 (kinds 1 and 2), which each lane holds in registers, two or one a
+// lane; there the phase difference needs no reduction and a shorter sine and
+// cosine do.  A trial outside the limits of the re-expansion is evaluated on
+// the full set.
 //
 // The step of Table 4 (selection, random draws, bound rule, stop rule) is that
 // of de_step_body.
 // ---------------------------------------------------------------------------
+constexpr int kRowD = kStride;  // doubles of a member's row in LDS: seven slots, then its objective
+
 struct FitLds {
-    double *xs, *fs, *zw, *un, *nar, *scr, *ring;
-    uint32_t* dr;
+    double *xs;        // two generations of P rows
+    double *zw, *un;   // full node set: -2 Z and W (4 doubles a node), u
+    double *lz, *lu;   // re-expanded set
+    double *scr;       // 4 doubles a node
+    double *ring;      // best-so-far values
+    uint64_t* dr;      // draws of the launch's generations
 };
 
+// largest re-expanded set, for a full set of K nodes
+__host__ __device__ inline int level_cap(int K) { return K <= 2 * kNodePts ? kNodePts : K / 8 * 5; }
+
 __host__ __device__ inline size_t fit_lds_doubles(int P, int maxK) {
-    return (size_t)((2 * P * kSlots + 1) & ~1) + ((2 * P + 1) & ~1) + 9 * (size_t)maxK + 5 * kNodePts + kNodeRing;
+    return (size_t)2 * P * kRowD + 9 * (size_t)maxK + 5 * (size_t)level_cap(maxK) + kNodeRing;
 }
 
 __device__ __forceinline__ FitLds fit_lds(double* base, int P, int maxK) {
     FitLds l;
     l.xs = base;
-    l.fs = l.xs + ((2 * P * kSlots + 1) & ~1);
-    l.zw = l.fs + ((2 * P + 1) & ~1);
+    l.zw = l.xs + 2 * P * kRowD;
     l.scr = l.zw + 4 * maxK;
-    l.un = l.scr + 4 * maxK;
-    l.nar = l.un + maxK;
-    l.ring = l.nar + 5 * kNodePts;
-    l.dr = reinterpret_cast<uint32_t*>(l.ring + kNodeRing);
+    l.lz = l.scr + 4 * maxK;
+    l.un = l.lz + 4 * level_cap(maxK);
+    l.lu = l.un + maxK;
+    l.ring = l.lu + level_cap(maxK);
+    l.dr = reinterpret_cast<uint64_t*>(l.ring + kNodeRing);
     return l;
 }
 
+// A re-expanded node set.
+struct Level {
+    double mid[8], lim[8];  // per slot: centre, and the distance a trial may lie from it
+    int K, kind;            // nodes (0: none yet, the full set); kind 1, 2: 16 or 8 in registers
+    int pend;               // generation before which it takes effect, -1: in effect
+    int pad;
+};
+
 struct FitShared {
-    double mid[8], lim[8];  // centre and limits of the narrow set, per slot
+    Level lev, next;  // in effect, and asked for (next.pend >= 0)
     double S2, best_f;
-    int stop[2];            // DeState flags of a stop, by generation parity
-    int pend;               // generation before which the weights are re-expanded, -1: none
+    int stop[2];      // DeState flags of a stop, by generation parity
     int best, stop_gen;
 };
 
@@ -333,13 +377,13 @@ struct NodeCand {
 template <bool SLOPE, bool QUART>
 __device__ __forceinline__ NodeCand node_cand(double dj) {
     NodeCand q;
-    q.A = row_bcast<0>(dj);
-    q.p0 = row_bcast<1>(dj);
-    q.p1 = row_bcast<2>(dj);
-    q.p2 = row_bcast<3>(dj);
-    q.p3 = row_bcast<4>(dj);
-    q.B = SLOPE ? row_bcast<5>(dj) : 0.0;
-    q.p4 = QUART ? row_bcast<6>(dj) : 0.0;
+    q.p3 = oct_bcast<4>(dj);
+    q.p4 = QUART ? oct_bcast<6>(dj) : 0.0;
+    q.p2 = oct_bcast<3>(dj);
+    q.p1 = oct_bcast<2>(dj);
+    q.p0 = oct_bcast<1>(dj);
+    q.A = oct_bcast<0>(dj);
+    q.B = SLOPE ? oct_bcast<5>(dj) : 0.0;
     return q;
 }
 
@@ -353,75 +397,68 @@ __device__ __forceinline__ double node_delta(const NodeCand& q, double u) {
 
 // One node's terms: a1 += amp Re(-2 Z e), a2 += s t with t = Wr s + Wi c
 // (Re(W e^2) = Wr - 2 s t), or with a slope amp^2 Re(W e^2).
-template <bool SLOPE>
+template <bool SLOPE, bool COR>
 __device__ __forceinline__ void node_terms(const NodeCand& q, double u, double c, double s, double zr, double zi,
                                            double wr, double wi, double& a1, double& a2) {
-    const double t = __fma_rn(wr, s, wi * c);
     if constexpr (SLOPE) {
         const double amp = __fma_rn(q.B, u, q.A);
         a1 = __fma_rn(amp, __fma_rn(zr, c, -(zi * s)), a1);
-        a2 = __fma_rn(amp * amp, __fma_rn(-2.0 * s, t, wr), a2);
+        if constexpr (!COR) a2 = __fma_rn(amp * amp, __fma_rn(-2.0 * s, __fma_rn(wr, s, wi * c), wr), a2);
     } else {
         a1 = __fma_rn(zr, c, __fma_rn(-zi, s, a1));
-        a2 = __fma_rn(s, t, a2);
+        if constexpr (!COR) a2 = __fma_rn(s, __fma_rn(wr, s, wi * c), a2);
     }
 }
 
-// Objective from a row's sums.
-template <bool SLOPE>
-__device__ __forceinline__ double node_objective(const NodeDesc* nd, const NodeCand& q, double a1, double a2, bool cor,
-                                                 double S2, double energy0, double N) {
-    double v[1];
-    if (cor)
-        v[0] = SLOPE ? a1 : q.A * a1;
-    else
-        v[0] = SLOPE ? __fma_rn(0.5, a2, a1) : q.A * __fma_rn(-q.A, a2, a1);
-    row_sums(v);
+// Objective from an octet's sums; en: half of (N + sum Wr).
+template <bool SLOPE, bool COR>
+__device__ __forceinline__ double node_objective(const NodeDesc* nd, const NodeCand& q, double a1, double a2, double S2,
+                                                 double en, double N) {
     // correlation objective, Eq. (2-2-5): F = 1 / (arctan(C) + pi/2)
-    if (cor) return 1.0 / (atan(-0.5 * v[0]) + 1.5707963267948966192);
-    double e;  // half the energy of the amplitude (with the mean of cos 2 phi's constant part)
+    if constexpr (COR) return 1.0 / (atan(-0.5 * oct_sum(SLOPE ? a1 : q.A * a1)) + 1.5707963267948966192);
+    const double v = oct_sum(SLOPE ? __fma_rn(0.5, a2, a1) : q.A * __fma_rn(-q.A, a2, a1));
+    double e;  // half the energy of the amplitude, with the constant part of cos 2 phi's sum
     if constexpr (SLOPE)
         e = 0.5 * __fma_rn(q.B * q.B, nd->su2, __fma_rn(2.0 * q.A * q.B, nd->su1, q.A * q.A * N));
     else
-        e = q.A * q.A * energy0;
-    return (S2 + e) + v[0];
+        e = q.A * q.A * en;
+    return (S2 + e) + v;
 }
 
-// Sums over the full node set for one candidate (the row's 16 lanes share the
-// nodes).
-template <bool SLOPE, bool QUART>
-__device__ __forceinline__ void wide_sums(const NodeCand& q, const double* zw, const double* un, int l16, int K, double& a1,
-                                          double& a2) {
+// Sums over a node set in LDS for one candidate (the octet's lanes share the
+// nodes; n a multiple of 8).
+template <bool SLOPE, bool QUART, bool COR>
+__device__ __forceinline__ void lds_sums(const NodeCand& q, const double* zw, const double* un, int l8, int n, double& a1,
+                                         double& a2) {
 #pragma unroll 2
-    for (int k = l16; k < K; k += 16) {
+    for (int k = l8; k < n; k += 8) {
         const double u = un[k];
         double r = node_delta<QUART>(q, u);
         r -= rint(r);
         double c, s;
         sincos_turns64(r, c, s);
-        node_terms<SLOPE>(q, u, c, s, zw[4 * k], zw[4 * k + 1], zw[4 * k + 2], zw[4 * k + 3], a1, a2);
+        node_terms<SLOPE, COR>(q, u, c, s, zw[4 * k], zw[4 * k + 1], zw[4 * k + 2], zw[4 * k + 3], a1, a2);
     }
 }
 
-// Half of (N + sum of Wr), the constant part of the energy: Wr at w[0],
-// w[stride], ..., summed over the wave.
-__device__ __forceinline__ double node_energy(const double* w, int n, int stride, double N) {
+// Half of (N + sum of Wr), the constant part of the energy, over the wave.
+__device__ __forceinline__ double node_energy(const double* zw, int n, double N) {
     double v[1] = {0.0};
-    for (int k = threadIdx.x & 63; k < n; k += 64) v[0] += w[k * stride];
+    for (int k = threadIdx.x & 63; k < n; k += 64) v[0] += zw[4 * k + 2];
     wave_sums(v);
     return 0.5 * (N + v[0]);
 }
 
-// Weights re-expanded about the phase of the member in sh.mid, by the whole
-// workgroup: Z exp(i d), W exp(2 i d) (d: that member's delta) as Chebyshev
-// moments over the full nodes, then values at 16 nodes.
+// The set asked for in sh.next, by the whole workgroup: Z exp(i d), W exp(2 i d)
+// (d: the delta of the member at its centre) as Chebyshev moments over the full
+// nodes, then values at the new nodes.
 __device__ __noinline__ void relevel(const NodeDesc* nd, const FitLds& l, FitShared& sh) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NT = blockDim.x, K = nd->K;
-    const NodeCand q{sh.mid[1] * nd->sc[1],
-                     (sh.mid[2] - nd->mid[2]) * nd->sc[2],
-                     (sh.mid[3] - nd->mid[3]) * nd->sc[3],
-                     (sh.mid[4] - nd->mid[4]) * nd->sc[4],
-                     (sh.mid[6] - nd->mid[6]) * nd->sc[6],
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NT = blockDim.x, K = nd->K, n = sh.next.K;
+    const NodeCand q{sh.next.mid[1] * nd->sc[1],
+                     (sh.next.mid[2] - nd->mid[2]) * nd->sc[2],
+                     (sh.next.mid[3] - nd->mid[3]) * nd->sc[3],
+                     (sh.next.mid[4] - nd->mid[4]) * nd->sc[4],
+                     (sh.next.mid[6] - nd->mid[6]) * nd->sc[6],
                      0.0,
                      0.0};
     for (int k = tid; k < K; k += NT) {
@@ -437,46 +474,128 @@ __device__ __noinline__ void relevel(const NodeDesc* nd, const FitLds& l, FitSha
         l.scr[4 * k + 3] = __fma_rn(wr, s2, wi * c2);
     }
     __syncthreads();
-    for (int j = wave; j < kNodePts; j += NT >> 6) {
+    const double inv = 0.25 / (double)K;
+    for (int j = wave; j < n; j += NT >> 6) {
         double a[4] = {0.0, 0.0, 0.0, 0.0};
         for (int k = lane; k < K; k += 64) {
-            const double t = cos_ratio(j * (2 * k + 1), 4 * K, 0.25 / (double)K);
+            const double t = cos_ratio(j * (2 * k + 1), 4 * K, inv);
 #pragma unroll
             for (int e = 0; e < 4; ++e) a[e] = __fma_rn(t, l.scr[4 * k + e], a[e]);
         }
         wave_sums(a);
         if (lane == 0) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) l.nar[e * kNodePts + j] = a[e];
+            for (int e = 0; e < 4; ++e) l.lz[4 * j + e] = a[e];
         }
     }
     __syncthreads();
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (tid < kNodePts) {
-        for (int j = 0; j < kNodePts; ++j) {
-            const double t = j ? cos_ratio(j * (2 * tid + 1), 4 * kNodePts, 1.0 / (4 * kNodePts)) : 0.5;
+    const double invn = 0.25 / (double)n;
+    for (int k = tid; k < n; k += NT) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < n; ++j) {
+            const double t = j ? cos_ratio(j * (2 * k + 1), 4 * n, invn) : 0.5;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = __fma_rn(t, l.nar[e * kNodePts + j], v[e]);
+            for (int e = 0; e < 4; ++e) v[e] = __fma_rn(t, l.lz[4 * j + e], v[e]);
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) l.scr[4 * k + e] = v[e] * (8.0 * invn);  // 2 / n
+        l.lu[k] = cos_ratio(2 * k + 1, 4 * n, invn) + nd->c;
     }
     __syncthreads();
-    if (tid < kNodePts) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) l.nar[e * kNodePts + tid] = 0.125 * v[e];
-        l.nar[4 * kNodePts + tid] = cos_ratio(2 * tid + 1, 4 * kNodePts, 1.0 / (4 * kNodePts)) + nd->c;
+    for (int e = tid; e < 4 * n; e += NT) l.lz[e] = l.scr[e];
+    if (tid == 0) {
+        sh.lev = sh.next;
+        sh.lev.pend = -1;
+        sh.next.pend = -1;
     }
-    if (tid == 0) sh.lim[7] = 1.0;
     __syncthreads();
 }
 
+// Growth of exp(i p) off [-1, 1]: log of its largest modulus on the ellipse of
+// sum of half axes e^eta, for |coefficients| <= b1 .. b4 of x .. x^4 (rad).
+__host__ __device__ inline double ellipse_growth(double b1, double b2, double b3, double b4, double eta) {
+    const double e = exp(eta), f = 1.0 / e, s1 = 0.5 * (e - f), c1 = 0.5 * (e + f);
+    const double s2 = 2.0 * s1 * c1, s3 = s1 * (3.0 + 4.0 * s1 * s1), s4 = 2.0 * s2 * (1.0 + 2.0 * s1 * s1);
+    return b1 * s1 + 0.5 * b2 * s2 + 0.25 * b3 * (s3 + 3.0 * s1) + 0.125 * b4 * (s4 + 4.0 * s2);
+}
+
+// Chebyshev nodes that interpolate exp(i p(x)) (times a polynomial of degree
+// `extra`) on [-1, 1] to 1e-15 by the bound at this eta: error <= 4 M rho^-K /
+// (rho - 1), M the largest modulus on the ellipse, rho = e^eta.  Every eta
+// gives a valid bound; callers take the best of a grid.
+__host__ __device__ inline double nodes_at(double b1, double b2, double b3, double b4, int extra, double eta) {
+    return (log(4e15 / (exp(eta) - 1.0)) + ellipse_growth(b1, b2, b3, b4, eta)) / eta + extra;
+}
+
+// Whether a smaller node set would carry the population after generation g,
+// whose best member is `best`; by one wave.
+__device__ __noinline__ void ask_level(const NodeDesc* nd, const FitLds& l, FitShared& sh, int P, double F, int g, int best) {
+    const int lane = threadIdx.x & 63;
+    const double* x = l.xs + (g & 1) * P * kRowD;
+    const double* xb = x + best * kRowD;
+    // largest distance of a member from the best one, per slot, with room for a
+    // mutant x1 + F (x2 - x3) of such members and half as much again; in turns
+    const double room = 1.5 * (1.0 + 2.0 * F);
+    double rng[kSlots], q[5];
+#pragma unroll
+    for (int j = 1; j < kSlots; ++j) {
+        double a = 0.0;
+        for (int m = lane; m < P; m += 64) a = fmax(a, fabs(x[m * kRowD + j] - xb[j]));
+        rng[j] = room * wave_extreme<true>(a);
+        if (j != 5) q[j == 6 ? 4 : j - 1] = rng[j] * nd->sc[j];
+    }
+    // coefficients in x (u = x + c), of 2 delta, rad
+    const double c = fabs(nd->c), w = 1.0 + c, pi4 = 12.566370614359172;
+    const double b1 = pi4 * (q[1] + c * (2.0 * q[2] + c * (3.0 * q[3] + 4.0 * c * q[4])));
+    const double b2 = pi4 * (q[2] + c * (3.0 * q[3] + 6.0 * c * q[4])), b3 = pi4 * (q[3] + 4.0 * c * q[4]), b4 = pi4 * q[4];
+    const double sum = q[0] + w * (q[1] + w * (q[2] + w * (q[3] + w * q[4])));  // largest |delta|, turns
+    const int extra = nd->slope ? 2 : 0;
+    // the distances scaled up as far as 8 or 16 nodes allow (their bound is
+    // linear in the coefficients at a fixed ellipse: the best of the wave's
+    // ellipses) and delta stays within the polynomials' range
+    const double eta = 0.1 * (double)(lane + 1);
+    const double at0 = log(4e15 / (exp(eta) - 1.0)), slope = ellipse_growth(b1, b2, b3, b4, eta);
+    const double s8 = fmin(wave_extreme<true>(((8 - extra) * eta - at0) / slope), kNodeTurns8 / sum);
+    const double s16 = fmin(wave_extreme<true>(((16 - extra) * eta - at0) / slope), kNodeTurns16 / sum);
+    int K = 0, kind = 0;
+    double scale = 1.0;
+    if (s8 >= 1.0) {
+        K = 8;
+        kind = 2;
+        scale = s8;
+    } else if (s16 >= 1.0) {
+        K = 16;
+        kind = 1;
+        scale = s16;
+    } else {
+        const double need = wave_extreme<false>((at0 + slope) / eta + extra);
+        if (need <= (double)kNodeMaxK) K = ((int)ceil(need) + 7) & ~7;
+    }
+    // worth it for fewer than five eighths of the nodes
+    const int cur = sh.lev.K ? sh.lev.K : nd->K;
+    if (K == 0 || (kind ? kind <= sh.lev.kind : 8 * K > 5 * cur) || K > level_cap(nd->K)) return;
+    if (lane == 0) {
+        Level& n = sh.next;
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const bool amp = j == 0 || j == 5;
+            n.mid[j] = amp ? 0.0 : xb[j];
+            n.lim[j] = amp ? __builtin_inf() : rng[j] * fmin(scale, 1e9);  // (finite: rng may be 0)
+        }
+        n.K = K;
+        n.kind = kind;
+        n.pend = g + 2;
+    }
+}
+
 // The bookkeeping of generation g, by one wave: best member, history, stop
-// rule, and every 16th generation whether the narrow set can take over.
+// rule, and every 16th generation a look at the node set.
 __device__ __forceinline__ void book(const NodeDesc* nd, const BlockDesc* d, const FitLds& l, FitShared& sh, int g) {
     const int lane = threadIdx.x & 63, P = d->P;
-    const double* f = l.fs + (g & 1) * P;
+    const double* f = l.xs + (g & 1) * P * kRowD + kSlots;
     double fv[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) fv[t] = lane + 64 * t < P ? f[lane + 64 * t] : __builtin_inf();
+    for (int t = 0; t < 4; ++t) fv[t] = lane + 64 * t < P ? f[(lane + 64 * t) * kRowD] : __builtin_inf();
     const double bf = wave_extreme<false>(fmin(fmin(fv[0], fv[1]), fmin(fv[2], fv[3])));
     int best = 0;  // lowest index on ties
 #pragma unroll
@@ -501,169 +620,198 @@ __device__ __forceinline__ void book(const NodeDesc* nd, const BlockDesc* d, con
         sh.best_f = bf;
         sh.stop_gen = g;
     }
-    if ((g & 15) != 15 || flags || sh.pend >= 0) return;
-    // largest distance of a member from the best one, per slot, and in turns
-    const double* x = l.xs + (g & 1) * P * kSlots;
-    const double* xb = x + best * kSlots;
-    double rng[kSlots], q[5];
-#pragma unroll
-    for (int j = 1; j < kSlots; ++j) {
-        double a = 0.0;
-        for (int m = lane; m < P; m += 64) a = fmax(a, fabs(x[m * kSlots + j] - xb[j]));
-        rng[j] = wave_extreme<true>(a);
-        if (j != 5) q[j == 6 ? 4 : j - 1] = rng[j] * nd->sc[j];
-    }
-    // growth of |exp(2 i delta)| on the ellipse of sum of half axes e^3 for a
-    // polynomial with these coefficients about x = 0: the interpolation error
-    // on 16 nodes is below 1e-15 while it stays below 15 (9 with the two
-    // further degrees of a sloping amplitude)
-    const double c = fabs(nd->c);
-    const double b1 = q[1] + c * (2.0 * q[2] + c * (3.0 * q[3] + 4.0 * c * q[4]));
-    const double b2 = q[2] + c * (3.0 * q[3] + 6.0 * c * q[4]), b3 = q[3] + 4.0 * c * q[4];
-    const double G = 12.566370614359172 * (10.018 * b1 + 100.86 * b2 + 1020.4 * b3 + 10273.0 * q[4]);
-    const double w = 1.0 + c;
-    const double sum = q[0] + w * (q[1] + w * (q[2] + w * (q[3] + w * q[4])));
-    // the limits: the distances scaled up as far as both bounds allow; worth it
-    // once a mutant x1 + F (x2 - x3) of such members lies well inside
-    const double scale = fmin((nd->slope ? 9.0 : 15.0) / G, 0.125 / sum);
-    if (scale >= 1.5 * (1.0 + 2.0 * d->F) && lane == 0) {
-#pragma unroll
-        for (int j = 0; j < kSlots; ++j) {
-            const bool amp = j == 0 || j == 5;
-            sh.mid[j] = amp ? 0.0 : xb[j];
-            sh.lim[j] = amp ? __builtin_inf() : rng[j] * scale;
-        }
-        sh.pend = g + 2;
-    }
+    if ((g & 15) == 15 && !flags && sh.lev.kind < 2 && sh.next.pend < 0) ask_level(nd, l, sh, P, d->F, g, best);
 }
 
 // The generations of the members' waves; returns the generation at which the
 // loop ended (g1, or the one dropped after a stop).
-template <int NM, bool SLOPE, bool QUART>
-__device__ __forceinline__ int member_loop(const NodeDesc* nd, const BlockDesc* d, int g0, int g1, bool fresh,
-                                           const FitLds& l, FitShared& sh) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15;
-    const int W = (blockDim.x >> 6) - 1, P = d->P, K = nd->K;
-    const bool cor = d->objective != 0;
-    const double N = (double)d->n, S2 = sh.S2, Fm = d->F;
-
-    // constants of the slot this lane holds (lanes 7-15: none)
-    const int jl = l16 < kSlots ? l16 : kSlots - 1;
-    const bool slot = l16 < kSlots;
-    const double lo_j = gld(&d->lo[jl]), hi_j = gld(&d->hi[jl]);
-    const double mid_w = slot ? gld(&nd->mid[jl]) : 0.0, sc_j = slot ? gld(&nd->sc[jl]) : 0.0;
-    const double en_w = node_energy(l.zw + 2, K, 4, N);
-
-    // the members of this row
-    const int row = (wave << 2) + (lane >> 4), nrow = 4 * W;
+template <int NM, bool SLOPE, bool QUART, bool COR>
+struct Members {
+    const NodeDesc* nd;
+    const FitLds& l;
+    FitShared& sh;
+    int g0, g1, P, K, l8, jl, m0, nrow;
+    bool slot;
+    double N, S2, F, lo, hi, mid_w, sc, en_w;
     double xi[NM], fo[NM];
-#pragma unroll
-    for (int t = 0; t < NM; ++t) {
-        const int m = min(row + t * nrow, P - 1);
-        xi[t] = l.xs[((g0 + 1) & 1) * P * kSlots + m * kSlots + jl];
-        fo[t] = fresh ? __builtin_inf() : l.fs[((g0 + 1) & 1) * P + m];
-    }
 
-    // trial coordinate of member m (generation g, draws w): apply_trial's arithmetic
-    auto trial = [&](const double* xin, uint32_t w, double x) {
-        const double x1 = xin[(w & 255u) * kSlots + jl];
-        const double x2 = xin[((w >> 8) & 255u) * kSlots + jl];
-        const double x3 = xin[((w >> 16) & 255u) * kSlots + jl];
-        double v = __fma_rn(Fm, x2 - x3, x1);
-        if (v < lo_j) v = (lo_j + x1) * 0.5;
-        if (v > hi_j) v = (hi_j + x1) * 0.5;
-        return (w >> (24 + jl)) & 1u ? v : x;
-    };
-    auto wide = [&](double y) {
-        const NodeCand q = node_cand<SLOPE, QUART>((y - mid_w) * sc_j);
+    __device__ __forceinline__ Members(const NodeDesc* nd_, const BlockDesc* d, int g0_, int g1_, bool fresh,
+                                       const FitLds& l_, FitShared& sh_)
+        : nd(nd_), l(l_), sh(sh_), g0(g0_), g1(g1_) {
+        const int tid = threadIdx.x, lane = tid & 63;
+        P = d->P;
+        K = nd->K;
+        N = (double)d->n;
+        S2 = sh.S2;
+        F = d->F;
+        l8 = lane & 7;
+        // constants of the slot this lane holds (lane 7: none)
+        slot = l8 < kSlots;
+        jl = slot ? l8 : kSlots - 1;
+        lo = gld(&d->lo[jl]);
+        hi = gld(&d->hi[jl]);
+        mid_w = slot ? gld(&nd->mid[jl]) : 0.0;
+        sc = slot ? gld(&nd->sc[jl]) : 0.0;
+        en_w = node_energy(l.zw, K, N);
+        m0 = ((tid >> 6) << 3) + (lane >> 3);
+        nrow = 8 * ((int)(blockDim.x >> 6) - 1);
+        const double* x = l.xs + ((g0 + 1) & 1) * P * kRowD;
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {
+            xi[t] = x[member(t) * kRowD + jl];
+            fo[t] = fresh ? __builtin_inf() : x[member(t) * kRowD + kSlots];
+        }
+    }
+    __device__ __forceinline__ int member(int t) const { return min(m0 + t * nrow, P - 1); }
+    __device__ __forceinline__ uint64_t draw(int t, int g) const { return l.dr[(g - g0) * P + member(t)]; }
+
+    // trial coordinate of member t with draws w: apply_trial's arithmetic
+    __device__ __forceinline__ double trial(int t, int g, uint64_t w) const {
+        const char* x = reinterpret_cast<const char*>(l.xs + ((g + 1) & 1) * P * kRowD + jl);
+        const uint32_t a = (uint32_t)w, b = (uint32_t)(w >> 32);
+        const double x1 = *reinterpret_cast<const double*>(x + (a & 0xFFFFu));
+        const double x2 = *reinterpret_cast<const double*>(x + (a >> 16));
+        const double x3 = *reinterpret_cast<const double*>(x + (b & 0xFFFFu));
+        double v = __fma_rn(F, x2 - x3, x1);
+        if (v < lo) v = (lo + x1) * 0.5;
+        if (v > hi) v = (hi + x1) * 0.5;
+        return (b >> (16 + l8)) & 1u ? v : xi[t];
+    }
+    __device__ __forceinline__ double full(double y) const {
+        const NodeCand q = node_cand<SLOPE, QUART>((y - mid_w) * sc);
         double a1 = 0.0, a2 = 0.0;
-        wide_sums<SLOPE, QUART>(q, l.zw, l.un, l16, K, a1, a2);
-        return node_objective<SLOPE>(nd, q, a1, a2, cor, S2, en_w, N);
-    };
-    auto keep = [&](int t, int g, double y, double ft) {
+        lds_sums<SLOPE, QUART, COR>(q, l.zw, l.un, l8, K, a1, a2);
+        return node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en_w, N);
+    }
+    __device__ __forceinline__ void keep(int t, int g, double y, double ft) {
         const bool take = g == 0 || ft <= fo[t];
         xi[t] = take ? y : xi[t];
         fo[t] = take ? ft : fo[t];
-        const int m = row + t * nrow;
-        if (m < P) {
-            if (slot) l.xs[(g & 1) * P * kSlots + m * kSlots + l16] = xi[t];
-            if (l16 == 0) l.fs[(g & 1) * P + m] = fo[t];
-        }
-    };
+        const int m = m0 + t * nrow;
+        if (m < P) l.xs[(g & 1) * P * kRowD + m * kRowD + l8] = slot ? xi[t] : fo[t];
+    }
+    // the end of generation g: true when generation g - 1 stopped the fit
+    __device__ __forceinline__ bool stopped(int g) const {
+        __syncthreads();
+        return g > g0 && sh.stop[g & 1];
+    }
 
-    int g = g0;
-    bool narrow = sh.lim[7] > 0.0;  // (slot 7 of lim holds the flag)
-    if (!narrow) {
+    // generations on the full set, or a re-expanded one in LDS, until one of kind
+    // 1 or 2 is in effect
+    __device__ __forceinline__ bool lds_loop(int& g) {
+        int n = sh.lev.K;
+        double mid = 0.0, lim = 0.0, en = 0.0;
+        auto level = [&]() {
+            n = sh.lev.K;
+            if (!n) return;
+            mid = slot ? sh.lev.mid[jl] : 0.0;
+            lim = slot ? sh.lev.lim[jl] : __builtin_inf();
+            en = node_energy(l.lz, n, N);
+        };
+        level();
         for (; g < g1; ++g) {
-            if (sh.pend == g) {
+            if (sh.next.pend == g) {
                 relevel(nd, l, sh);
-                narrow = true;
-                break;
+                if (sh.lev.kind) return false;
+                level();
             }
-            const double* xin = l.xs + ((g + 1) & 1) * P * kSlots;
 #pragma unroll
             for (int t = 0; t < NM; ++t) {
-                double y = xi[t];
-                if (g > 0) y = trial(xin, l.dr[(g - g0) * P + min(row + t * nrow, P - 1)], y);
-                keep(t, g, y, wide(y));
+                const double y = g > 0 ? trial(t, g, draw(t, g)) : xi[t];
+                double ft;
+                if (n && __ballot(fabs(y - mid) <= lim) == ~0ull) {
+                    const NodeCand q = node_cand<SLOPE, QUART>((y - mid) * sc);
+                    double a1 = 0.0, a2 = 0.0;
+                    lds_sums<SLOPE, QUART, COR>(q, l.lz, l.lu, l8, n, a1, a2);
+                    ft = node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
+                } else {
+                    ft = full(y);
+                }
+                keep(t, g, y, ft);
             }
-            __syncthreads();
-            if (g > g0 && sh.stop[g & 1]) return g;
+            if (stopped(g)) return true;
         }
-        if (!narrow) return g;
+        return false;
     }
 
-    const double nzr = l.nar[l16], nzi = l.nar[kNodePts + l16], nwr = l.nar[2 * kNodePts + l16],
-                 nwi = l.nar[3 * kNodePts + l16], nu = l.nar[4 * kNodePts + l16];
-    const double en_n = node_energy(l.nar + 2 * kNodePts, kNodePts, 1, N);
-    const double mid_n = slot ? sh.mid[jl] : 0.0, lim = slot ? sh.lim[jl] : __builtin_inf();
-    double kc[kNarDeg64 + 1], ks[kNarDeg64 + 1];  // held in vector registers
+    // generations on 16 (KIND 1) or 8 (KIND 2) nodes in registers
+    template <int KIND>
+    __device__ __forceinline__ bool register_loop(int& g) {
+        constexpr int R = KIND == 1 ? 2 : 1;  // nodes per lane
+        constexpr int D = KIND == 1 ? kNarDeg64 : kNar8Deg64;
+        double zr[R], zi[R], wr[R], wi[R], u[R];
 #pragma unroll
-    for (int k = 0; k <= kNarDeg64; ++k) {
-        kc[k] = kCosNar64[k];
-        ks[k] = kSinNar64[k];
-        asm volatile("" : "+v"(kc[k]), "+v"(ks[k]));
-    }
-    for (; g < g1; ++g) {
-        const double* xin = l.xs + ((g + 1) & 1) * P * kSlots;
-#pragma unroll
-        for (int t = 0; t < NM; ++t) {
-            const double y = trial(xin, l.dr[(g - g0) * P + min(row + t * nrow, P - 1)], xi[t]);
-            const double dn = y - mid_n;
-            double ft;
-            if (__builtin_expect(__ballot(fabs(dn) <= lim) == ~0ull, 1)) {
-                const NodeCand q = node_cand<SLOPE, QUART>(dn * sc_j);
-                const double r = node_delta<QUART>(q, nu), u = r * r;
-                double c = kc[0], s = ks[0];
-#pragma unroll
-                for (int k = 1; k <= kNarDeg64; ++k) {
-                    c = __fma_rn(c, u, kc[k]);
-                    s = __fma_rn(s, u, ks[k]);
-                }
-                s *= r;
-                double a1 = 0.0, a2 = 0.0;
-                node_terms<SLOPE>(q, nu, c, s, nzr, nzi, nwr, nwi, a1, a2);
-                ft = node_objective<SLOPE>(nd, q, a1, a2, cor, S2, en_n, N);
-            } else {
-                ft = wide(y);
-            }
-            keep(t, g, y, ft);
+        for (int r = 0; r < R; ++r) {
+            const int k = l8 + 8 * r;
+            zr[r] = l.lz[4 * k];
+            zi[r] = l.lz[4 * k + 1];
+            wr[r] = l.lz[4 * k + 2];
+            wi[r] = l.lz[4 * k + 3];
+            u[r] = l.lu[k];
         }
-        __syncthreads();
-        if (g > g0 && sh.stop[g & 1]) return g;
+        const double en = node_energy(l.lz, 8 * R, N);
+        const double mid = slot ? sh.lev.mid[jl] : 0.0, lim = slot ? sh.lev.lim[jl] : __builtin_inf();
+        double kc[D + 1], ks[D + 1];  // held in vector registers
+#pragma unroll
+        for (int k = 0; k <= D; ++k) {
+            kc[k] = KIND == 1 ? kCosNar64[k] : kCosNar8[k];
+            ks[k] = KIND == 1 ? kSinNar64[k] : kSinNar8[k];
+            asm volatile("" : "+v"(kc[k]), "+v"(ks[k]));
+        }
+        uint64_t w[NM];
+#pragma unroll
+        for (int t = 0; t < NM; ++t) w[t] = draw(t, g);
+        for (; g < g1; ++g) {
+            if (KIND == 1 && sh.next.pend == g) {
+                relevel(nd, l, sh);
+                return false;
+            }
+#pragma unroll
+            for (int t = 0; t < NM; ++t) {
+                const double y = trial(t, g, w[t]);
+                if (g + 1 < g1) w[t] = draw(t, g + 1);
+                const double dn = y - mid;
+                const unsigned long long inside = __ballot(fabs(dn) <= lim);
+                const NodeCand q = node_cand<SLOPE, QUART>(dn * sc);
+                double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double x = node_delta<QUART>(q, u[r]), x2 = x * x;
+                    double c = kc[0], s = ks[0];
+#pragma unroll
+                    for (int k = 1; k <= D; ++k) {
+                        c = __fma_rn(c, x2, kc[k]);
+                        s = __fma_rn(s, x2, ks[k]);
+                    }
+                    s *= x;
+                    node_terms<SLOPE, COR>(q, u[r], c, s, zr[r], zi[r], wr[r], wi[r], a1, a2);
+                }
+                double ft = node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
+                // (the limits are tested last, off the chain of dependent
+                // operations: outside them the value above is dropped)
+                asm volatile("" : "+v"(ft));
+                if (__builtin_expect(inside != ~0ull, 0)) ft = full(y);
+                keep(t, g, y, ft);
+            }
+            if (stopped(g)) return true;
+        }
+        return false;
     }
-    return g;
-}
+
+    __device__ __forceinline__ int run() {
+        int g = g0;
+        if (sh.lev.kind == 0 && lds_loop(g)) return g;
+        if (g < g1 && sh.lev.kind == 1 && register_loop<1>(g)) return g;
+        if (g < g1 && register_loop<2>(g)) return g;
+        return g;
+    }
+};
 
 // The same barriers for the bookkeeping wave, one generation behind.
 __device__ __forceinline__ int book_loop(const NodeDesc* nd, const BlockDesc* d, int g0, int g1, const FitLds& l,
                                          FitShared& sh) {
-    bool narrow = sh.lim[7] > 0.0;
     for (int g = g0; g < g1; ++g) {
-        if (!narrow && sh.pend == g) {
-            relevel(nd, l, sh);
-            narrow = true;
-        }
+        if (sh.next.pend == g) relevel(nd, l, sh);
         if (g > g0) book(nd, d, l, sh, g - 1);
         __syncthreads();
         if (g > g0 && sh.stop[g & 1]) return g;
@@ -671,21 +819,20 @@ __device__ __forceinline__ int book_loop(const NodeDesc* nd, const BlockDesc* d,
     return g1;
 }
 
-template <int NM>
+template <int NM, bool COR>
 __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, int g0, int ngen, bool fresh, const FitLds& l,
                                         FitShared& sh) {
     const int tid = threadIdx.x, NT = blockDim.x, W = (NT >> 6) - 1, P = d->P, g1 = g0 + ngen;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int g;
-    if (wave == W) {
+    if (wave == W)
         g = book_loop(nd, d, g0, g1, l, sh);
-    } else if (nd->slope) {
-        g = d->quartic ? member_loop<NM, true, true>(nd, d, g0, g1, fresh, l, sh)
-                       : member_loop<NM, true, false>(nd, d, g0, g1, fresh, l, sh);
-    } else {
-        g = d->quartic ? member_loop<NM, false, true>(nd, d, g0, g1, fresh, l, sh)
-                       : member_loop<NM, false, false>(nd, d, g0, g1, fresh, l, sh);
-    }
+    else if (nd->slope)
+        g = d->quartic ? Members<NM, true, true, COR>(nd, d, g0, g1, fresh, l, sh).run()
+                       : Members<NM, true, false, COR>(nd, d, g0, g1, fresh, l, sh).run();
+    else
+        g = d->quartic ? Members<NM, false, true, COR>(nd, d, g0, g1, fresh, l, sh).run()
+                       : Members<NM, false, false, COR>(nd, d, g0, g1, fresh, l, sh).run();
     int flags;
     if (g < g1) {
         flags = sh.stop[g & 1];  // generation g - 1 stopped the fit; g is dropped
@@ -697,20 +844,23 @@ __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, 
 
     // state for the next launch: the population after the last kept generation
     const int gl = flags ? sh.stop_gen : g1 - 1;
-    const double* xl = l.xs + (gl & 1) * P * kSlots;
-    const double* fl = l.fs + (gl & 1) * P;
-    for (int e = tid; e < P * kSlots; e += NT) {
-        const int m = e / kSlots;
-        gst(d->pop + (size_t)m * kStride + (e - m * kSlots), xl[e]);
+    const double* xl = l.xs + (gl & 1) * P * kRowD;
+    for (int e = tid; e < P * kRowD; e += NT) {
+        const int j = e & (kRowD - 1);
+        if (j < kSlots)
+            gst(d->pop + e, xl[e]);
+        else
+            gst(d->fpop + e / kRowD, xl[e]);
     }
-    for (int m = tid; m < P; m += NT) gst(d->fpop + m, fl[m]);
     if (!flags) {
-        for (int e = tid; e < 5 * kNodePts; e += NT) gst(nd->nar + e, l.nar[e]);
-        if (tid < 8) {
-            gst(nd->nar + 5 * kNodePts + tid, sh.mid[tid]);
-            gst(nd->nar + 5 * kNodePts + 8 + tid, sh.lim[tid]);
-        }
-        if (tid == 0) gst(reinterpret_cast<int*>(nd->nar + kNodeNarrow), sh.pend);
+        double* o = nd->nar;
+        constexpr int nl = 2 * sizeof(Level) / sizeof(double);
+        static_assert(nl <= kNodeLevelHead, "both level records fit their place");
+        for (int e = tid; e < nl; e += NT) gst(o + e, reinterpret_cast<const double*>(&sh.lev)[e]);
+        o += kNodeLevelHead;
+        const int n = sh.lev.K;
+        for (int e = tid; e < 4 * n; e += NT) gst(o + e, l.lz[e]);
+        for (int e = tid; e < n; e += NT) gst(o + 4 * n + e, l.lu[e]);
     }
     if (tid == 0) {
         DeState* st = d->st;
@@ -722,8 +872,9 @@ __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, 
     }
 }
 
-template <int NM>
-__global__ __launch_bounds__(1024) void k_node_fit(const NodeDesc* __restrict__ nds, const BlockDesc* __restrict__ bds,
+// MAXT: largest workgroup (512 threads leave each lane twice the registers).
+template <int NM, bool COR, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_node_fit(const NodeDesc* __restrict__ nds, const BlockDesc* __restrict__ bds,
                                                    int nblk, int P, int maxK, int off, int ngen, int next_ngen, int chunk,
                                                    int flip, int slices) {
     extern __shared__ __align__(16) double lds[];
@@ -740,13 +891,15 @@ __global__ __launch_bounds__(1024) void k_node_fit(const NodeDesc* __restrict__ 
     const FitLds l = fit_lds(lds, P, maxK);
     const int K = nd->K;
 
-    const uint32_t* dr = nd->draws + (size_t)((nd->parity + flip) & 1) * chunk * P;
+    const uint64_t* dr = nd->draws + (size_t)((nd->parity + flip) & 1) * chunk * P;
     for (int e = tid; e < ngen * P; e += NT) l.dr[e] = gld(dr + e);
     for (int k = tid; k < K; k += NT) l.un[k] = cos_ratio(2 * k + 1, 4 * K, 0.25 / (double)K) + nd->c;
     if (fresh) {
         init_block(d);
-        if (tid < 8) sh.mid[tid] = sh.lim[tid] = 0.0;
-        if (tid == 0) sh.pend = -1;
+        if (tid == 0) {
+            sh.lev.K = sh.lev.kind = 0;
+            sh.lev.pend = sh.next.pend = -1;
+        }
         const int n4 = 4 * K;
         for (int e = tid; e < n4; e += NT) {
             double s = 0.0;
@@ -779,27 +932,20 @@ __global__ __launch_bounds__(1024) void k_node_fit(const NodeDesc* __restrict__ 
             }
         }
         if (tid == 0) gst(nd->wts + 4 * kNodeMaxK, sh.S2);
-        for (int e = tid; e < P * kSlots; e += NT) {
-            const int m = e / kSlots;
-            l.xs[P * kSlots + e] = d->pop[(size_t)m * kStride + (e - m * kSlots)];  // written by init_block
-        }
+        for (int e = tid; e < P * kRowD; e += NT) l.xs[P * kRowD + e] = d->pop[e];  // written by init_block
     } else {
         for (int e = tid; e < 4 * K; e += NT) l.zw[e] = gld(nd->wts + e);
-        for (int e = tid; e < 5 * kNodePts; e += NT) l.nar[e] = gld(nd->nar + e);
-        if (tid < 8) {
-            sh.mid[tid] = gld(nd->nar + 5 * kNodePts + tid);
-            sh.lim[tid] = gld(nd->nar + 5 * kNodePts + 8 + tid);
-        }
-        if (tid == 0) {
-            sh.pend = gld(reinterpret_cast<const int*>(nd->nar + kNodeNarrow));
-            sh.S2 = gld(nd->wts + 4 * kNodeMaxK);
-        }
-        const int slot = (g0 + 1) & 1;
-        for (int e = tid; e < P * kSlots; e += NT) {
-            const int m = e / kSlots;
-            l.xs[slot * P * kSlots + e] = gld(d->pop + (size_t)m * kStride + (e - m * kSlots));
-        }
-        for (int m = tid; m < P; m += NT) l.fs[slot * P + m] = gld(d->fpop + m);
+        const double* o = nd->nar;
+        for (int e = tid; e < (int)(2 * sizeof(Level) / sizeof(double)); e += NT)
+            reinterpret_cast<double*>(&sh.lev)[e] = gld(o + e);
+        const int n = reinterpret_cast<const Level*>(o)->K;
+        o += kNodeLevelHead;
+        for (int e = tid; e < 4 * n; e += NT) l.lz[e] = gld(o + e);
+        for (int e = tid; e < n; e += NT) l.lu[e] = gld(o + 4 * n + e);
+        if (tid == 0) sh.S2 = gld(nd->wts + 4 * kNodeMaxK);
+        double* x = l.xs + ((g0 + 1) & 1) * P * kRowD;
+        for (int e = tid; e < P * kRowD; e += NT)
+            x[e] = (e & (kRowD - 1)) < kSlots ? gld(d->pop + e) : gld(d->fpop + e / kRowD);
         for (int g = g0 - 1 - tid; g >= 0 && g >= g0 - kNodeRing; g -= NT)
             l.ring[g & (kNodeRing - 1)] = gld(d->hist + g);
     }
@@ -813,41 +959,27 @@ __global__ __launch_bounds__(1024) void k_node_fit(const NodeDesc* __restrict__ 
         }
         return;
     }
-    fit_run<NM>(nd, d, g0, ngen, fresh, l, sh);
+    fit_run<NM, COR>(nd, d, g0, ngen, fresh, l, sh);
 }
 
 using FitKernel = void (*)(const NodeDesc*, const BlockDesc*, int, int, int, int, int, int, int, int, int);
 
-// members per row: the fewest that leave a wave for the bookkeeping
-int members_per_row(int P) { return P <= 60 ? 1 : (P <= 120 ? 2 : 4); }
+// members per octet: the fewest that leave a wave for the bookkeeping
+int members_per_octet(int P) { return P <= 120 ? 1 : 2; }
 int fit_waves(int P) {
-    const int nm = members_per_row(P);
-    return (P + 4 * nm - 1) / (4 * nm) + 1;
+    const int nm = members_per_octet(P);
+    return (P + 8 * nm - 1) / (8 * nm) + 1;
 }
-FitKernel fit_kernel(int P) {
-    switch (members_per_row(P)) {
-        case 1: return k_node_fit<1>;
-        case 2: return k_node_fit<2>;
-        default: return k_node_fit<4>;
-    }
+template <bool COR>
+FitKernel pick_fit(int P) {
+    if (members_per_octet(P) == 2) return k_node_fit<2, COR, 1024>;
+    return fit_waves(P) <= 8 ? k_node_fit<1, COR, 512> : k_node_fit<1, COR, 1024>;
 }
+FitKernel fit_kernel(int P, bool cor) { return cor ? pick_fit<true>(P) : pick_fit<false>(P); }
 
-// log of the largest |exp(i p(x))| on the Bernstein ellipse of parameter eta
-// (half axes cosh eta and sinh eta) for a polynomial with |coefficient of x^j| <= b[j] rad
-double ellipse_growth(const double* b, double eta) {
-    const double s1 = std::sinh(eta), s2 = std::sinh(2 * eta), s3 = std::sinh(3 * eta), s4 = std::sinh(4 * eta);
-    return b[1] * s1 + b[2] / 2 * s2 + b[3] / 4 * (s3 + 3 * s1) + b[4] / 8 * (s4 + 4 * s2);
-}
-
-// Chebyshev nodes that interpolate exp(i p(x)) (times a polynomial of degree
-// `extra`) on [-1, 1] to 1e-15: error <= 4 M rho^-K / (rho - 1), M the largest
-// modulus on the ellipse, rho = e^eta, for any eta; the best of a grid.
 double nodes_needed(const double* b, int extra) {
     double best = 1e18;
-    for (int i = 1; i <= 160; ++i) {
-        const double eta = 0.025 * i;
-        best = std::min(best, (std::log(4e15 / (std::exp(eta) - 1.0)) + ellipse_growth(b, eta)) / eta + extra);
-    }
+    for (int i = 1; i <= 160; ++i) best = std::min(best, nodes_at(b[1], b[2], b[3], b[4], extra, 0.025 * i));
     return best;
 }
 
@@ -929,21 +1061,21 @@ bool node_plan(const pt_block& B, double ref, int P, NodePlan* out) {
 }
 
 size_t node_fit_lds(int P, int maxK, int chunk) {
-    return fit_lds_doubles(P, maxK) * sizeof(double) + (((size_t)chunk * P * 4 + 15) & ~(size_t)15);
+    return (fit_lds_doubles(P, maxK) + (size_t)chunk * P) * sizeof(double);
 }
 
 int node_chunk(int P, int maxK, int lds_max) {
     const int64_t room = (int64_t)lds_max - 1024 - (int64_t)node_fit_lds(P, maxK, 0) - 16;
-    return (int)std::max<int64_t>(0, std::min<int64_t>(500, room / (4 * P)));
+    return (int)std::max<int64_t>(0, std::min<int64_t>(500, room / (8 * P)));
 }
 
 hipError_t node_setup(int lds_max) {
-    const void* k[] = {reinterpret_cast<const void*>(k_node_fit<1>), reinterpret_cast<const void*>(k_node_fit<2>),
-                       reinterpret_cast<const void*>(k_node_fit<4>)};
-    for (const void* f : k) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - 1024);
-        if (e != hipSuccess) return e;
-    }
+    for (int P : {4, 100, kNodeMaxP})
+        for (bool cor : {false, true}) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fit_kernel(P, cor)),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - 1024);
+            if (e != hipSuccess) return e;
+        }
     return hipSuccess;
 }
 
@@ -961,10 +1093,10 @@ hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int t
 }
 
 hipError_t node_fit(const NodeDesc* nd, const BlockDesc* bd, int nblk, int P, int maxK, int off, int ngen, int next_ngen,
-                    int chunk, int flip, hipStream_t s) {
+                    int chunk, int flip, bool cor, hipStream_t s) {
     const int nt = 64 * fit_waves(P);
     const int slices = (P * next_ngen + nt - 1) / nt;
-    const FitKernel k = fit_kernel(P);
+    const FitKernel k = fit_kernel(P, cor);
     hipLaunchKernelGGL(k, dim3((unsigned)(nblk + nblk * slices)), dim3((unsigned)nt),
                        (unsigned)node_fit_lds(P, maxK, ngen), s, nd, bd, nblk, P, maxK, off, ngen, next_ngen, chunk, flip,
                        slices > 0 ? slices : 1);

@@ -1000,8 +1000,8 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
         work += p.pts_doubles + p.s2_doubles + p.mom_doubles;
     }
     int chunk = ctx->timing ? 1 : std::min(node_chunk(P, maxK, ctx->lds_max), window ? kNodeCheck : iters);
-    chunk = std::min(chunk, std::max(16, (int)(kNodeDrawBytes / ((size_t)8 * P * nblk))));
-    const size_t draws = ((size_t)2 * chunk * P * sizeof(uint32_t) + 15) / 16 * 2;  // in doubles
+    chunk = std::min(chunk, std::max(16, (int)(kNodeDrawBytes / ((size_t)16 * P * nblk))));
+    const size_t draws = (size_t)2 * chunk * P;  // (8 bytes each)
     const size_t fixed = kNodeWtsDoubles + kNodeNarDoubles + draws;
     const size_t ndb = (sizeof(NodeDesc) * nblk + 255) & ~(size_t)255, bdb = sizeof(BlockDesc) * nblk;
     if ((rc = ensure_state(ctx, nall, de)) || (rc = ctx->node_ws.ensure((work + fixed * nblk) * sizeof(double))) ||
@@ -1024,7 +1024,7 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
             ws += doubles;
             return p;
         };
-        n.draws = reinterpret_cast<uint32_t*>(take(draws));
+        n.draws = reinterpret_cast<uint64_t*>(take(draws));
         n.wts = take(kNodeWtsDoubles);
         n.nar = take(kNodeNarDoubles);
         n.pts = take(plans[k].pts_doubles);
@@ -1053,7 +1053,7 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
             if (!e0 || !e1) return fail(PT_EDEVICE, "hipEventCreate failed");
             HIPCHK(hipEventRecord(e0, s));
         }
-        HIPCHK(node_fit(nd, bd, nblk, P, maxK, off, ngen, next, chunk, c & 1, s));
+        HIPCHK(node_fit(nd, bd, nblk, P, maxK, off, ngen, next, chunk, c & 1, de->objective != PT_OBJ_CHI2, s));
         if (ctx->timing) {
             HIPCHK(hipEventRecord(e1, s));
             ctx->ev_pending.push_back({e0, e1});
@@ -2133,7 +2133,7 @@ int server_admit(pt_server* sv, hipStream_t s) {
 int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, const BlockDesc* dd, int K,
                  hipStream_t s, int* launches) {
     const int P = sv->cfg.de.pop, chunk = std::min(sv->chunk, K);
-    const size_t draws = ((size_t)2 * chunk * P * sizeof(uint32_t) + 15) / 16 * 2;  // in doubles
+    const size_t draws = (size_t)2 * chunk * P;  // (8 bytes each)
     size_t work = 0;
     int maxK = 0, proj = 0, mom = 0, rc;
     for (int q = 0; q < nn; ++q) {
@@ -2163,7 +2163,7 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
         }
         n.wts = static_cast<double*>(sl.node.p);
         n.nar = n.wts + kNodeWtsDoubles;
-        n.draws = reinterpret_cast<uint32_t*>(n.nar + kNodeNarDoubles);
+        n.draws = reinterpret_cast<uint64_t*>(n.nar + kNodeNarDoubles);
         n.g0 = sl.fresh ? 0 : sl.gen;
         n.parity = sl.parity;
         hn[q] = n;
@@ -2178,7 +2178,8 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
     for (int off = 0; off < K; off += chunk, ++*launches) {
         const int ngen = std::min(chunk, K - off), left = K - off - ngen;
         // the last launch of the step makes the draws of the next step's first
-        HIPCHK(node_fit(nd, dd, nn, P, maxK, off, ngen, left ? std::min(chunk, left) : chunk, chunk, *launches & 1, s));
+        HIPCHK(node_fit(nd, dd, nn, P, maxK, off, ngen, left ? std::min(chunk, left) : chunk, chunk, *launches & 1,
+                        sv->cfg.de.objective != PT_OBJ_CHI2, s));
     }
     return PT_OK;
 }
