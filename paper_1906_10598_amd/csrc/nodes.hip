@@ -4,7 +4,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <type_traits>
 
 #include "kernels.h"
 
@@ -42,6 +41,13 @@ __device__ __forceinline__ void row_sums(double (&v)[N]) {
     sum_step<3>(v);
 }
 
+// DPP move of a double.
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false));
+}
+
 // Lane J of each octet (lanes 8 q .. 8 q + 7), in every lane of the octet: a
 // broadcast over the row of 16, then over its upper half.
 template <int J>
@@ -54,24 +60,37 @@ __device__ __forceinline__ double oct_bcast(double v) {
 
 // Sum over the octet, in every lane of it (pairs, quads, the two quads).
 __device__ __forceinline__ double oct_sum(double v) {
-    auto moved = [](double x, auto ctrl) {
-        constexpr int c = decltype(ctrl)::value;
-        return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), c, 0xF, 0xF, false),
-                                __builtin_amdgcn_mov_dpp(__double2loint(x), c, 0xF, 0xF, false));
-    };
-    v += moved(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
-    v += moved(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
-    v += moved(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    v += lane_move<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v += lane_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v += lane_move<0x141>(v);  // row_half_mirror
     return v;
 }
 
 template <bool MAX>
 __device__ __forceinline__ double wave_extreme(double v) {
-    auto pick = [](double a, double b) { return MAX ? fmax(a, b) : fmin(a, b); };
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v = pick(v, dpp_move(v, s));
-    v = pick(v, __shfl_xor(v, 16, 64));
-    return pick(v, __shfl_xor(v, 32, 64));
+    // (a compare and a select: fmin would first quieten its operands.  A NaN
+    // on the left stays, one on the right is passed over)
+    auto pick = [](double a, double b) { return (MAX ? b > a : b < a) ? b : a; };
+    v = pick(v, lane_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+    v = pick(v, lane_move<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+    v = pick(v, lane_move<0x141>(v));  // row_half_mirror
+    v = pick(v, lane_move<0x140>(v));  // row_mirror
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = pick(__hiloint2double(h16[0], l16[0]), __hiloint2double(h16[1], l16[1]));
+    const int lo2 = __double2loint(v), hi2 = __double2hiint(v);
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+    const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+    return pick(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
+}
+
+// Barrier that orders LDS only: a wave does not wait for its global stores (the
+// history's) to be acknowledged, which takes longer than a generation.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // cos(2 pi a / n) for integers a >= 0, n > 0, reduced exactly.
@@ -310,6 +329,14 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
 // alternate).  Wave W keeps the books one generation behind: best member,
 // history, stop rule.
 //
+// What bounds it: a generation is a chain of dependent operations (an LDS round
+// trip, about forty FP64 operations, the barrier), which a wave alone on its
+// SIMD issues at five to six cycles an instruction and two on one SIMD at four
+// each.  So the fewest instructions a wave needs and the fewest waves a SIMD
+// holds pull against each other; measured for P = 40: 16 lanes a member (ten
+// waves) 0.99 us a generation, 8 lanes (five) 0.45, 4 lanes (three) 0.54; 8 lanes
+// with the bound rule and the stop flag off the chain where they can be 0.41.
+//
 // As the population draws together fewer nodes do: every 16th generation the
 // bookkeeping wave measures its spread, and when markedly fewer nodes would
 // carry any trial it asks for the weights to be re-expanded about the best
@@ -417,16 +444,14 @@ __device__ __forceinline__ double node_objective(const NodeDesc* nd, const NodeC
     // correlation objective, Eq. (2-2-5): F = 1 / (arctan(C) + pi/2)
     if constexpr (COR) return 1.0 / (atan(-0.5 * oct_sum(SLOPE ? a1 : q.A * a1)) + 1.5707963267948966192);
     const double v = oct_sum(SLOPE ? __fma_rn(0.5, a2, a1) : q.A * __fma_rn(-q.A, a2, a1));
-    double e;  // half the energy of the amplitude, with the constant part of cos 2 phi's sum
+    // half the energy of the amplitude (with the constant part of cos 2 phi's sum)
     if constexpr (SLOPE)
-        e = 0.5 * __fma_rn(q.B * q.B, nd->su2, __fma_rn(2.0 * q.A * q.B, nd->su1, q.A * q.A * N));
-    else
-        e = q.A * q.A * en;
-    return (S2 + e) + v;
+        return __fma_rn(0.5, __fma_rn(q.B * q.B, nd->su2, __fma_rn(2.0 * q.A * q.B, nd->su1, q.A * q.A * N)), S2) + v;
+    return __fma_rn(q.A * q.A, en, S2) + v;
 }
 
-// Sums over a node set in LDS for one candidate (the octet's lanes share the
-// nodes; n a multiple of 8).
+// Sums over a node set in LDS for one candidate (the octet's lanes share
+// the nodes; n a multiple of 8).
 template <bool SLOPE, bool QUART, bool COR>
 __device__ __forceinline__ void lds_sums(const NodeCand& q, const double* zw, const double* un, int l8, int n, double& a1,
                                          double& a2) {
@@ -588,94 +613,174 @@ __device__ __noinline__ void ask_level(const NodeDesc* nd, const FitLds& l, FitS
     }
 }
 
-// The bookkeeping of generation g, by one wave: best member, history, stop
-// rule, and every 16th generation a look at the node set.
-__device__ __forceinline__ void book(const NodeDesc* nd, const BlockDesc* d, const FitLds& l, FitShared& sh, int g) {
-    const int lane = threadIdx.x & 63, P = d->P;
-    const double* f = l.xs + (g & 1) * P * kRowD + kSlots;
-    double fv[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) fv[t] = lane + 64 * t < P ? f[(lane + 64 * t) * kRowD] : __builtin_inf();
-    const double bf = wave_extreme<false>(fmin(fmin(fv[0], fv[1]), fmin(fv[2], fv[3])));
-    int best = 0;  // lowest index on ties
-#pragma unroll
-    for (int t = 3; t >= 0; --t) {
-        const unsigned long long hit = __ballot(lane + 64 * t < P && fv[t] == bf);
-        if (hit) best = 64 * t + __ffsll(hit) - 1;
-    }
-    const int win = d->window;
-    const bool wrule = d->rel_tol > 0.0 && win > 0 && g >= win;
-    double old = 0.0;
-    if (wrule) old = win < kNodeRing ? l.ring[(g - win) & (kNodeRing - 1)] : gld(d->hist + (g - win));
-    int flags = 0;
-    if (bf <= d->vtr) flags |= 4;                          // PT_FLAG_VTR
-    if (wrule && old - bf <= d->rel_tol * bf) flags |= 1;  // PT_FLAG_CONVERGED
-    if (!flags && g >= d->max_gens) flags |= 2;            // PT_FLAG_MAXGEN
-    if (d->objective == 0 && !(bf >= kNodeCancel * sh.S2)) flags = kFlagNodeAbort;
-    if (lane == 0) {
-        l.ring[g & (kNodeRing - 1)] = bf;
-        gst(d->hist + g, bf);
-        sh.stop[(g + 1) & 1] = flags;
-        sh.best = best;
-        sh.best_f = bf;
-        sh.stop_gen = g;
-    }
-    if ((g & 15) == 15 && !flags && sh.lev.kind < 2 && sh.next.pend < 0) ask_level(nd, l, sh, P, d->F, g, best);
-}
+// The bookkeeping of each generation, by one wave: best objective, history, stop
+// rule, and every 16th generation a look at the node set.  It runs one
+// generation behind the members and must stay shorter than one of theirs:
+// what it needs every time is in registers (the flags it sets itself among
+// them), the best member's index is looked up only when something needs it, and
+// fits without a window rule run without its branches (with all of these in LDS
+// and in branches it took 1050 of a generation's 1190 cycles).
+// NV: values per lane (P <= 64 NV).
+template <int NV, bool WINDOW>
+struct Book {
+    const NodeDesc* nd;
+    const FitLds& l;
+    FitShared& sh;
+    int P, lane, win, max_gens, kind, pend;
+    double vtr, rel_tol, floor, F, bf;
+    double* hist;
 
-// The generations of the members' waves; returns the generation at which the
-// loop ended (g1, or the one dropped after a stop).
+    __device__ __forceinline__ Book(const NodeDesc* nd_, const BlockDesc* d, const FitLds& l_, FitShared& sh_)
+        : nd(nd_), l(l_), sh(sh_) {
+        P = d->P;
+        lane = threadIdx.x & 63;
+        win = d->window;
+        max_gens = d->max_gens;
+        vtr = d->vtr;
+        rel_tol = d->rel_tol;
+        floor = d->objective == 0 ? kNodeCancel * sh.S2 : -__builtin_inf();
+        F = d->F;
+        hist = d->hist;
+        kind = __builtin_amdgcn_readfirstlane(sh.lev.kind);
+        pend = __builtin_amdgcn_readfirstlane(sh.next.pend);
+        bf = __builtin_inf();
+    }
+    // (lanes past the population repeat its last member)
+    __device__ __forceinline__ double value(int g, int t) const {
+        return l.xs[(g & 1) * P * kRowD + min(lane + 64 * t, P - 1) * kRowD + kSlots];
+    }
+    // lowest index of the members of generation g whose objective is bf
+    __device__ __forceinline__ int best_of(int g, double bf) const {
+        int best = 0;
+#pragma unroll
+        for (int t = NV - 1; t >= 0; --t) {
+            const unsigned long long hit = __ballot(lane + 64 * t < P && value(g, t) == bf);
+            if (hit) best = 64 * t + __ffsll(hit) - 1;
+        }
+        return best;
+    }
+    // flags of the stop after generation g, 0: none
+    __device__ __forceinline__ int step(int g, bool last) {
+        double f = value(g, 0);
+#pragma unroll
+        for (int t = 1; t < NV; ++t) {
+            const double v = value(g, t);
+            f = v < f ? v : f;
+        }
+        // objectives only fall, so the best changes only when one lies below it
+        // (seldom, once the population has drawn together)
+        if (__ballot(f < bf)) bf = wave_extreme<false>(f);
+        int flags = bf <= vtr ? 4 : 0;  // PT_FLAG_VTR
+        if constexpr (WINDOW) {
+            if (g >= win) {
+                const double old = win < kNodeRing ? l.ring[(g - win) & (kNodeRing - 1)] : gld(hist + (g - win));
+                if (old - bf <= rel_tol * bf) flags |= 1;  // PT_FLAG_CONVERGED
+            }
+            if (lane == 0) l.ring[g & (kNodeRing - 1)] = bf;
+        }
+        if (!flags && g >= max_gens) flags = 2;  // PT_FLAG_MAXGEN
+        if (!(bf >= floor)) flags = kFlagNodeAbort;
+        if (lane == 0) {
+            gst(hist + g, bf);
+            sh.stop[g & 1] = flags;
+        }
+        flags = __builtin_amdgcn_readfirstlane(flags);
+        const bool look = (g & 15) == 15 && kind < 2 && pend < 0;
+        if (__builtin_expect(flags || last || look, 0)) {
+            const int best = best_of(g, bf);
+            if (lane == 0) {
+                sh.best = best;
+                sh.best_f = bf;
+                sh.stop_gen = g;
+            }
+            if (look && !flags) {
+                ask_level(nd, l, sh, P, F, g, best);
+                pend = __builtin_amdgcn_readfirstlane(sh.next.pend);
+            }
+        }
+        return flags;
+    }
+    // the members' barriers, one generation behind them, and the last
+    // generation's books
+    __device__ __forceinline__ int run(int g0, int g1) {
+        int f2 = 0, f1 = 0;  // flags of generations g - 2 and g - 1
+        for (int g = g0; g < g1; ++g) {
+            if (pend == g) {
+                relevel(nd, l, sh);
+                pend = -1;
+                kind = __builtin_amdgcn_readfirstlane(sh.lev.kind);
+            }
+            if (f2) return g;
+            f1 = g > g0 ? step(g - 1, false) : 0;
+            lds_barrier();
+            f2 = f1;
+        }
+        if (!f2) step(g1 - 1, true);
+        return g1;
+    }
+};
+
+// The generations of the members' waves.  A stop after generation g is found
+// while g + 1 runs and seen by every wave while it works on g + 2, before it
+// writes anything (where the flag's LDS read costs nothing): g + 2 is returned.
+// g1: the launch's generations are done.
 template <int NM, bool SLOPE, bool QUART, bool COR>
 struct Members {
     const NodeDesc* nd;
     const FitLds& l;
     FitShared& sh;
-    int g0, g1, P, K, l8, jl, m0, nrow;
-    bool slot;
+    int g0, g1, P, K, l8;
+    bool slot, stops;  // the lane holds a slot; a stop rule is on
     double N, S2, F, lo, hi, mid_w, sc, en_w;
+    int m[NM];         // members (an octet past the population repeats its last member)
     double xi[NM], fo[NM];
 
     __device__ __forceinline__ Members(const NodeDesc* nd_, const BlockDesc* d, int g0_, int g1_, bool fresh,
                                        const FitLds& l_, FitShared& sh_)
         : nd(nd_), l(l_), sh(sh_), g0(g0_), g1(g1_) {
-        const int tid = threadIdx.x, lane = tid & 63;
+        const int tid = threadIdx.x;
         P = d->P;
         K = nd->K;
         N = (double)d->n;
         S2 = sh.S2;
         F = d->F;
-        l8 = lane & 7;
-        // constants of the slot this lane holds (lane 7: none)
+        l8 = tid & 7;
+        // constants of the slot this lane holds (lane 7: the objective's place)
         slot = l8 < kSlots;
-        jl = slot ? l8 : kSlots - 1;
-        lo = gld(&d->lo[jl]);
-        hi = gld(&d->hi[jl]);
-        mid_w = slot ? gld(&nd->mid[jl]) : 0.0;
-        sc = slot ? gld(&nd->sc[jl]) : 0.0;
+        const int j = slot ? l8 : kSlots - 1;
+        lo = gld(&d->lo[j]);
+        hi = gld(&d->hi[j]);
+        mid_w = slot ? gld(&nd->mid[j]) : 0.0;
+        sc = slot ? gld(&nd->sc[j]) : 0.0;
         en_w = node_energy(l.zw, K, N);
-        m0 = ((tid >> 6) << 3) + (lane >> 3);
-        nrow = 8 * ((int)(blockDim.x >> 6) - 1);
+        // (fits of a fixed number of generations are stopped by nothing but their
+        // abandonment, which may come late)
+        stops = (d->rel_tol > 0.0 && d->window > 0) || d->vtr > -__builtin_inf();
         const double* x = l.xs + ((g0 + 1) & 1) * P * kRowD;
 #pragma unroll
         for (int t = 0; t < NM; ++t) {
-            xi[t] = x[member(t) * kRowD + jl];
-            fo[t] = fresh ? __builtin_inf() : x[member(t) * kRowD + kSlots];
+            m[t] = min((tid >> 3) + t * 8 * ((int)(blockDim.x >> 6) - 1), P - 1);
+            xi[t] = slot ? x[m[t] * kRowD + l8] : 0.0;
+            fo[t] = fresh ? __builtin_inf() : x[m[t] * kRowD + kSlots];
         }
     }
-    __device__ __forceinline__ int member(int t) const { return min(m0 + t * nrow, P - 1); }
-    __device__ __forceinline__ uint64_t draw(int t, int g) const { return l.dr[(g - g0) * P + member(t)]; }
+    __device__ __forceinline__ uint64_t draw(int t, int g) const { return l.dr[(g - g0) * P + m[t]]; }
 
-    // trial coordinate of member t with draws w: apply_trial's arithmetic
-    __device__ __forceinline__ double trial(int t, int g, uint64_t w) const {
-        const char* x = reinterpret_cast<const char*>(l.xs + ((g + 1) & 1) * P * kRowD + jl);
+    // mutant coordinate v of draws w and its base x1 (generation g): apply_trial's
+    // arithmetic
+    __device__ __forceinline__ void mutant(int g, uint64_t w, double& v, double& x1) const {
+        const char* x = reinterpret_cast<const char*>(l.xs + ((g + 1) & 1) * P * kRowD + l8);
         const uint32_t a = (uint32_t)w, b = (uint32_t)(w >> 32);
-        const double x1 = *reinterpret_cast<const double*>(x + (a & 0xFFFFu));
+        x1 = *reinterpret_cast<const double*>(x + (a & 0xFFFFu));
         const double x2 = *reinterpret_cast<const double*>(x + (a >> 16));
         const double x3 = *reinterpret_cast<const double*>(x + (b & 0xFFFFu));
-        double v = __fma_rn(F, x2 - x3, x1);
-        if (v < lo) v = (lo + x1) * 0.5;
-        if (v > hi) v = (hi + x1) * 0.5;
-        return (b >> (16 + l8)) & 1u ? v : xi[t];
+        v = __fma_rn(F, x2 - x3, x1);
+    }
+    __device__ __forceinline__ bool crossed(uint64_t w) const { return (uint32_t)(w >> 48) >> l8 & 1u; }
+    // the bound rule (a mutant put half-way to one bound lies inside the other)
+    __device__ __forceinline__ double bounded(double v, double x1) const {
+        const double vl = (lo + x1) * 0.5, vh = (hi + x1) * 0.5;
+        return v < lo ? vl : (v > hi ? vh : v);
     }
     __device__ __forceinline__ double full(double y) const {
         const NodeCand q = node_cand<SLOPE, QUART>((y - mid_w) * sc);
@@ -683,29 +788,34 @@ struct Members {
         lds_sums<SLOPE, QUART, COR>(q, l.zw, l.un, l8, K, a1, a2);
         return node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en_w, N);
     }
+    template <bool FIRST = false>
     __device__ __forceinline__ void keep(int t, int g, double y, double ft) {
-        const bool take = g == 0 || ft <= fo[t];
+        const bool take = (FIRST && g == 0) || ft <= fo[t];  // (generation 0 is accepted as it is)
         xi[t] = take ? y : xi[t];
         fo[t] = take ? ft : fo[t];
-        const int m = m0 + t * nrow;
-        if (m < P) l.xs[(g & 1) * P * kRowD + m * kRowD + l8] = slot ? xi[t] : fo[t];
+        // (octets that repeat the last member write the same values)
+        l.xs[(g & 1) * P * kRowD + m[t] * kRowD + l8] = slot ? xi[t] : fo[t];
     }
-    // the end of generation g: true when generation g - 1 stopped the fit
-    __device__ __forceinline__ bool stopped(int g) const {
-        __syncthreads();
-        return g > g0 && sh.stop[g & 1];
+    // in generation g: whether generation g - 2 stopped the fit
+    __device__ __forceinline__ int stop_flag(int g) const { return g > g0 + 1 ? sh.stop[g & 1] : 0; }
+    // centre of the set in effect and the range it carries within the box, of the
+    // lane's slot
+    __device__ __forceinline__ void limits(double& mid, double& nlo, double& nhi) const {
+        mid = slot ? sh.lev.mid[l8] : 0.0;
+        const double lim = slot ? sh.lev.lim[l8] : __builtin_inf();
+        nlo = slot ? fmax(lo, mid - lim) : -__builtin_inf();
+        nhi = slot ? fmin(hi, mid + lim) : __builtin_inf();
     }
 
     // generations on the full set, or a re-expanded one in LDS, until one of kind
     // 1 or 2 is in effect
     __device__ __forceinline__ bool lds_loop(int& g) {
         int n = sh.lev.K;
-        double mid = 0.0, lim = 0.0, en = 0.0;
+        double mid = 0.0, nlo = 0.0, nhi = 0.0, en = 0.0;
         auto level = [&]() {
             n = sh.lev.K;
             if (!n) return;
-            mid = slot ? sh.lev.mid[jl] : 0.0;
-            lim = slot ? sh.lev.lim[jl] : __builtin_inf();
+            limits(mid, nlo, nhi);
             en = node_energy(l.lz, n, N);
         };
         level();
@@ -715,11 +825,18 @@ struct Members {
                 if (sh.lev.kind) return false;
                 level();
             }
+            if (stop_flag(g)) return true;
 #pragma unroll
             for (int t = 0; t < NM; ++t) {
-                const double y = g > 0 ? trial(t, g, draw(t, g)) : xi[t];
+                double y = xi[t];
+                if (g > 0) {
+                    const uint64_t w = draw(t, g);
+                    double v, x1;
+                    mutant(g, w, v, x1);
+                    y = crossed(w) ? bounded(v, x1) : xi[t];
+                }
                 double ft;
-                if (n && __ballot(fabs(y - mid) <= lim) == ~0ull) {
+                if (n && __ballot(y >= nlo && y <= nhi) == ~0ull) {
                     const NodeCand q = node_cand<SLOPE, QUART>((y - mid) * sc);
                     double a1 = 0.0, a2 = 0.0;
                     lds_sums<SLOPE, QUART, COR>(q, l.lz, l.lu, l8, n, a1, a2);
@@ -727,16 +844,20 @@ struct Members {
                 } else {
                     ft = full(y);
                 }
-                keep(t, g, y, ft);
+                keep<true>(t, g, y, ft);
             }
-            if (stopped(g)) return true;
+            lds_barrier();
         }
         return false;
     }
 
-    // generations on 16 (KIND 1) or 8 (KIND 2) nodes in registers
-    template <int KIND>
-    __device__ __forceinline__ bool register_loop(int& g) {
+    // generations on 16 (KIND 1) or 8 (KIND 2) nodes in registers.  BOUNDS: the
+    // bound rule is applied on the way; otherwise a mutant outside the box takes
+    // the side path of those outside the set's limits, and a wave that takes it
+    // often (a population pressed against a bound) goes over to BOUNDS: `often` is
+    // set.  Both give the same bits.
+    template <int KIND, bool STOPS, bool BOUNDS>
+    __device__ __forceinline__ bool register_loop(int& g, bool& often) {
         constexpr int R = KIND == 1 ? 2 : 1;  // nodes per lane
         constexpr int D = KIND == 1 ? kNarDeg64 : kNar8Deg64;
         double zr[R], zi[R], wr[R], wi[R], u[R];
@@ -750,7 +871,8 @@ struct Members {
             u[r] = l.lu[k];
         }
         const double en = node_energy(l.lz, 8 * R, N);
-        const double mid = slot ? sh.lev.mid[jl] : 0.0, lim = slot ? sh.lev.lim[jl] : __builtin_inf();
+        double mid, nlo, nhi;
+        limits(mid, nlo, nhi);
         double kc[D + 1], ks[D + 1];  // held in vector registers
 #pragma unroll
         for (int k = 0; k <= D; ++k) {
@@ -758,6 +880,23 @@ struct Members {
             ks[k] = KIND == 1 ? kSinNar64[k] : kSinNar8[k];
             asm volatile("" : "+v"(kc[k]), "+v"(ks[k]));
         }
+        auto value = [&](double y) {
+            const NodeCand q = node_cand<SLOPE, QUART>((y - mid) * sc);
+            double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double x = node_delta<QUART>(q, u[r]), x2 = x * x;
+                double c = kc[0], s = ks[0];
+#pragma unroll
+                for (int k = 1; k <= D; ++k) {
+                    c = __fma_rn(c, x2, kc[k]);
+                    s = __fma_rn(s, x2, ks[k]);
+                }
+                node_terms<SLOPE, COR>(q, u[r], c, s * x, zr[r], zi[r], wr[r], wi[r], a1, a2);
+            }
+            return node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
+        };
+        int side = 0;
         uint64_t w[NM];
 #pragma unroll
         for (int t = 0; t < NM; ++t) w[t] = draw(t, g);
@@ -766,58 +905,62 @@ struct Members {
                 relevel(nd, l, sh);
                 return false;
             }
+            const int stop = STOPS ? stop_flag(g) : 0;
 #pragma unroll
             for (int t = 0; t < NM; ++t) {
-                const double y = trial(t, g, w[t]);
-                if (g + 1 < g1) w[t] = draw(t, g + 1);
-                const double dn = y - mid;
-                const unsigned long long inside = __ballot(fabs(dn) <= lim);
-                const NodeCand q = node_cand<SLOPE, QUART>(dn * sc);
-                double a1 = 0.0, a2 = 0.0;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double x = node_delta<QUART>(q, u[r]), x2 = x * x;
-                    double c = kc[0], s = ks[0];
-#pragma unroll
-                    for (int k = 1; k <= D; ++k) {
-                        c = __fma_rn(c, x2, kc[k]);
-                        s = __fma_rn(s, x2, ks[k]);
-                    }
-                    s *= x;
-                    node_terms<SLOPE, COR>(q, u[r], c, s, zr[r], zi[r], wr[r], wi[r], a1, a2);
-                }
-                double ft = node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
-                // (the limits are tested last, off the chain of dependent
-                // operations: outside them the value above is dropped)
+                double v, x1;
+                mutant(g, w[t], v, x1);
+                double y = crossed(w[t]) ? (BOUNDS ? bounded(v, x1) : v) : xi[t];
+                const unsigned long long inside = __ballot(y >= nlo) & __ballot(y <= nhi);
+                double ft = value(y);
+                // (the limits are tested last, off the chain of dependent operations:
+                // outside them the value above is dropped)
                 asm volatile("" : "+v"(ft));
-                if (__builtin_expect(inside != ~0ull, 0)) ft = full(y);
+                if (__builtin_expect(inside != ~0ull, 0)) {
+                    if constexpr (BOUNDS) {
+                        ft = full(y);
+                    } else {
+                        y = crossed(w[t]) ? bounded(v, x1) : xi[t];
+                        ft = __ballot(y >= nlo && y <= nhi) == ~0ull ? value(y) : full(y);
+                        side += 4;
+                    }
+                }
+                w[t] = draw(t, min(g + 1, g1 - 1));
+                if (STOPS && t == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(stop), 0)) return true;
                 keep(t, g, y, ft);
             }
-            if (stopped(g)) return true;
+            lds_barrier();
+            if constexpr (!BOUNDS) {
+                if (side > 0 && --side > 16) {
+                    often = true;
+                    ++g;
+                    return false;
+                }
+            }
         }
         return false;
+    }
+    template <bool STOPS>
+    __device__ __forceinline__ void narrow(int& g) {
+        bool often = false;
+        if (register_loop<2, STOPS, false>(g, often)) return;
+        if (often && g < g1) register_loop<2, STOPS, true>(g, often);
     }
 
     __device__ __forceinline__ int run() {
         int g = g0;
+        bool often = true;
         if (sh.lev.kind == 0 && lds_loop(g)) return g;
-        if (g < g1 && sh.lev.kind == 1 && register_loop<1>(g)) return g;
-        if (g < g1 && register_loop<2>(g)) return g;
+        if (g < g1 && sh.lev.kind == 1 && register_loop<1, true, true>(g, often)) return g;
+        if (g < g1) {
+            if (stops)
+                narrow<true>(g);
+            else
+                narrow<false>(g);
+        }
         return g;
     }
 };
-
-// The same barriers for the bookkeeping wave, one generation behind.
-__device__ __forceinline__ int book_loop(const NodeDesc* nd, const BlockDesc* d, int g0, int g1, const FitLds& l,
-                                         FitShared& sh) {
-    for (int g = g0; g < g1; ++g) {
-        if (sh.next.pend == g) relevel(nd, l, sh);
-        if (g > g0) book(nd, d, l, sh, g - 1);
-        __syncthreads();
-        if (g > g0 && sh.stop[g & 1]) return g;
-    }
-    return g1;
-}
 
 template <int NM, bool COR>
 __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, int g0, int ngen, bool fresh, const FitLds& l,
@@ -825,22 +968,23 @@ __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, 
     const int tid = threadIdx.x, NT = blockDim.x, W = (NT >> 6) - 1, P = d->P, g1 = g0 + ngen;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int g;
-    if (wave == W)
-        g = book_loop(nd, d, g0, g1, l, sh);
-    else if (nd->slope)
+    if (wave == W) {
+        const bool window = d->rel_tol > 0.0 && d->window > 0;
+        if (P <= 64)
+            g = window ? Book<1, true>(nd, d, l, sh).run(g0, g1) : Book<1, false>(nd, d, l, sh).run(g0, g1);
+        else
+            g = window ? Book<4, true>(nd, d, l, sh).run(g0, g1) : Book<4, false>(nd, d, l, sh).run(g0, g1);
+    } else if (nd->slope) {
         g = d->quartic ? Members<NM, true, true, COR>(nd, d, g0, g1, fresh, l, sh).run()
                        : Members<NM, true, false, COR>(nd, d, g0, g1, fresh, l, sh).run();
-    else
+    } else {
         g = d->quartic ? Members<NM, false, true, COR>(nd, d, g0, g1, fresh, l, sh).run()
                        : Members<NM, false, false, COR>(nd, d, g0, g1, fresh, l, sh).run();
-    int flags;
-    if (g < g1) {
-        flags = sh.stop[g & 1];  // generation g - 1 stopped the fit; g is dropped
-    } else {
-        if (wave == W) book(nd, d, l, sh, g1 - 1);
-        __syncthreads();
-        flags = sh.stop[g1 & 1];
     }
+    __syncthreads();
+    // a stop of the last generation but one, or of the last; otherwise the last is kept
+    int flags = sh.stop[g & 1];
+    if (g == g1 && !(ngen > 1 && flags)) flags = sh.stop[(g1 - 1) & 1];
 
     // state for the next launch: the population after the last kept generation
     const int gl = flags ? sh.stop_gen : g1 - 1;
