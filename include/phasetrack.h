@@ -220,8 +220,8 @@ int pt_objective(pt_ctx* ctx, const pt_block* block, const double* pop, int P,
  * forbid device allocation).  Arguments, results and the arithmetic are those
  * of pt_objective (same kernels, same geometry, bit-identical outputs); the
  * caller still owns pop and out.
- *   - The descriptor, the packed rows and the P x ceil(n / (256 S)) tile
- *     partial sums (S = samples per lane of the chosen geometry) live in the
+ *   - The P x ceil(n / (256 S)) tile partial sums (S = samples per lane of the
+ *     chosen geometry), past 1 KiB + 64 P bytes set aside, live in the
  *     library's fixed array of PT_NOALLOC_SCRATCH_BYTES bytes; a call that
  *     needs more (roughly P x n > 2e9 samples at 16 samples per lane) fails with
  *     PT_EINVAL and a message giving the size it needed.

@@ -15,6 +15,9 @@ namespace pt {
 // preloading puts them in scalar registers (see LeadIn)
 using ObjKernel = void (*)(int, int, int, int, const double*, const double*, const double*, const double*,
                            const BlockDesc*);
+// k_eval(block, pop, out, sync, arith, rule, total_units)
+struct EvalRule;
+using EvalKernel = void (*)(BlockDesc, const double*, double*, int*, int*, EvalRule, int);
 using PersistKernel = void (*)(const BlockDesc*, int, int, int, int, int*, uint64_t);
 
 // Kernel arithmetic modes (template argument MODE of the kernels).
@@ -26,6 +29,7 @@ enum { kModePoly = PT_ARITH_FP64_POLY, kModeMixed = PT_ARITH_MIXED, kModePhasor 
 // from the descriptor, 2 the one taking them as kernel arguments (one block).
 #define PT_DECLARE_INSTANCES(TN, S)                                                 \
     ObjKernel objective_kernel_##TN##_s##S(int cpg, int mode, bool slope, int lead); \
+    EvalKernel eval_kernel_##TN##_s##S(int cpg, bool mixed);                         \
     PersistKernel persistent_kernel_##TN##_s##S(int cpg, int mode, bool slope);
 PT_DECLARE_INSTANCES(f32, 4)
 PT_DECLARE_INSTANCES(f32, 8)

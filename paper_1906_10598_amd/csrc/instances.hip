@@ -56,6 +56,15 @@ ObjKernel PT_NAME(objective_kernel_)(int cpg, int mode, bool slope, int lead) {
     }
 }
 
+EvalKernel PT_NAME(eval_kernel_)(int cpg, bool mixed) {
+    switch (cpg) {
+        case 1: return mixed ? k_eval<T, S, 1, true> : k_eval<T, S, 1, false>;
+        case 2: return mixed ? k_eval<T, S, 2, true> : k_eval<T, S, 2, false>;
+        case 4: return mixed ? k_eval<T, S, 4, true> : k_eval<T, S, 4, false>;
+        default: return mixed ? k_eval<T, S, 8, true> : k_eval<T, S, 8, false>;
+    }
+}
+
 PersistKernel PT_NAME(persistent_kernel_)(int cpg, int mode, bool slope) {
     switch (cpg) {
         case 1: return ppick_mode<1>(mode, slope);

@@ -159,6 +159,24 @@ __device__ __forceinline__ void wave_sums(double (&v)[N]) {
     for (int r = 0; r < N; ++r) v[r] = swap_add<true>(v[r]);
 }
 
+// Smallest (largest) value of the wave, in every lane, by the same moves.  A
+// compare and a select: fmin would first quieten its operands.  A NaN on the
+// left stays, one on the right is passed over.
+template <bool MAX>
+__device__ __forceinline__ double wave_extreme(double v) {
+    auto pick = [](double a, double b) { return (MAX ? b > a : b < a) ? b : a; };
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v = pick(v, dpp_move(v, s));
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = pick(__hiloint2double(h16[0], l16[0]), __hiloint2double(h16[1], l16[1]));
+    const int lo2 = __double2loint(v), hi2 = __double2hiint(v);
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+    const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+    return pick(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
+}
+
 __device__ __forceinline__ int find_block(const BlockDesc* __restrict__ descs, int nblk, int unit) {
     int lo = 0, hi = nblk - 1;
     while (lo < hi) {
@@ -219,6 +237,43 @@ __device__ __forceinline__ Cand make_cand(const double* x, double fs) {
 struct Anchor {
     double b0, b1, b2, b3, b4;
 };
+
+// Validity of the FP64 phasor path (see lane_rot) for every candidate with
+// f0 in [f0lo, f0hi], |f1| <= f1max, |f2| <= f2max, |f3| <= f3max and chunk
+// centres |m| <= span samples from the reference (turns per sample^k at a
+// centre: c3 = a3 + 4 a4 m, c2 = a2 + 3 a3 m + 6 a4 m^2, c1 = f(t) / fs), with
+// C = S / 2 and T = 256 S samples per tile:
+//   (1) C^3 |c3| + C^4 |c4| <= 1e-12 turns (dropped terms);
+//   (2) theta^2 / 2 <= 1e-11 with theta = 2 pi |c2| C^2 (first-order
+//       quadratic correction);
+//   (3) |sin 2 pi c1| >= S * 2.2e-4 over the block's frequency range
+//       (conditioning of the three-term recurrence): c1 at least `delta` =
+//       asin(S 2.2e-4) / (2 pi) from every multiple of 1/2;
+//   (4) 2 pi T (2 |c2| + 3 |c3| T + 4 |c4| T^2) <= 6e-3: the local frequency
+//       moves by less than that angle across a tile (small-angle rotation).
+// (Host and device decide alike: no contraction.)
+__host__ __device__ inline bool phasor_valid(int spl, double delta, double fs, double span, double f0lo, double f0hi,
+                                             double f1max, double f2max, double f3max) {
+#pragma clang fp contract(off)
+    const double two_pi = 2.0 * 3.14159265358979323846;
+    const double a3 = f2max / (6.0 * fs * fs * fs);
+    const double a4 = f3max / (24.0 * fs * fs * fs * fs);
+    const double b3 = a3 + 4.0 * a4 * span;
+    const double b2 = f1max / (2.0 * fs * fs) + 3.0 * a3 * span + 6.0 * a4 * span * span;
+    const double C = spl / 2;
+    if (!(C * C * C * (b3 + C * a4) <= 1e-12)) return false;
+    const double th = two_pi * b2 * C * C;
+    if (!(0.5 * th * th <= 1e-11)) return false;
+    const double T = 256.0 * spl;
+    if (!(two_pi * T * (2.0 * b2 + 3.0 * b3 * T + 4.0 * a4 * T * T) <= 6e-3)) return false;
+    const double tmax = span / fs;
+    const double dev = f1max * tmax + f2max * tmax * tmax / 2.0 + f3max * tmax * tmax * tmax / 6.0;
+    const double xlo = (f0lo - dev) / fs, xhi = (f0hi + dev) / fs;  // turns per sample
+    if (!(fabs(xlo) < 1e300 && fabs(xhi) < 1e300) || xhi - xlo > 1e6) return false;
+    // no multiple of 1/2 within delta of [xlo, xhi]
+    const double k0 = ceil(2.0 * (xlo - delta));
+    return !(k0 / 2.0 <= xhi + delta);
+}
 
 __device__ __forceinline__ Anchor make_anchor(const Cand& c, double m0) {
     Anchor a;
@@ -798,11 +853,10 @@ __device__ __forceinline__ double reduce_partials(const BlockDesc* __restrict__ 
 // out[p] = objective of candidate p (bare evaluation, no DE state); one
 // workgroup of the DE step's size, NT doubles of dynamic LDS.
 #ifndef PT_INSTANCE_TU  // (the instance translation units hold only templates)
-__global__ void k_reduce_out(const BlockDesc* __restrict__ descs, double* __restrict__ out) {
+__global__ void k_reduce_eval(BlockDesc d, double* __restrict__ out) {
     extern __shared__ double red[];
-    const BlockDesc* d = descs;
-    const double v = reduce_partials<false>(d, d->partials, red);
-    if ((int)threadIdx.x < d->P) out[threadIdx.x] = v;
+    const double v = reduce_partials<false>(&d, d.partials, red);
+    if ((int)threadIdx.x < d.P) out[threadIdx.x] = v;
 }
 #endif
 
@@ -1498,6 +1552,147 @@ __device__ __forceinline__ bool de_lead(const BlockDesc* __restrict__ d, int L, 
         xst(&st_out->old, old);
     }
     return false;
+}
+
+// ---------------------------------------------------------------------------
+// Bare objective of a caller's population (no DE state), in one launch.
+//
+// The population lives on the device and decides the arithmetic: the amplitude
+// slope and the quartic term are on when any row uses them, and the FP64 phasor
+// path applies where every row satisfies its bounds.  Reading the rows back to
+// decide on the host cost a copy and a synchronisation (about 20 of the 55 us of
+// a call on the paper-scale block), so every workgroup takes the rows' extents
+// itself, while its samples are on their way, and runs the variant they allow;
+// where the launch would take several rounds of resident workgroups, a workgroup
+// takes several groups of candidates through the samples it holds.
+// A call takes (before -> now) 50 -> 25 us for 32 rows over 4096 samples (launch
+// and synchronisation), 55 -> 31 us for 40 rows over 4e5, 97 -> 90 us for 160
+// rows over 1e6 samples (there the FP64 instructions bound it).
+// Rows come straight from the caller; the workgroup that finishes last adds up
+// the tiles' partial sums (reduce_partials with 256 threads; `tail` = 0 for
+// larger populations, whose sums k_reduce_eval adds) and leaves the counters
+// at zero for the next call.
+// ---------------------------------------------------------------------------
+struct EvalRule {
+    double span, delta;  // phasor_valid's
+    int phasor;          // the phasor path may be used at all
+    int tail;            // the last workgroup writes `out`
+    int gpw;             // candidate groups per workgroup, at most kEvalMembers / CPG
+};
+constexpr int kEvalMembers = 64;
+
+template <typename T, int S, int CPG, bool MIXED>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_eval(
+    BlockDesc d, const double* __restrict__ pop, double* __restrict__ out, int* __restrict__ sync,
+    int* __restrict__ arith, EvalRule rule, int total_units) {
+    const int bid = blockIdx.x, Ux = (int)gridDim.x >> 3, unit = (bid & 7) * Ux + (bid >> 3);
+    if (unit >= total_units) return;
+    const int parts = (d.ngroups + rule.gpw - 1) / rule.gpw;
+    const int tile = unit / parts, g0 = (unit - tile * parts) * rule.gpw, g1 = min(g0 + rule.gpw, d.ngroups);
+    const int tid = threadIdx.x;
+    using V = typename std::conditional<MIXED, float, double>::type;
+    __shared__ Cand cs[kEvalMembers];
+    __shared__ RotConst rc[MIXED ? 1 : kEvalMembers];
+    __shared__ double red[CPG < 2 ? 2 : CPG][kThreads];
+    __shared__ double ext[kThreads / 64][5];
+    __shared__ int s_bits[kThreads / 64], s_last;
+    T raw[S];
+    load_lane_raw<T, S>(&d, tile, raw);
+
+    // extents of the rows: f0 from .. to, largest |f1|, |f2|, |f3|, and whether
+    // slots 5 and 6 are used
+    double x[5] = {__builtin_inf(), -__builtin_inf(), 0.0, 0.0, 0.0};
+    int bits = 0;
+    for (int p = tid; p < d.P; p += kThreads) {
+        const double* r = pop + (size_t)p * kSlots;
+        const double f0 = gld(r + 2), f1 = fabs(gld(r + 3)), f2 = fabs(gld(r + 4)), a5 = gld(r + 5), f3 = gld(r + 6);
+        x[0] = f0 < x[0] ? f0 : x[0];
+        x[1] = x[1] < f0 ? f0 : x[1];
+        x[2] = x[2] < f1 ? f1 : x[2];
+        x[3] = x[3] < f2 ? f2 : x[3];
+        x[4] = x[4] < fabs(f3) ? fabs(f3) : x[4];
+        bits |= (a5 != 0.0 ? 1 : 0) | (f3 != 0.0 ? 2 : 0);
+    }
+    const int lane = tid & 63, wave = tid >> 6;
+    bits = (__ballot(bits & 1) ? 1 : 0) | (__ballot(bits & 2) ? 2 : 0);
+    x[0] = wave_extreme<false>(x[0]);
+#pragma unroll
+    for (int k = 1; k < 5; ++k) x[k] = wave_extreme<true>(x[k]);
+    if (lane < 5) ext[wave][lane] = lane == 0 ? x[0] : lane == 1 ? x[1] : lane == 2 ? x[2] : lane == 3 ? x[3] : x[4];
+    if (lane == 0) s_bits[wave] = bits;
+    const int cbase = g0 * CPG, ncand = min(g1 * CPG, d.P) - cbase;
+    if (tid < ncand) cs[tid] = make_cand<false>(pop + (size_t)(cbase + tid) * kSlots, d.fs);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kThreads / 64; ++q) {
+        bits |= s_bits[q];
+        x[0] = ext[q][0] < x[0] ? ext[q][0] : x[0];
+#pragma unroll
+        for (int k = 1; k < 5; ++k) x[k] = x[k] < ext[q][k] ? ext[q][k] : x[k];
+    }
+    const bool slope = __builtin_amdgcn_readfirstlane(bits & 1);
+    d.quartic = __builtin_amdgcn_readfirstlane(bits >> 1);
+    bool phasor = false;
+    if constexpr (!MIXED) {
+        phasor = rule.phasor && x[2] < __builtin_inf() && x[3] < __builtin_inf() && x[4] < __builtin_inf() &&
+                 phasor_valid(S, rule.delta, d.fs, rule.span, x[0], x[1], x[2], x[3], x[4]);
+        phasor = __builtin_amdgcn_readfirstlane((int)phasor);
+        if (phasor) {
+            const double mt = (double)((int64_t)tile * (kThreads * S)) - d.ref;  // the tile's first sample
+            if (tid < ncand) rc[tid] = slope ? make_rot_const<S, true>(cs[tid], mt) : make_rot_const<S, false>(cs[tid], mt);
+            __syncthreads();
+        }
+    }
+    V sv[S];
+    bool full;
+    int valid;
+    finish_lane<V, T, S>(&d, tile, raw, sv, full, valid);
+    // one loop per variant (see objective_unit)
+    auto run = [&](auto mode, auto sl) {
+        for (int g = g0; g < g1; ++g) {
+            const int c0 = (g - g0) * CPG;
+            objective_unit<S, CPG, decltype(mode)::value, decltype(sl)::value>(&d, tile, g, sv, full, valid, cs + c0,
+                                                                               rc + (MIXED ? 0 : c0), red, d.partials);
+            if (g + 1 < g1) __syncthreads();  // red is free again
+        }
+    };
+    using M0 = std::integral_constant<int, MIXED ? 1 : 0>;
+    if (!MIXED && phasor) {
+        if (slope)
+            run(std::integral_constant<int, MIXED ? 1 : 2>{}, std::true_type{});
+        else
+            run(std::integral_constant<int, MIXED ? 1 : 2>{}, std::false_type{});
+    } else {
+        if (slope)
+            run(M0{}, std::true_type{});
+        else
+            run(M0{}, std::false_type{});
+    }
+    if (unit == 0 && tid == 0) *arith = MIXED ? 1 : (phasor ? 2 : 0);
+    if (!rule.tail) return;
+
+    // arrivals, counted per XCD range first as in k_objective
+    __syncthreads();  // every wave's partial stores are issued
+    if (tid == 0) {
+        const int xcd = bid & 7, nx = min(total_units, (xcd + 1) * Ux) - xcd * Ux;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, PT_REL_SCOPE);
+        bool last = __hip_atomic_fetch_add(sync + xcd * kSyncLine, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nx - 1;
+        if (last) {
+            const int nranges = (total_units + Ux - 1) / Ux;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, PT_ACQ_SCOPE);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, PT_REL_SCOPE);
+            last = __hip_atomic_fetch_add(sync + 16 * kSyncLine, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                   nranges - 1;
+            if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, PT_ACQ_SCOPE);
+        }
+        s_last = last;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    const double v = reduce_partials<true>(&d, d.partials, &red[0][0]);
+    if (tid < d.P) gst(out + tid, v);
+    if (tid < 8) __hip_atomic_store(sync + tid * kSyncLine, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 8) __hip_atomic_store(sync + 16 * kSyncLine, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------

@@ -66,25 +66,6 @@ __device__ __forceinline__ double oct_sum(double v) {
     return v;
 }
 
-template <bool MAX>
-__device__ __forceinline__ double wave_extreme(double v) {
-    // (a compare and a select: fmin would first quieten its operands.  A NaN
-    // on the left stays, one on the right is passed over)
-    auto pick = [](double a, double b) { return (MAX ? b > a : b < a) ? b : a; };
-    v = pick(v, lane_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
-    v = pick(v, lane_move<0x4E>(v));   // quad_perm [2, 3, 0, 1]
-    v = pick(v, lane_move<0x141>(v));  // row_half_mirror
-    v = pick(v, lane_move<0x140>(v));  // row_mirror
-    const int lo = __double2loint(v), hi = __double2hiint(v);
-    const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    v = pick(__hiloint2double(h16[0], l16[0]), __hiloint2double(h16[1], l16[1]));
-    const int lo2 = __double2loint(v), hi2 = __double2hiint(v);
-    const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
-    const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
-    return pick(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
-}
-
 // Barrier that orders LDS only: a wave does not wait for its global stores (the
 // history's) to be acknowledged, which takes longer than a generation.
 __device__ __forceinline__ void lds_barrier() {

@@ -145,6 +145,16 @@ ObjKernel objective_kernel(int dtype, Geometry g, int mode, bool slope, int lead
     }
 }
 
+EvalKernel eval_kernel(int dtype, Geometry g, bool mixed) {
+    const bool f64 = dtype == PT_F64;
+    switch (g.spl) {
+        case 4: return f64 ? eval_kernel_f64_s4(g.cpg, mixed) : eval_kernel_f32_s4(g.cpg, mixed);
+        case 8: return f64 ? eval_kernel_f64_s8(g.cpg, mixed) : eval_kernel_f32_s8(g.cpg, mixed);
+        case 16: return f64 ? eval_kernel_f64_s16(g.cpg, mixed) : eval_kernel_f32_s16(g.cpg, mixed);
+        default: return f64 ? eval_kernel_f64_s32(g.cpg, mixed) : eval_kernel_f32_s32(g.cpg, mixed);
+    }
+}
+
 PersistKernel persistent_kernel(int dtype, Geometry g, int mode, bool slope) {
     const bool f64 = dtype == PT_F64;
     switch (g.spl) {
@@ -157,38 +167,13 @@ PersistKernel persistent_kernel(int dtype, Geometry g, int mode, bool slope) {
     }
 }
 
-// Validity of the FP64 phasor path (see lane_rot) for every candidate with
-// f0 in [f0lo, f0hi], |f1| <= f1max, |f2| <= f2max, |f3| <= f3max and chunk
-// centres |m| <= span samples from the reference (turns per sample^k at a
-// centre: c3 = a3 + 4 a4 m, c2 = a2 + 3 a3 m + 6 a4 m^2, c1 = f(t) / fs), with
-// C = S / 2 and T = 256 S samples per tile:
-//   (1) C^3 |c3| + C^4 |c4| <= 1e-12 turns (dropped terms);
-//   (2) theta^2 / 2 <= 1e-11 with theta = 2 pi |c2| C^2 (first-order
-//       quadratic correction);
-//   (3) |sin 2 pi c1| >= S * 2.2e-4 over the block's frequency range
-//       (conditioning of the three-term recurrence);
-//   (4) 2 pi T (2 |c2| + 3 |c3| T + 4 |c4| T^2) <= 6e-3: the local frequency
-//       moves by less than that angle across a tile (small-angle rotation).
+// Distance of the carrier from the multiples of half a turn per sample that the
+// phasor path's condition (3) asks for.
+double phasor_delta(int spl) { return std::asin(std::min(1.0, spl * 2.2e-4)) / (2.0 * M_PI); }
+
 bool phasor_ok(int spl, double fs, double span, double f0lo, double f0hi, double f1max, double f2max,
                double f3max) {
-    const double a3 = f2max / (6.0 * fs * fs * fs);
-    const double a4 = f3max / (24.0 * fs * fs * fs * fs);
-    const double b3 = a3 + 4.0 * a4 * span;
-    const double b2 = f1max / (2.0 * fs * fs) + 3.0 * a3 * span + 6.0 * a4 * span * span;
-    const double C = spl / 2;
-    if (!(C * C * C * (b3 + C * a4) <= 1e-12)) return false;
-    const double th = 2.0 * M_PI * b2 * C * C;
-    if (!(0.5 * th * th <= 1e-11)) return false;
-    const double T = 256.0 * spl;
-    if (!(2.0 * M_PI * T * (2.0 * b2 + 3.0 * b3 * T + 4.0 * a4 * T * T) <= 6e-3)) return false;
-    const double tmax = span / fs;
-    const double dev = f1max * tmax + f2max * tmax * tmax / 2.0 + f3max * tmax * tmax * tmax / 6.0;
-    const double xlo = (f0lo - dev) / fs, xhi = (f0hi + dev) / fs;  // turns per sample
-    if (!(std::isfinite(xlo) && std::isfinite(xhi)) || xhi - xlo > 1e6) return false;
-    const double delta = std::asin(std::min(1.0, spl * 2.2e-4)) / (2.0 * M_PI);
-    // no multiple of 1/2 within delta of [xlo, xhi]
-    const double k0 = std::ceil(2.0 * (xlo - delta));
-    return !(k0 / 2.0 <= xhi + delta);
+    return phasor_valid(spl, phasor_delta(spl), fs, span, f0lo, f0hi, f1max, f2max, f3max);
 }
 
 double box_max(const pt_box& bx, int j) { return std::max(std::fabs(bx.lo[j]), std::fabs(bx.hi[j])); }
@@ -298,6 +283,10 @@ struct pt_ctx {
     std::map<std::tuple<int, int, int>, Geometry> tuned;  // (size class, P, mixed)
     // this device's copy of the allocation-free entry point's array
     unsigned char* noalloc = nullptr;
+    // bare objective evaluations: arrival counters (zero between calls), and the
+    // arithmetic the device chose (pinned host memory)
+    DevBuf eval_sync;
+    PinBuf eval_arith;
     // graph cache
     struct GraphKey {
         void* desc;
@@ -1183,6 +1172,12 @@ int pt_ctx_create(int device, pt_ctx** out) {
     void* na = nullptr;
     HIPCHK(hipGetSymbolAddress(&na, HIP_SYMBOL(scratch)));
     c->noalloc = static_cast<unsigned char*>(na);
+    int rc = c->eval_sync.ensure(kSyncInts * sizeof(int));
+    if (rc || (rc = c->eval_arith.ensure(sizeof(int)))) {
+        c->eval_sync.release();
+        return rc;
+    }
+    HIPCHK(hipMemset(c->eval_sync.p, 0, kSyncInts * sizeof(int)));
     int clk_khz = 0;
     if (hipDeviceGetAttribute(&clk_khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || clk_khz <= 0)
         clk_khz = 100000;
@@ -1219,12 +1214,14 @@ void pt_ctx_destroy(pt_ctx* ctx) {
     }
     DevBuf* bufs[] = {&ctx->desc,    &ctx->pop,      &ctx->trial,   &ctx->fpop,  &ctx->partials, &ctx->hist,
                       &ctx->state,   &ctx->rec,      &ctx->staging, &ctx->eval_pop, &ctx->tune_block, &ctx->errflag,
-                      &ctx->sync,    &ctx->seed_out, &ctx->seed_stage, &ctx->node_desc, &ctx->node_ws};
+                      &ctx->sync,    &ctx->seed_out, &ctx->seed_stage, &ctx->node_desc, &ctx->node_ws,
+                      &ctx->eval_sync};
     for (DevBuf* b : bufs) b->release();
     ctx->hdesc.release();
     ctx->hrec.release();
     ctx->hseed.release();
     ctx->hnode.release();
+    ctx->eval_arith.release();
     ctx->hstate.release();
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
@@ -1356,27 +1353,83 @@ static int eval_setup(pt_ctx* ctx, const pt_block* block, const double* pop, int
     return PT_OK;
 }
 
+// Plan of a bare evaluation: geometry, descriptor (partials not set) and rule.
+// The workgroup that finishes last adds up the tiles' sums where one of 256
+// threads can (P <= 256); the launch of k_reduce_eval that this saves is 3 to 4 us.
+struct EvalPlan {
+    Geometry geo;
+    BlockDesc d;
+    EvalRule rule;
+    int64_t units;
+    EvalKernel kernel;
+};
+static EvalPlan eval_plan(pt_ctx* ctx, const pt_block& blk, int P, int precision, int objective) {
+    EvalPlan e;
+    const bool mixed = precision == PT_PREC_MIXED;
+    e.geo = choose_geometry(ctx, blk.n, P, mixed);
+    const int64_t tile = (int64_t)kThreads * e.geo.spl, ntiles = (blk.n + tile - 1) / tile;
+    // Candidate groups per workgroup: the samples, the rows' extents and the tile
+    // constants are then fetched once for all of them, but a launch of few
+    // workgroups leaves places idle.  With 2 (32 samples per lane), 3 (16) or 4
+    // workgroups resident per compute unit a launch takes ceil(workgroups /
+    // places) rounds, each of the candidates, about one more per group for its
+    // reduction and four for the set-up.  The group size is chosen along with it
+    // unless it was set or tuned (it changes no sum).
+    const int64_t places = 256 * (e.geo.spl == 32 ? 2 : e.geo.spl == 16 ? 3 : 4);
+    const bool given = ctx->forced.spl || ctx->tuned.count(std::make_tuple(size_class(blk.n), P, (int)mixed));
+    const int cpg0 = e.geo.cpg;
+    int64_t best = INT64_MAX;
+    for (int cpg : kCpg) {
+        if (given && cpg != cpg0) continue;
+        const int groups = (P + cpg - 1) / cpg;
+        for (int gpw = 1; gpw <= std::min(groups, kEvalMembers / cpg); ++gpw) {
+            const int64_t wgs = ntiles * ((groups + gpw - 1) / gpw);
+            const int64_t cost = (wgs + places - 1) / places * (std::min(gpw * cpg, P) + gpw + 4);
+            if (cost < best) best = cost, e.rule.gpw = gpw, e.units = wgs, e.geo.cpg = cpg;
+        }
+    }
+    const pt_de_settings de = eval_settings(P, precision, objective);
+    e.d = base_desc(blk, &de, (int)ntiles, (P + e.geo.cpg - 1) / e.geo.cpg);
+    e.rule.span = (double)blk.n + std::fabs(block_ref(&blk));
+    e.rule.delta = phasor_delta(e.geo.spl);
+    e.rule.phasor = ctx->fp64_method != PT_FP64_POLY;
+    e.rule.tail = P <= kThreads;
+    e.kernel = eval_kernel(blk.dtype, e.geo, mixed);
+    return e;
+}
+
+// Enqueue the evaluation, wait for it, and note what it used.
+static int eval_run(pt_ctx* ctx, const EvalPlan& e, const double* pop, double* out, int* sync, hipStream_t s) {
+    int* arith = static_cast<int*>(ctx->eval_arith.p);
+    hipLaunchKernelGGL(e.kernel, dim3((unsigned)((e.units + 7) / 8 * 8)), dim3(kThreads), 0, s, e.d, pop, out, sync, arith,
+                       e.rule, (int)e.units);
+    HIPCHK(hipGetLastError());
+    if (!e.rule.tail) {
+        const unsigned nt = pow2_at_least(e.d.P);
+        hipLaunchKernelGGL(k_reduce_eval, dim3(1), dim3(nt), nt * sizeof(double), s, e.d, out);
+        HIPCHK(hipGetLastError());
+    }
+    HIPCHK(hipStreamSynchronize(s));
+    ctx->last_arith = *arith;
+    ctx->last_geo = e.geo;
+    return PT_OK;
+}
+
 int pt_objective(pt_ctx* ctx, const pt_block* block, const double* pop, int P, int precision, int objective,
                  void* hip_stream, double* out) {
     if (!ctx) return fail(PT_EINVAL, "ctx is null");
     if (!out) return fail(PT_EINVAL, "out is null");
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Plan pl;
-    ObjKernel obj = nullptr;
-    int rc = eval_setup(ctx, block, pop, P, precision, objective, s, &pl, &obj);
+    int rc = check_eval_args(block, pop, P, precision, objective);
     if (rc) return rc;
-    const BlockDesc* d = static_cast<const BlockDesc*>(ctx->desc.p);
-    launch_objective(obj, pl.grid, 0, s, d, 1, pl.total_units, 0);
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce_out, dim3(1), dim3(pl.de_threads), pl.de_threads * sizeof(double), s, d, out);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(s));
-    return PT_OK;
-}
-
-// One descriptor into device memory, passed by value (no host staging).
-__global__ void k_put_desc(BlockDesc d, BlockDesc* dst) {
-    if (threadIdx.x == 0) *dst = d;
+    HIPCHK(hipSetDevice(ctx->device));
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    std::vector<pt_block> staged;
+    if ((rc = stage_blocks(ctx, block, 1, s, &staged))) return rc;
+    EvalPlan e = eval_plan(ctx, staged[0], P, precision, objective);
+    if (e.units > (int64_t)1 << 30) return fail(PT_EINVAL, "batch too large (%lld work units)", (long long)e.units);
+    if ((rc = ctx->partials.ensure((size_t)P * e.d.ntiles * sizeof(double)))) return rc;
+    e.d.partials = static_cast<double*>(ctx->partials.p);
+    return eval_run(ctx, e, pop, out, static_cast<int*>(ctx->eval_sync.p), s);
 }
 
 int pt_objective_noalloc(pt_ctx* ctx, const pt_block* block, const double* pop, int P, int precision,
@@ -1388,72 +1441,22 @@ int pt_objective_noalloc(pt_ctx* ctx, const pt_block* block, const double* pop, 
     if (!block->on_device) return fail(PT_EINVAL, "pt_objective_noalloc: samples must be a device pointer");
     if (!ctx->noalloc) return fail(PT_EDEVICE, "pt_objective_noalloc: no device array on this context");
     HIPCHK(hipSetDevice(ctx->device));
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
-
-    // population extents (the arithmetic choice of pt_objective), read in
-    // pieces through a fixed host buffer
-    constexpr int kRows = 64;
-    double rows_h[kRows * PT_NSLOT];
-    PopExtents ext;
-    for (int r0 = 0; r0 < P; r0 += kRows) {
-        const int cnt = std::min(kRows, P - r0);
-        HIPCHK(hipMemcpyAsync(rows_h, pop + (size_t)r0 * PT_NSLOT, sizeof(double) * PT_NSLOT * cnt,
-                              hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        ext.add(rows_h, cnt);
-    }
-    pt_block blk = *block;
-    ext.apply(blk);
-    const pt_de_settings de = eval_settings(P, precision, objective);
-
-    // the plan pt_objective's set-up makes for one block without DE state
-    Plan pl;
-    pl.nblk = 1;
-    pl.P = P;
-    pl.dtype = blk.dtype;
-    pl.mixed = precision == PT_PREC_MIXED;
-    pl.slope = blk.box.lo[5] != 0.0 || blk.box.hi[5] != 0.0;
-    pl.geo = choose_geometry(ctx, blk.n, P, pl.mixed);
-    pl.mode = pl.mixed ? kModeMixed : kModePoly;
-    pl.mode = ext.mode(pl, ctx, block);
-    const int64_t tile = (int64_t)kThreads * pl.geo.spl;
-    const int groups = (P + pl.geo.cpg - 1) / pl.geo.cpg;
-    const int64_t ntiles = (blk.n + tile - 1) / tile;
-    const int64_t units = ntiles * groups;
-    pl.de_threads = pow2_at_least(P);
-
-    // layout in the array: descriptor | rows (P x kStride) | partials (P x ntiles)
+    EvalPlan e = eval_plan(ctx, *block, P, precision, objective);
+    // the partial sums (P x ntiles) lie in the array past the places of a
+    // descriptor and of packed rows, which count towards its size as stated
     constexpr size_t kDescBytes = 1024;
-    static_assert(sizeof(BlockDesc) <= kDescBytes, "descriptor slot too small");
     const size_t row_bytes = ((size_t)P * kStride * sizeof(double) + 255) & ~(size_t)255;
-    const size_t need = kDescBytes + row_bytes + (size_t)P * (size_t)ntiles * sizeof(double);
+    const size_t need = kDescBytes + row_bytes + (size_t)P * (size_t)e.d.ntiles * sizeof(double);
     if (need > (size_t)PT_NOALLOC_SCRATCH_BYTES)
         return fail(PT_EINVAL,
                     "pt_objective_noalloc: P = %d and n = %lld need %zu bytes of device memory, more than the "
                     "%zu-byte array (P x ceil(n / %lld) partial sums must fit)",
-                    P, (long long)blk.n, need, (size_t)PT_NOALLOC_SCRATCH_BYTES, (long long)tile);
-    BlockDesc* dd = reinterpret_cast<BlockDesc*>(ctx->noalloc);
-    double* rows = reinterpret_cast<double*>(ctx->noalloc + kDescBytes);
-    double* part = reinterpret_cast<double*>(ctx->noalloc + kDescBytes + row_bytes);
-    BlockDesc d = base_desc(blk, &de, (int)ntiles, groups);
-    d.trial = rows;
-    d.pop = rows;
-    d.partials = part;
-
-    const ObjKernel obj = objective_kernel(pl.dtype, pl.geo, pl.mode, pl.slope);
-    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, d, dd);
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_pack_rows, dim3(1), dim3(256), 0, s, pop, rows, P);
-    HIPCHK(hipGetLastError());
-    launch_objective(obj, (unsigned)((units + 7) / 8 * 8), 0, s, (const BlockDesc*)dd, 1, (int)units, 0);
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce_out, dim3(1), dim3(pl.de_threads), pl.de_threads * sizeof(double), s,
-                       (const BlockDesc*)dd, out);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(s));
-    ctx->last_arith = pl.mode;
-    ctx->last_geo = pl.geo;
-    return PT_OK;
+                    P, (long long)block->n, need, (size_t)PT_NOALLOC_SCRATCH_BYTES,
+                    (long long)((int64_t)kThreads * e.geo.spl));
+    e.d.partials = reinterpret_cast<double*>(ctx->noalloc + kDescBytes + row_bytes);
+    // (no counters in that array: calls that raced on it would leave them wrong)
+    e.rule.tail = 0;
+    return eval_run(ctx, e, pop, out, nullptr, static_cast<hipStream_t>(hip_stream));
 }
 
 int pt_time_objective(pt_ctx* ctx, const pt_block* block, const double* pop, int P, int precision, int reps,
