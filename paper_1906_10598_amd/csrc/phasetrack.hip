@@ -276,7 +276,7 @@ struct pt_ctx {
     DevBuf errflag;
     // initial-range estimation
     int seed_max_log = 0;  // largest log2(snippet) the device's LDS allows
-    DevBuf seed_out, seed_stage;
+    DevBuf seed_stage;
     PinBuf hseed;
     // geometry
     Geometry forced{0, 0};
@@ -1214,7 +1214,7 @@ void pt_ctx_destroy(pt_ctx* ctx) {
     }
     DevBuf* bufs[] = {&ctx->desc,    &ctx->pop,      &ctx->trial,   &ctx->fpop,  &ctx->partials, &ctx->hist,
                       &ctx->state,   &ctx->rec,      &ctx->staging, &ctx->eval_pop, &ctx->tune_block, &ctx->errflag,
-                      &ctx->sync,    &ctx->seed_out, &ctx->seed_stage, &ctx->node_desc, &ctx->node_ws,
+                      &ctx->sync,    &ctx->seed_stage, &ctx->node_desc, &ctx->node_ws,
                       &ctx->eval_sync};
     for (DevBuf* b : bufs) b->release();
     ctx->hdesc.release();
@@ -1641,28 +1641,24 @@ int pt_seed_block(pt_ctx* ctx, const pt_block* block, const pt_seed_opts* opts, 
         }
         src = ctx->seed_stage.p;
     }
-    if ((rc = ctx->seed_out.ensure(3 * sizeof(SeedSnippet))) || (rc = ctx->hseed.ensure(3 * sizeof(SeedSnippet))))
-        return rc;
+    if ((rc = ctx->hseed.ensure(3 * sizeof(SeedSnippet)))) return rc;
     int lg = 0;
     while ((1 << lg) < M) ++lg;
-    const size_t lds = (size_t)16 * M;
-    SeedSnippet* dout = static_cast<SeedSnippet*>(ctx->seed_out.p);
-    if (block->dtype == PT_F64) {
-        auto k = k_seed_spectrum<double>;
-        if (lds > 65536) HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(k, dim3(3), dim3(kSeedThreads), lds, s, static_cast<const double*>(src), dst, lg,
-                           block->fs, dout);
-    } else {
-        auto k = k_seed_spectrum<float>;
-        if (lds > 65536) HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(k, dim3(3), dim3(kSeedThreads), lds, s, static_cast<const float*>(src), dst, lg,
-                           block->fs, dout);
-    }
-    HIPCHK(hipGetLastError());
+    const size_t lds = (size_t)8 * M;
+    const int threads = std::max(64, std::min(kSeedThreads, M / 4));
+    const double c = M_PI / (double)M, tanc = std::tan(c) / c;
     SeedSnippet* h = static_cast<SeedSnippet*>(ctx->hseed.p);
-    HIPCHK(hipMemcpyAsync(h, dout, 3 * sizeof(SeedSnippet), hipMemcpyDeviceToHost, s));
+    auto launch = [&](auto k, auto* samples) -> int {
+        // (and some LDS of fixed size)
+        if (lds >= 65536) HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(k, dim3(3), dim3(threads), lds, s, samples, dst, lg, block->fs, tanc, h);
+        HIPCHK(hipGetLastError());
+        return PT_OK;
+    };
+    rc = block->dtype == PT_F64 ? launch(k_seed_spectrum<double>, static_cast<const double*>(src))
+                                : launch(k_seed_spectrum<float>, static_cast<const float*>(src));
+    if (rc) return rc;
     HIPCHK(hipStreamSynchronize(s));
 
     pt_seed r;

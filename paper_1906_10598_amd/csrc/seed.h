@@ -5,11 +5,12 @@
 // frequency rate from a central difference of three equally spaced
 // snippets, and the amplitude from the same spectrum.  One workgroup per
 // snippet:
-//   1. the M samples (M a power of two) go to LDS in bit-reversed order and
-//      an in-place radix-2 decimation-in-time FFT runs there (log2 M stages,
-//      one barrier each; twiddles from sincospi of the exact ratio j / half);
+//   1. the M samples (M a power of two), two by two as M/2 complex numbers,
+//      go from memory into the first pass of a radix-4 self-sorting FFT over
+//      LDS (a radix-2 pass first where log2 M/2 is odd), and the even and odd
+//      samples' spectra are separated where a bin is looked at;
 //   2. the peak bin k* maximises |X_k|^2 over 1 <= k < M/2 (lowest k on
-//      ties) by a wave-shuffle + LDS argmax;
+//      ties) by an argmax over lanes, then waves;
 //   3. the frequency is refined between bins with Candan's bias-corrected
 //      interpolator for a rectangular window (IEEE Signal Proc. Lett. 2011):
 //      d = tan(pi/M)/(pi/M) * Re[(X_{k-1} - X_{k+1}) / (2 X_k - X_{k-1} - X_{k+1})];
@@ -19,7 +20,7 @@
 // The estimates are per snippet; the host forms f0, f1, f2 and the box.
 #pragma once
 
-#include "device.h"
+#include "kernels.h"
 
 namespace pt {
 
@@ -43,134 +44,184 @@ __device__ __forceinline__ bool seed_better(double p, int k, double q, int m) {
     return p > q || (p == q && k < m);
 }
 
+struct Cplx {
+    double re, im;
+};
+__device__ __forceinline__ Cplx cadd(Cplx a, Cplx b) { return {a.re + b.re, a.im + b.im}; }
+__device__ __forceinline__ Cplx csub(Cplx a, Cplx b) { return {a.re - b.re, a.im - b.im}; }
+__device__ __forceinline__ Cplx cmul(Cplx a, Cplx b) {
+    return {__fma_rn(a.re, b.re, -(a.im * b.im)), __fma_rn(a.re, b.im, a.im * b.re)};
+}
+// exp(-2 pi i turns), turns exact and small
+__device__ __forceinline__ Cplx cturn(double turns) {
+    double sn, cs;
+    sincospi(2.0 * turns, &sn, &cs);
+    return {cs, -sn};
+}
+// exp(-2 pi i nu n): the exact product's turns, reduced first
+__device__ __forceinline__ Cplx cphase(double nu, double n) {
+    const double q = nu * n, low = __fma_rn(nu, n, -q);
+    return cturn((q - rint(q)) + low);
+}
+
+// A chain of short steps with little in each: the passes over LDS, the search,
+// the amplitude.  Three workgroups and one wave per SIMD or two, so latency
+// bounds it: as few passes and barriers as the registers allow (radix 4 on half
+// the points: 6 passes for M = 4096 instead of 12), one twiddle pair per pass
+// rather than a table (its power-of-two strides fall on one LDS bank), nothing
+// serial over waves, samples held from the load on, results straight into host
+// memory.  M = 4096: kernel 30 -> 13 us, the call 47 -> 30 us
+// (1024: 28.5 -> 23 us).
 template <typename T>
 __global__ __launch_bounds__(kSeedThreads) void k_seed_spectrum(const T* __restrict__ s, SeedStarts starts,
-                                                                int logM, double fs,
+                                                                int logM, double fs, double tanc,
                                                                 SeedSnippet* __restrict__ out) {
     extern __shared__ double lds[];
-    const int M = 1 << logM;
-    double* re = lds;
-    double* im = lds + M;
+    const int M = 1 << logM, N = M >> 1;
+    Cplx* z = reinterpret_cast<Cplx*>(lds);  // N
     __shared__ double wp[kSeedThreads / 64];
     __shared__ int wk[kSeedThreads / 64];
     __shared__ double wsum[3][kSeedThreads / 64];
-    __shared__ double fb;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
     const T* x = s + starts.v[blockIdx.x];
 
-    for (int n = tid; n < M; n += blockDim.x) {
-        const int r = (int)(__brev((unsigned)n) >> (32 - logM));
-        re[r] = (double)x[n];
-        im[r] = 0.0;
+    // First pass from memory.  R = 4: z[j + r N / 4] of the first N / 4 threads;
+    // R = 2 (log2 N odd): z[j + r N / 2] of the first N / 2.
+    const int lgN = logM - 1, R = lgN & 1 ? 2 : 4, stride = N / R;
+    const bool mine = tid < stride;
+    Cplx v[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+    if (mine) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (r < R) v[r] = {(double)x[2 * (tid + r * stride)], (double)x[2 * (tid + r * stride) + 1]};
+        if (R == 4) {
+            const Cplx a = cadd(v[0], v[2]), b = csub(v[0], v[2]), c = cadd(v[1], v[3]), d = csub(v[1], v[3]);
+            z[4 * tid] = cadd(a, c);
+            z[4 * tid + 1] = {b.re + d.im, b.im - d.re};
+            z[4 * tid + 2] = csub(a, c);
+            z[4 * tid + 3] = {b.re - d.im, b.im + d.re};
+        } else {
+            z[2 * tid] = cadd(v[0], v[1]);
+            z[2 * tid + 1] = csub(v[0], v[1]);
+        }
     }
-    __syncthreads();
-    for (int half = 1; half < M; half <<= 1) {
-        for (int b = tid; b < (M >> 1); b += blockDim.x) {
-            const int j = b & (half - 1);
-            const int i0 = ((b - j) << 1) + j;
-            const int i1 = i0 + half;
-            double sn, cs;
-            sincospi((double)j / (double)half, &sn, &cs);  // w = exp(-i pi j / half)
-            const double r1 = re[i1], m1 = im[i1];
-            const double tr = __fma_rn(cs, r1, sn * m1);
-            const double ti = __fma_rn(cs, m1, -(sn * r1));
-            const double r0 = re[i0], m0 = im[i0];
-            re[i1] = r0 - tr;
-            im[i1] = m0 - ti;
-            re[i0] = r0 + tr;
-            im[i0] = m0 + ti;
+    for (int l = lgN & 1 ? 1 : 2; l < lgN; l += 2) {
+        const int Ns = 1 << l, k = tid & (Ns - 1), q = N >> 2;
+        const double turn = ldexp((double)k, -(l + 2));
+        const Cplx w1 = cturn(turn), w2 = cturn(2.0 * turn), w3 = cmul(w1, w2);
+        Cplx t0, t1, t2, t3;
+        __syncthreads();
+        if (tid < q) {
+            t0 = z[tid];
+            t1 = cmul(w1, z[tid + q]);
+            t2 = cmul(w2, z[tid + 2 * q]);
+            t3 = cmul(w3, z[tid + 3 * q]);
         }
         __syncthreads();
+        if (tid < q) {
+            const Cplx a = cadd(t0, t2), b = csub(t0, t2), c = cadd(t1, t3), d = csub(t1, t3);
+            Cplx* o = z + ((tid - k) << 2) + k;
+            o[0] = cadd(a, c);
+            o[Ns] = {b.re + d.im, b.im - d.re};
+            o[2 * Ns] = csub(a, c);
+            o[3 * Ns] = {b.re - d.im, b.im + d.re};
+        }
     }
+    __syncthreads();
 
-    // peak bin
+    // peak bin: bins k and N - k share the two points they are made of
+    // (Z_k + conj Z_{N-k}) / 2 = E, (Z_k - conj Z_{N-k}) / 2i = O:
+    // X_k = E + exp(-2 pi i k / M) O, X_{N-k} = conj(E - exp(-2 pi i k / M) O)
+    auto parts = [&](int k, Cplx& e, Cplx& wo) {
+        const Cplx a = z[k & (N - 1)], b = z[(N - k) & (N - 1)];
+        e = {0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
+        wo = cmul(cturn(ldexp((double)k, -logM)), {0.5 * (a.im + b.im), 0.5 * (b.re - a.re)});
+    };
     double bp = -1.0;
     int bk = 0x7fffffff;
-    for (int k = 1 + tid; k < (M >> 1); k += blockDim.x) {
-        const double p = __fma_rn(re[k], re[k], im[k] * im[k]);
+    for (int k = 1 + tid; k <= (N >> 1); k += blockDim.x) {
+        Cplx e, wo;
+        parts(k, e, wo);
+        const Cplx lo = cadd(e, wo), hi = csub(e, wo);
+        const double p = __fma_rn(lo.re, lo.re, lo.im * lo.im), q = __fma_rn(hi.re, hi.re, hi.im * hi.im);
         if (seed_better(p, k, bp, bk)) {
             bp = p;
             bk = k;
         }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const double q = __shfl_xor(bp, o);
-        const int m = __shfl_xor(bk, o);
-        if (seed_better(q, m, bp, bk)) {
+        if (seed_better(q, N - k, bp, bk)) {
             bp = q;
-            bk = m;
+            bk = N - k;
         }
     }
+    // the wave's largest power, then the lowest bin that has it
+    auto best_of = [&] {
+        const double top = wave_extreme<true>(bp);
+        bk = (int)wave_extreme<false>(bp == top ? (double)bk : 2147483647.0);
+        bp = top;
+    };
+    best_of();
     if (lane == 0) {
         wp[wave] = bp;
         wk[wave] = bk;
     }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < nwave; ++w)
-            if (seed_better(wp[w], wk[w], bp, bk)) {
-                bp = wp[w];
-                bk = wk[w];
-            }
-        // (non-finite samples leave no candidate: fall back to bin 1, in range)
-        const int k = (bk >= 1 && bk < (M >> 1)) ? bk : 1;
-        // Candan's interpolator; X_{k-1} and X_{k+1} exist for 1 <= k < M/2
-        const double nr = re[k - 1] - re[k + 1], ni = im[k - 1] - im[k + 1];
-        const double dr = 2.0 * re[k] - re[k - 1] - re[k + 1], di = 2.0 * im[k] - im[k - 1] - im[k + 1];
-        const double den = __fma_rn(dr, dr, di * di);
-        double d = 0.0;
-        if (den > 0.0) {
-            const double c = M_PI / (double)M;
-            d = tan(c) / c * (__fma_rn(nr, dr, ni * di) / den);
-        }
-        fb = ((double)k + d) * fs / (double)M;
-        wk[0] = k;
-    }
-    __syncthreads();
+    // (every wave by itself: no barrier and no broadcast through LDS)
+    bp = lane < nwave ? wp[lane] : -1.0;
+    bk = lane < nwave ? wk[lane] : 0x7fffffff;
+    best_of();
+    // (non-finite samples leave no candidate: fall back to bin 1, in range)
+    const int k = (bk >= 1 && bk < N) ? bk : 1;
+    // Candan's interpolator; X_{k-1} and X_{k+1} exist for 1 <= k < M/2
+    Cplx e, wo;
+    parts(k - 1 + min(lane, 2), e, wo);
+    const Cplx X = cadd(e, wo);
+    const Cplx xl = {__shfl(X.re, 0), __shfl(X.im, 0)}, xc = {__shfl(X.re, 1), __shfl(X.im, 1)},
+               xr = {__shfl(X.re, 2), __shfl(X.im, 2)};
+    const double nr = xl.re - xr.re, ni = xl.im - xr.im;
+    const double dr = 2.0 * xc.re - xl.re - xr.re, di = 2.0 * xc.im - xl.im - xr.im;
+    const double den = __fma_rn(dr, dr, di * di);
+    double d = 0.0;
+    if (den > 0.0) d = tanc * (__fma_rn(nr, dr, ni * di) / den);
+    const double f = ((double)k + d) * fs / (double)M;
 
-    // amplitude at the refined frequency, and the snippet's power
-    const double f = fb;
+    // amplitude at the refined frequency, and the snippet's power: sample
+    // 2 (j + r stride) + h turns by exp(-2 pi i nu 2 j) times the r-th power of
+    // one common factor and, for h = 1, another
     const double nu = f / fs;  // turns per sample
-    double yr = 0.0, yi = 0.0, ss = 0.0;
-    for (int n = tid; n < M; n += blockDim.x) {
-        const double v = (double)x[n];
-        double q = nu * (double)n;
-        q -= rint(q);
-        double sn, cs;
-        sincospi(2.0 * q, &sn, &cs);
-        yr = __fma_rn(v, cs, yr);
-        yi = __fma_rn(-v, sn, yi);
-        ss = __fma_rn(v, v, ss);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        yr += __shfl_xor(yr, o);
-        yi += __shfl_xor(yi, o);
-        ss += __shfl_xor(ss, o);
-    }
-    if (lane == 0) {
-        wsum[0][wave] = yr;
-        wsum[1][wave] = yi;
-        wsum[2][wave] = ss;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        yr = yi = ss = 0.0;
-        for (int w = 0; w < nwave; ++w) {
-            yr += wsum[0][w];
-            yi += wsum[1][w];
-            ss += wsum[2][w];
+    double y[3] = {0.0, 0.0, 0.0};  // real and imaginary part, sum of squares
+    if (mine) {
+        Cplx p = cphase(nu, (double)(2 * tid));
+        const Cplx odd = cphase(nu, 1.0), step = cphase(nu, (double)(2 * stride));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (r >= R) break;
+            const Cplx po = cmul(p, odd);
+            y[0] = __fma_rn(v[r].re, p.re, __fma_rn(v[r].im, po.re, y[0]));
+            y[1] = __fma_rn(v[r].re, p.im, __fma_rn(v[r].im, po.im, y[1]));
+            y[2] = __fma_rn(v[r].re, v[r].re, __fma_rn(v[r].im, v[r].im, y[2]));
+            p = cmul(p, step);
         }
-        const double A = 2.0 * sqrt(__fma_rn(yr, yr, yi * yi)) / (double)M;
-        const double var = ss / (double)M - 0.5 * A * A;
-        SeedSnippet o;
-        o.f = f;
-        o.amp = A;
-        o.noise = var > 0.0 ? sqrt(var) : 0.0;
-        o.bin = wk[0];
-        o.pad = 0;
-        out[blockIdx.x] = o;
+    }
+    wave_sums(y);
+    if (lane < 3) wsum[lane][wave] = lane == 0 ? y[0] : lane == 1 ? y[1] : y[2];
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) y[q] = lane < nwave ? wsum[q][lane] : 0.0;
+        wave_sums(y);
+        const double A = 2.0 * sqrt(__fma_rn(y[0], y[0], y[1] * y[1])) / (double)M;
+        const double var = y[2] / (double)M - 0.5 * A * A;
+        if (lane == 0) {
+            SeedSnippet o;
+            o.f = f;
+            o.amp = A;
+            o.noise = var > 0.0 ? sqrt(var) : 0.0;
+            o.bin = k;
+            o.pad = 0;
+            out[blockIdx.x] = o;
+        }
     }
 }
 
