@@ -393,9 +393,9 @@ typedef struct {
                                    holds n * sizeof(sample) + (max_gens + 1) * 8 + 2 * (P * 136 +
                                    P * ntiles * 8 + 48), ntiles = ceil(n / (256 * spl)): samples,
                                    history and two slots of rows, objectives, partials and state;
-                                   node weights and draws (18 KB + 8 P per generation of a step,
-                                   at most 500) and the working space of one step's new blocks
-                                   are not counted */
+                                   node weights and draws (30 KB + 16 P, P rounded up to 8 or above
+                                   120 to 16, per generation of a step, at most 512, and 30 more)
+                                   and the working space of one step's new blocks are not counted */
     pt_de_settings de;          /* settings of every block (pop <= 256) */
     int32_t seed_first;         /* 1: seed each track's first box from its samples */
     int32_t seed_snippet;       /* pt_seed_opts.snippet (0 = default) */

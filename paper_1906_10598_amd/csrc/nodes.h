@@ -26,11 +26,12 @@
 // Three kernels:
 //   k_node_project  samples -> 16 points per tile of samples (the same
 //                   interpolation inside a tile, whose phase span needs only
-//                   16 nodes); also the random draws of the first chunk
-//   k_node_moments  points -> Chebyshev moments of the block, partial sums
-//   k_node_fit      moments -> Z, W (first chunk), then whole generations of
+//                   16 nodes)
+//   k_node_moments  points -> Chebyshev moments of the block, partial sums; also
+//                   the random draws of the first launch of generations
+//   k_node_fit      moments -> Z, W (first launch), then whole generations of
 //                   Differential Evolution, one workgroup per block; also the
-//                   random draws of the next chunk
+//                   random draws of the next launch, if there is one
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -80,7 +81,7 @@ struct NodeDesc {
     double* mom;       // nmom x K x 4 partial moments
     double* wts;       // K x 4 weights, then S2
     double* nar;       // the re-expanded set between launches
-    uint64_t* draws;   // two halves of chunk x P packed draws
+    uint64_t* draws;   // two halves of packed draws, node_draw_words each
 };
 
 struct NodePlan {
@@ -94,16 +95,25 @@ constexpr size_t kNodeNarDoubles = kNodeLevelHead + 5 * (kNodeMaxK / 8 * 5);
 // the block (length, rate, reference, box) and the population size only.
 bool node_plan(const pt_block& b, double ref, int P, NodePlan* out);
 
-// Largest number of generations one k_node_fit launch runs for population P
-// and nodes up to maxK, and its dynamic LDS bytes.
-int node_chunk(int P, int maxK, int lds_max);
-size_t node_fit_lds(int P, int maxK, int chunk);
+// Dynamic LDS bytes of k_node_fit for population P and nodes up to maxK, and
+// whether the device has them.
+size_t node_fit_lds(int P, int maxK);
+bool node_fits(int P, int maxK, int lds_max);
+
+// Members per octet of lanes (the fewest that leave a wave for the bookkeeping)
+// and waves of members of a population's workgroup; 8-byte words that the packed
+// draws of some generations take (from any generation on, in blocks of 16).
+__host__ __device__ inline int node_nm(int P) { return P <= 120 ? 1 : 2; }
+__host__ __device__ inline int node_waves(int P) { return (P + 8 * node_nm(P) - 1) / (8 * node_nm(P)); }
+__host__ __device__ inline size_t node_draw_words(int P, int gens) {
+    return (size_t)((gens + 30) / 16) * 128 * node_nm(P) * node_waves(P);
+}
 
 // Launches (nd / bd: device tables of nblk blocks; chunk: generations per
 // half of `draws`).  `off`: generations run since the tables were uploaded.
-hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_proj, int P, int ngen, int chunk,
+hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_proj, hipStream_t s);
+hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, int P, int ngen, int chunk,
                         hipStream_t s);
-hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, hipStream_t s);
 hipError_t node_fit(const NodeDesc* nd, const BlockDesc* bd, int nblk, int P, int maxK, int off, int ngen, int next_ngen,
                     int chunk, int flip, bool cor, hipStream_t s);
 hipError_t node_setup(int lds_max);  // once per device

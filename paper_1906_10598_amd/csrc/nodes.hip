@@ -104,19 +104,23 @@ __device__ __forceinline__ uint64_t node_pack(const BlockDesc* d, const Draws& w
            ((uint64_t)((uint32_t)(w.r3 * kRow) | (m << 16)) << 32);
 }
 
-// The draws of generations g .. g + ngen - 1 of every member, by workgroups
-// of 256 threads beside the kernel's own work: they depend on nothing but the
+// The draws of generations g_off .. g_off + ngen - 1 of every member, by
+// workgroups beside the kernel's own work: they depend on nothing but the
 // stream, so they are kept off the fit's chain of generations (three Philox
-// calls cost as much as a whole evaluation there).
+// calls cost as much as a whole evaluation there).  Order: per 16 generations
+// (from a multiple of 16 on), per wave and member of its octets, generation,
+// octet -- 1 KB that a wave of the fit reads with one load.
 __device__ __forceinline__ void node_draws(const NodeDesc* nd, const BlockDesc* bd, int slice, int slices, int P, int g_off,
                                            int ngen, int chunk, int flip) {
     const int b = slice / slices, id = (slice - b * slices) * (int)blockDim.x + (int)threadIdx.x;
-    if (id >= P * ngen) return;
+    const int nm = node_nm(P), W = node_waves(P), part = id >> 7;
     const NodeDesc* n = nd + b;
     const BlockDesc* d = bd + b;
-    const int gl = id / P, i = id - gl * P;
-    const Draws w = trial_draws(d, i, (uint32_t)(n->g0 + g_off + gl));
-    n->draws[(size_t)((n->parity + flip) & 1) * chunk * P + id] = node_pack(d, w);
+    const int g0 = n->g0 + g_off, g = (g0 & ~15) + 16 * (part / (nm * W)) + ((id >> 3) & 15), wt = part % (nm * W);
+    if (g < g0 || g >= g0 + ngen) return;
+    const int i = min(8 * (wt / nm) + (id & 7) + 8 * W * (wt % nm), P - 1);
+    const Draws w = trial_draws(d, i, (uint32_t)g);
+    n->draws[((n->parity + flip) & 1) * node_draw_words(P, chunk) + id] = node_pack(d, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -231,13 +235,9 @@ __device__ __forceinline__ void project_unit(const NodeDesc* nd, const BlockDesc
 }
 
 __global__ __launch_bounds__(256) void k_node_project(const NodeDesc* __restrict__ nds, const BlockDesc* __restrict__ bds,
-                                                      int nblk, int total, int P, int ngen, int chunk, int slices) {
+                                                      int nblk) {
     __shared__ double tab[64], red[260];
     const int wg = blockIdx.x;
-    if (wg >= total) {
-        node_draws(nds, bds, wg - total, slices, P, 0, ngen, chunk, 0);
-        return;
-    }
     const int b = node_block_of(nds, nblk, wg, false);
     const NodeDesc* nd = nds + b;
     const BlockDesc* d = bds + b;
@@ -249,11 +249,18 @@ __global__ __launch_bounds__(256) void k_node_project(const NodeDesc* __restrict
 
 // ---------------------------------------------------------------------------
 // Moments: sum over 128 points of value x T_j(x_point) for j < K; a lane holds
-// one j, the waves share the points.
+// one j, the waves share the points.  Workgroups past `total` make the draws of
+// the fit's first launch (here rather than beside the projection, whose registers
+// allow two waves on a SIMD: 64 blocks' draws of 1500 generations, 3.8e6 of them,
+// 58 us there, 41 here).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict__ nds, const BlockDesc* __restrict__ bds,
-                                                      int nblk) {
+                                                      int nblk, int total, int P, int ngen, int chunk, int slices) {
     __shared__ double th[kNodeGroup], v[kNodeGroup][4], red[4][64][4];
+    if ((int)blockIdx.x >= total) {
+        node_draws(nds, bds, blockIdx.x - total, slices, P, 0, ngen, chunk, 0);
+        return;
+    }
     const int b = node_block_of(nds, nblk, blockIdx.x, true);
     const NodeDesc* nd = nds + b;
     const BlockDesc* d = bds + b;
@@ -316,7 +323,11 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
 // each.  So the fewest instructions a wave needs and the fewest waves a SIMD
 // holds pull against each other; measured for P = 40: 16 lanes a member (ten
 // waves) 0.99 us a generation, 8 lanes (five) 0.45, 4 lanes (three) 0.54; 8 lanes
-// with the bound rule and the stop flag off the chain where they can be 0.41.
+// with the bound rule and the stop flag off the chain where they can be 0.41, with what
+// waits for a multiple of 8 out of the loop 0.365 (P = 64 0.38, 120 0.58, 240
+// 1.17).  The draws pass through LDS 16 generations at a time, so a launch runs
+// as many generations as there are; while all of a launch's lay there, a fit of
+// 2000 generations took five launches, each ~14 us for its start.
 //
 // As the population draws together fewer nodes do: every 16th generation the
 // bookkeeping wave measures its spread, and when markedly fewer nodes would
@@ -338,14 +349,15 @@ struct FitLds {
     double *lz, *lu;   // re-expanded set
     double *scr;       // 4 doubles a node
     double *ring;      // best-so-far values
-    uint64_t* dr;      // draws of the launch's generations
+    uint64_t* dr;      // draws: 32 generations per wave and member of its octets
 };
 
 // largest re-expanded set, for a full set of K nodes
 __host__ __device__ inline int level_cap(int K) { return K <= 2 * kNodePts ? kNodePts : K / 8 * 5; }
 
 __host__ __device__ inline size_t fit_lds_doubles(int P, int maxK) {
-    return (size_t)2 * P * kRowD + 9 * (size_t)maxK + 5 * (size_t)level_cap(maxK) + kNodeRing;
+    return (size_t)2 * P * kRowD + 9 * (size_t)maxK + 5 * (size_t)level_cap(maxK) + kNodeRing +
+           (size_t)256 * node_nm(P) * node_waves(P);
 }
 
 __device__ __forceinline__ FitLds fit_lds(double* base, int P, int maxK) {
@@ -666,7 +678,7 @@ struct Book {
             sh.stop[g & 1] = flags;
         }
         flags = __builtin_amdgcn_readfirstlane(flags);
-        const bool look = (g & 15) == 15 && kind < 2 && pend < 0;
+        const bool look = (g & 15) == 14 && kind < 2 && pend < 0;  // takes effect at a multiple of 16
         if (__builtin_expect(flags || last || look, 0)) {
             const int best = best_of(g, bf);
             if (lane == 0) {
@@ -715,9 +727,12 @@ struct Members {
     double N, S2, F, lo, hi, mid_w, sc, en_w;
     int m[NM];         // members (an octet past the population repeats its last member)
     double xi[NM], fo[NM];
+    const uint64_t* src;  // the wave's draws: next block of 16 generations, this lane's 16 bytes
+    uint64_t pre[NM][2];  // on their way
+    uint64_t* ring;       // and their places in LDS
 
     __device__ __forceinline__ Members(const NodeDesc* nd_, const BlockDesc* d, int g0_, int g1_, bool fresh,
-                                       const FitLds& l_, FitShared& sh_)
+                                       const uint64_t* draws, const FitLds& l_, FitShared& sh_)
         : nd(nd_), l(l_), sh(sh_), g0(g0_), g1(g1_) {
         const int tid = threadIdx.x;
         P = d->P;
@@ -740,17 +755,58 @@ struct Members {
         const double* x = l.xs + ((g0 + 1) & 1) * P * kRowD;
 #pragma unroll
         for (int t = 0; t < NM; ++t) {
-            m[t] = min((tid >> 3) + t * 8 * ((int)(blockDim.x >> 6) - 1), P - 1);
+            m[t] = min((tid >> 3) + t * 8 * waves(), P - 1);
             xi[t] = slot ? x[m[t] * kRowD + l8] : 0.0;
             fo[t] = fresh ? __builtin_inf() : x[m[t] * kRowD + kSlots];
         }
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        src = draws + wave * NM * 128 + 2 * lane;
+        ring = l.dr + wave * NM * 256;
+        fetch();
+        put(g0 >> 4);
+        if (g0 & 15) {
+            if ((g0 | 15) + 1 < g1) fetch();
+            if (g0 & 8) put((g0 >> 4) + 1);
+        }
     }
-    __device__ __forceinline__ uint64_t draw(int t, int g) const { return l.dr[(g - g0) * P + m[t]]; }
+    __device__ __forceinline__ static int waves() { return (int)(blockDim.x >> 6) - 1; }
+    // The draws come 16 generations at a time, a block ahead: loaded when one
+    // begins, put into LDS when half of it is over (by the wave that reads them).
+    __device__ __forceinline__ void fetch() {
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {
+            typedef uint64_t pair_t __attribute__((ext_vector_type(2)));
+            const pair_t v = *(const PT_GLOBAL pair_t*)(src + t * 128);
+            pre[t][0] = v.x;
+            pre[t][1] = v.y;
+        }
+        src += waves() * NM * 128;
+    }
+    __device__ __forceinline__ void put(int block) {
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {
+            uint64_t* o = ring + t * 256 + (block & 1) * 128 + 2 * (threadIdx.x & 63);
+            o[0] = pre[t][0];
+            o[1] = pre[t][1];
+        }
+    }
+    // at multiples of 8
+    __device__ __forceinline__ void feed(int g) {
+        if (g & 8)
+            put((g >> 4) + 1);
+        else if (g + 16 < g1)
+            fetch();
+    }
+    __device__ __forceinline__ uint64_t draw(int t, int g) const {
+        return ring[t * 256 + (g & 31) * 8 + ((threadIdx.x >> 3) & 7)];
+    }
 
-    // mutant coordinate v of draws w and its base x1 (generation g): apply_trial's
-    // arithmetic
-    __device__ __forceinline__ void mutant(int g, uint64_t w, double& v, double& x1) const {
-        const char* x = reinterpret_cast<const char*>(l.xs + ((g + 1) & 1) * P * kRowD + l8);
+    // this lane's column of the rows that generation g reads
+    __device__ __forceinline__ const char* column(int g) const {
+        return reinterpret_cast<const char*>(l.xs + ((g + 1) & 1) * P * kRowD + l8);
+    }
+    // mutant coordinate v of draws w and its base x1: apply_trial's arithmetic
+    __device__ __forceinline__ void mutant(const char* x, uint64_t w, double& v, double& x1) const {
         const uint32_t a = (uint32_t)w, b = (uint32_t)(w >> 32);
         x1 = *reinterpret_cast<const double*>(x + (a & 0xFFFFu));
         const double x2 = *reinterpret_cast<const double*>(x + (a >> 16));
@@ -770,12 +826,16 @@ struct Members {
         return node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en_w, N);
     }
     template <bool FIRST = false>
-    __device__ __forceinline__ void keep(int t, int g, double y, double ft) {
+    __device__ __forceinline__ void keep(int t, int g, char* x, double y, double ft) {
         const bool take = (FIRST && g == 0) || ft <= fo[t];  // (generation 0 is accepted as it is)
         xi[t] = take ? y : xi[t];
         fo[t] = take ? ft : fo[t];
         // (octets that repeat the last member write the same values)
-        l.xs[(g & 1) * P * kRowD + m[t] * kRowD + l8] = slot ? xi[t] : fo[t];
+        *reinterpret_cast<double*>(x) = slot ? xi[t] : fo[t];
+    }
+    // member t's place in the rows that generation g writes
+    __device__ __forceinline__ char* place(int t, int g) const {
+        return reinterpret_cast<char*>(l.xs + (g & 1) * P * kRowD + m[t] * kRowD + l8);
     }
     // in generation g: whether generation g - 2 stopped the fit
     __device__ __forceinline__ int stop_flag(int g) const { return g > g0 + 1 ? sh.stop[g & 1] : 0; }
@@ -801,10 +861,13 @@ struct Members {
         };
         level();
         for (; g < g1; ++g) {
-            if (sh.next.pend == g) {
-                relevel(nd, l, sh);
-                if (sh.lev.kind) return false;
-                level();
+            if (!(g & 7)) {
+                if (!(g & 15) && sh.next.pend == g) {
+                    relevel(nd, l, sh);
+                    if (sh.lev.kind) return false;
+                    level();
+                }
+                feed(g);
             }
             if (stop_flag(g)) return true;
 #pragma unroll
@@ -813,7 +876,7 @@ struct Members {
                 if (g > 0) {
                     const uint64_t w = draw(t, g);
                     double v, x1;
-                    mutant(g, w, v, x1);
+                    mutant(column(g), w, v, x1);
                     y = crossed(w) ? bounded(v, x1) : xi[t];
                 }
                 double ft;
@@ -825,7 +888,7 @@ struct Members {
                 } else {
                     ft = full(y);
                 }
-                keep<true>(t, g, y, ft);
+                keep<true>(t, g, place(t, g), y, ft);
             }
             lds_barrier();
         }
@@ -877,46 +940,62 @@ struct Members {
             }
             return node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
         };
-        int side = 0;
         uint64_t w[NM];
 #pragma unroll
         for (int t = 0; t < NM; ++t) w[t] = draw(t, g);
-        for (; g < g1; ++g) {
-            if (KIND == 1 && sh.next.pend == g) {
-                relevel(nd, l, sh);
-                return false;
-            }
-            const int stop = STOPS ? stop_flag(g) : 0;
-#pragma unroll
-            for (int t = 0; t < NM; ++t) {
-                double v, x1;
-                mutant(g, w[t], v, x1);
-                double y = crossed(w[t]) ? (BOUNDS ? bounded(v, x1) : v) : xi[t];
-                const unsigned long long inside = __ballot(y >= nlo) & __ballot(y <= nhi);
-                double ft = value(y);
-                // (the limits are tested last, off the chain of dependent operations:
-                // outside them the value above is dropped)
-                asm volatile("" : "+v"(ft));
-                if (__builtin_expect(inside != ~0ull, 0)) {
-                    if constexpr (BOUNDS) {
-                        ft = full(y);
-                    } else {
-                        y = crossed(w[t]) ? bounded(v, x1) : xi[t];
-                        ft = __ballot(y >= nlo && y <= nhi) == ~0ull ? value(y) : full(y);
-                        side += 4;
-                    }
-                }
-                w[t] = draw(t, min(g + 1, g1 - 1));
-                if (STOPS && t == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(stop), 0)) return true;
-                keep(t, g, y, ft);
-            }
-            lds_barrier();
-            if constexpr (!BOUNDS) {
-                if (side > 0 && --side > 16) {
-                    often = true;
-                    ++g;
+        // In stretches to the next multiple of 8: what can wait is done between
+        // them (draws, a pending set, the count of side paths), and the two copies'
+        // places are held and swapped instead of worked out (P = 40: 115
+        // instructions and 0.44 us a generation with these inside, 91 and 0.365
+        // without).
+        while (g < g1) {
+            if (!(g & 7)) {
+                if (KIND == 1 && !(g & 15) && sh.next.pend == g) {
+                    relevel(nd, l, sh);
                     return false;
                 }
+                feed(g);
+            }
+            const char* xr = column(g);
+            char* xw[NM];
+#pragma unroll
+            for (int t = 0; t < NM; ++t) xw[t] = place(t, g);
+            int swap = (g & 1 ? 1 : -1) * P * kRowD * (int)sizeof(double);  // from the copy read to the one written
+            int side = 0;
+            const int end = min((g | 7) + 1, g1);
+            do {
+                const int stop = STOPS ? stop_flag(g) : 0;
+#pragma unroll
+                for (int t = 0; t < NM; ++t) {
+                    double v, x1;
+                    mutant(xr, w[t], v, x1);
+                    double y = crossed(w[t]) ? (BOUNDS ? bounded(v, x1) : v) : xi[t];
+                    const unsigned long long inside = __ballot(y >= nlo) & __ballot(y <= nhi);
+                    double ft = value(y);
+                    // (the limits are tested last, off the chain of dependent operations:
+                    // outside them the value above is dropped)
+                    asm volatile("" : "+v"(ft));
+                    if (__builtin_expect(inside != ~0ull, 0)) {
+                        if constexpr (BOUNDS) {
+                            ft = full(y);
+                        } else {
+                            y = crossed(w[t]) ? bounded(v, x1) : xi[t];
+                            ft = __ballot(y >= nlo && y <= nhi) == ~0ull ? value(y) : full(y);
+                            ++side;
+                        }
+                    }
+                    w[t] = draw(t, g + 1);  // (not a draw after the last generation, and not used)
+                    if (STOPS && t == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(stop), 0)) return true;
+                    keep(t, g, xw[t], y, ft);
+                    xw[t] -= swap;
+                }
+                xr += swap;
+                swap = -swap;
+                lds_barrier();
+            } while (++g < end);
+            if (!BOUNDS && side > 2 * NM) {
+                often = true;
+                return false;
             }
         }
         return false;
@@ -944,8 +1023,8 @@ struct Members {
 };
 
 template <int NM, bool COR>
-__device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, int g0, int ngen, bool fresh, const FitLds& l,
-                                        FitShared& sh) {
+__device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, int g0, int ngen, bool fresh,
+                                        const uint64_t* draws, const FitLds& l, FitShared& sh) {
     const int tid = threadIdx.x, NT = blockDim.x, W = (NT >> 6) - 1, P = d->P, g1 = g0 + ngen;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int g;
@@ -956,11 +1035,11 @@ __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, 
         else
             g = window ? Book<4, true>(nd, d, l, sh).run(g0, g1) : Book<4, false>(nd, d, l, sh).run(g0, g1);
     } else if (nd->slope) {
-        g = d->quartic ? Members<NM, true, true, COR>(nd, d, g0, g1, fresh, l, sh).run()
-                       : Members<NM, true, false, COR>(nd, d, g0, g1, fresh, l, sh).run();
+        g = d->quartic ? Members<NM, true, true, COR>(nd, d, g0, g1, fresh, draws, l, sh).run()
+                       : Members<NM, true, false, COR>(nd, d, g0, g1, fresh, draws, l, sh).run();
     } else {
-        g = d->quartic ? Members<NM, false, true, COR>(nd, d, g0, g1, fresh, l, sh).run()
-                       : Members<NM, false, false, COR>(nd, d, g0, g1, fresh, l, sh).run();
+        g = d->quartic ? Members<NM, false, true, COR>(nd, d, g0, g1, fresh, draws, l, sh).run()
+                       : Members<NM, false, false, COR>(nd, d, g0, g1, fresh, draws, l, sh).run();
     }
     __syncthreads();
     // a stop of the last generation but one, or of the last; otherwise the last is kept
@@ -1016,8 +1095,7 @@ __global__ __launch_bounds__(MAXT) void k_node_fit(const NodeDesc* __restrict__ 
     const FitLds l = fit_lds(lds, P, maxK);
     const int K = nd->K;
 
-    const uint64_t* dr = nd->draws + (size_t)((nd->parity + flip) & 1) * chunk * P;
-    for (int e = tid; e < ngen * P; e += NT) l.dr[e] = gld(dr + e);
+    const uint64_t* draws = nd->draws + ((nd->parity + flip) & 1) * node_draw_words(P, chunk);
     for (int k = tid; k < K; k += NT) l.un[k] = cos_ratio(2 * k + 1, 4 * K, 0.25 / (double)K) + nd->c;
     if (fresh) {
         init_block(d);
@@ -1084,20 +1162,15 @@ __global__ __launch_bounds__(MAXT) void k_node_fit(const NodeDesc* __restrict__ 
         }
         return;
     }
-    fit_run<NM, COR>(nd, d, g0, ngen, fresh, l, sh);
+    fit_run<NM, COR>(nd, d, g0, ngen, fresh, draws, l, sh);
 }
 
 using FitKernel = void (*)(const NodeDesc*, const BlockDesc*, int, int, int, int, int, int, int, int, int);
 
-// members per octet: the fewest that leave a wave for the bookkeeping
-int members_per_octet(int P) { return P <= 120 ? 1 : 2; }
-int fit_waves(int P) {
-    const int nm = members_per_octet(P);
-    return (P + 8 * nm - 1) / (8 * nm) + 1;
-}
+int fit_waves(int P) { return node_waves(P) + 1; }
 template <bool COR>
 FitKernel pick_fit(int P) {
-    if (members_per_octet(P) == 2) return k_node_fit<2, COR, 1024>;
+    if (node_nm(P) == 2) return k_node_fit<2, COR, 1024>;
     return fit_waves(P) <= 8 ? k_node_fit<1, COR, 512> : k_node_fit<1, COR, 1024>;
 }
 FitKernel fit_kernel(int P, bool cor) { return cor ? pick_fit<true>(P) : pick_fit<false>(P); }
@@ -1185,14 +1258,9 @@ bool node_plan(const pt_block& B, double ref, int P, NodePlan* out) {
     return true;
 }
 
-size_t node_fit_lds(int P, int maxK, int chunk) {
-    return (fit_lds_doubles(P, maxK) + (size_t)chunk * P) * sizeof(double);
-}
+size_t node_fit_lds(int P, int maxK) { return fit_lds_doubles(P, maxK) * sizeof(double); }
 
-int node_chunk(int P, int maxK, int lds_max) {
-    const int64_t room = (int64_t)lds_max - 1024 - (int64_t)node_fit_lds(P, maxK, 0) - 16;
-    return (int)std::max<int64_t>(0, std::min<int64_t>(500, room / (8 * P)));
-}
+bool node_fits(int P, int maxK, int lds_max) { return (int64_t)node_fit_lds(P, maxK) <= (int64_t)lds_max - 1024; }
 
 hipError_t node_setup(int lds_max) {
     for (int P : {4, 100, kNodeMaxP})
@@ -1204,26 +1272,26 @@ hipError_t node_setup(int lds_max) {
     return hipSuccess;
 }
 
-hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_proj, int P, int ngen, int chunk,
-                        hipStream_t s) {
-    const int slices = (P * ngen + 255) / 256;
-    hipLaunchKernelGGL(k_node_project, dim3((unsigned)(total_proj + nblk * slices)), dim3(256), 0, s, nd, bd, nblk,
-                       total_proj, P, ngen, chunk, slices);
+hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_proj, hipStream_t s) {
+    hipLaunchKernelGGL(k_node_project, dim3((unsigned)total_proj), dim3(256), 0, s, nd, bd, nblk);
     return hipGetLastError();
 }
 
-hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, hipStream_t s) {
-    hipLaunchKernelGGL(k_node_moments, dim3((unsigned)total_mom), dim3(256), 0, s, nd, bd, nblk);
+hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, int P, int ngen, int chunk,
+                        hipStream_t s) {
+    const int slices = (int)((node_draw_words(P, ngen) + 255) / 256);
+    hipLaunchKernelGGL(k_node_moments, dim3((unsigned)(total_mom + nblk * slices)), dim3(256), 0, s, nd, bd, nblk, total_mom,
+                       P, ngen, chunk, slices);
     return hipGetLastError();
 }
 
 hipError_t node_fit(const NodeDesc* nd, const BlockDesc* bd, int nblk, int P, int maxK, int off, int ngen, int next_ngen,
                     int chunk, int flip, bool cor, hipStream_t s) {
     const int nt = 64 * fit_waves(P);
-    const int slices = (P * next_ngen + nt - 1) / nt;
+    const int slices = (int)((node_draw_words(P, next_ngen) + nt - 1) / nt);
     const FitKernel k = fit_kernel(P, cor);
     hipLaunchKernelGGL(k, dim3((unsigned)(nblk + nblk * slices)), dim3((unsigned)nt),
-                       (unsigned)node_fit_lds(P, maxK, ngen), s, nd, bd, nblk, P, maxK, off, ngen, next_ngen, chunk, flip,
+                       (unsigned)node_fit_lds(P, maxK), s, nd, bd, nblk, P, maxK, off, ngen, next_ngen, chunk, flip,
                        slices > 0 ? slices : 1);
     return hipGetLastError();
 }

@@ -969,10 +969,12 @@ int run_direct(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<
     return PT_OK;
 }
 
-// Generations per stop check of a node-weight fit with the window rule (fits
-// of the benchmark stop after 200 to 350 generations), and bytes its draws may
-// take.
-constexpr int kNodeCheck = 64;
+// Generations of one launch of a node-weight fit: all of them up to 2048 (a
+// further launch is ~15 us: its start, and the weights and the population from
+// memory again); with the window rule, which stops fits after a few hundred, up
+// to 512 (the draws of those not run are made in vain, beside the fit); and
+// bytes the draws may take.
+constexpr int kNodeGens = 2048, kNodeGensWindow = 512;
 constexpr size_t kNodeDrawBytes = (size_t)256 << 20;
 
 // Fits of the blocks `idx` through node weights (plans[k] for idx[k]); rec[b]:
@@ -988,9 +990,9 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
         maxK = std::max(maxK, p.nd.K);
         work += p.pts_doubles + p.s2_doubles + p.mom_doubles;
     }
-    int chunk = ctx->timing ? 1 : std::min(node_chunk(P, maxK, ctx->lds_max), window ? kNodeCheck : iters);
-    chunk = std::min(chunk, std::max(16, (int)(kNodeDrawBytes / ((size_t)16 * P * nblk))));
-    const size_t draws = (size_t)2 * chunk * P;  // (8 bytes each)
+    int chunk = ctx->timing ? 1 : std::min(window ? kNodeGensWindow : kNodeGens, iters);
+    chunk = std::min<int64_t>(chunk, std::max<int64_t>(16, kNodeDrawBytes / (node_draw_words(P, 1) * nblk)));
+    const size_t draws = (chunk < iters ? 2 : 1) * node_draw_words(P, chunk);  // (8 bytes each)
     const size_t fixed = kNodeWtsDoubles + kNodeNarDoubles + draws;
     const size_t ndb = (sizeof(NodeDesc) * nblk + 255) & ~(size_t)255, bdb = sizeof(BlockDesc) * nblk;
     if ((rc = ensure_state(ctx, nall, de)) || (rc = ctx->node_ws.ensure((work + fixed * nblk) * sizeof(double))) ||
@@ -1024,8 +1026,8 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
     HIPCHK(hipMemcpyAsync(ctx->node_desc.p, hn, ndb + bdb, hipMemcpyHostToDevice, s));
     const NodeDesc* nd = static_cast<const NodeDesc*>(ctx->node_desc.p);
     const BlockDesc* bd = reinterpret_cast<const BlockDesc*>(static_cast<const char*>(ctx->node_desc.p) + ndb);
-    HIPCHK(node_project(nd, bd, nblk, proj, P, std::min(chunk, iters), chunk, s));
-    HIPCHK(node_moments(nd, bd, nblk, mom, s));
+    HIPCHK(node_project(nd, bd, nblk, proj, s));
+    HIPCHK(node_moments(nd, bd, nblk, mom, P, std::min(chunk, iters), chunk, s));
     DeState* hst = static_cast<DeState*>(ctx->hstate.p);
     auto stopped = [&](const DeState* h) {
         for (int b : idx)
@@ -1098,7 +1100,7 @@ int run_fit(pt_ctx* ctx, const pt_block* given, int nblk, const pt_de_settings* 
     for (int b = 0; b < nblk; ++b) {
         NodePlan p;
         if (!direct && nodes_allowed(ctx) && node_plan(blocks[b], block_ref(&blocks[b]), de->pop, &p) &&
-            node_chunk(de->pop, p.nd.K, ctx->lds_max) >= 16) {
+            node_fits(de->pop, p.nd.K, ctx->lds_max)) {
             by_nodes.push_back(b);
             plans.push_back(p);
         } else {
@@ -1954,7 +1956,6 @@ struct pt_server {
     uint64_t next_ticket = 1;
     DevBuf desc, rec;
     PinBuf hdesc, hrec, hstate;
-    int chunk = 0;  // generations per node-weight launch
     DevBuf node_desc, node_ws;
     PinBuf hnode;
     std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
@@ -2006,7 +2007,8 @@ int slot_mode(const pt_server* sv, const pt_block& b) {
 // evaluating its samples in the arithmetic of slot_mode.
 void slot_form(const pt_server* sv, pt_server::Slot& sl) {
     sl.mode = slot_mode(sv, sl.blk);
-    sl.nodes = nodes_allowed(sv->ctx) && sv->chunk >= 16 && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan);
+    sl.nodes = nodes_allowed(sv->ctx) && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan) &&
+               node_fits(sv->cfg.de.pop, sl.plan.nd.K, sv->ctx->lds_max);
 }
 
 // Warm box of a track's next block around the prediction from its last fit.
@@ -2128,11 +2130,11 @@ int server_admit(pt_server* sv, hipStream_t s) {
 
 // One step of the node-weight blocks, act[0 .. nn) (the first nn_fresh new;
 // dd: the step's descriptors on the device): K generations, in launches of up
-// to sv->chunk.
+// to kNodeGensWindow.
 int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, const BlockDesc* dd, int K,
                  hipStream_t s, int* launches) {
-    const int P = sv->cfg.de.pop, chunk = std::min(sv->chunk, K);
-    const size_t draws = (size_t)2 * chunk * P;  // (8 bytes each)
+    const int P = sv->cfg.de.pop, chunk = std::min(kNodeGensWindow, K);
+    const size_t draws = 2 * node_draw_words(P, chunk);  // (8 bytes each)
     size_t work = 0;
     int maxK = 0, proj = 0, mom = 0, rc;
     for (int q = 0; q < nn; ++q) {
@@ -2170,8 +2172,8 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
     HIPCHK(hipMemcpyAsync(sv->node_desc.p, hn, sizeof(NodeDesc) * nn, hipMemcpyHostToDevice, s));
     const NodeDesc* nd = static_cast<const NodeDesc*>(sv->node_desc.p);
     if (nn_fresh) {
-        HIPCHK(node_project(nd, dd, nn_fresh, proj, P, chunk, chunk, s));
-        HIPCHK(node_moments(nd, dd, nn_fresh, mom, s));
+        HIPCHK(node_project(nd, dd, nn_fresh, proj, s));
+        HIPCHK(node_moments(nd, dd, nn_fresh, mom, P, chunk, chunk, s));
     }
     *launches = 0;
     for (int off = 0; off < K; off += chunk, ++*launches) {
@@ -2267,7 +2269,6 @@ int pt_server_create(pt_ctx* ctx, const pt_server_config* cfg, pt_server** out) 
     if (sv->cfg.max_attempts == 0) sv->cfg.max_attempts = 1;
     sv->geo = cfg->spl ? Geometry{cfg->spl, cfg->cpg} : default_geometry(400000, cfg->de.pop);
     sv->lead = ctx->step_fusion == PT_FUSION_LEAD;
-    sv->chunk = node_chunk(cfg->de.pop, kNodeMaxK, ctx->lds_max);
     sv->slots.resize(cfg->max_slots);
     *out = sv.release();
     return PT_OK;
