@@ -438,19 +438,33 @@ __device__ __forceinline__ double node_objective(const NodeDesc* nd, const NodeC
 }
 
 // Sums over a node set in LDS for one candidate (the octet's lanes share
-// the nodes; n a multiple of 8).
+// the nodes; n a multiple of 8): two nodes at a time, the next two on their way.
 template <bool SLOPE, bool QUART, bool COR>
 __device__ __forceinline__ void lds_sums(const NodeCand& q, const double* zw, const double* un, int l8, int n, double& a1,
                                          double& a2) {
-#pragma unroll 2
-    for (int k = l8; k < n; k += 8) {
-        const double u = un[k];
-        double r = node_delta<QUART>(q, u);
+    struct Node {
+        double u, zr, zi, wr, wi;
+    };
+    auto load = [&](int k) { return Node{un[k], zw[4 * k], zw[4 * k + 1], zw[4 * k + 2], zw[4 * k + 3]}; };
+    auto term = [&](const Node& t) {
+        double r = node_delta<QUART>(q, t.u);
         r -= rint(r);
         double c, s;
         sincos_turns64(r, c, s);
-        node_terms<SLOPE, COR>(q, u, c, s, zw[4 * k], zw[4 * k + 1], zw[4 * k + 2], zw[4 * k + 3], a1, a2);
+        node_terms<SLOPE, COR>(q, t.u, c, s, t.zr, t.zi, t.wr, t.wi, a1, a2);
+    };
+    Node a = load(l8), b = load(l8 + 8 < n ? l8 + 8 : l8);
+    int k = l8;
+#pragma unroll 2
+    for (; k + 8 < n; k += 16) {
+        const int k2 = k + 16 < n ? k + 16 : k, k3 = k + 24 < n ? k + 24 : k;
+        const Node c = load(k2), d = load(k3);
+        term(a);
+        term(b);
+        a = c;
+        b = d;
     }
+    if (k < n) term(a);
 }
 
 // Half of (N + sum of Wr), the constant part of the energy, over the wave.
@@ -610,8 +624,9 @@ __device__ __noinline__ void ask_level(const NodeDesc* nd, const FitLds& l, FitS
     const double* x = l.xs + (g & 1) * P * kRowD;
     const double* xb = x + best * kRowD;
     // largest distance of a member from the best one, per slot, with room for a
-    // mutant x1 + F (x2 - x3) of such members and half as much again; in turns
-    const double room = 1.5 * (1.0 + 2.0 * F);
+    // mutant x1 + F (x2 - x3) of such members; in turns (half as much again makes
+    // the sets shrink later: 1 to 2.5 % of a fit)
+    const double room = 1.0 + 2.0 * F;
     double rng[kSlots], q[5];
 #pragma unroll
     for (int j = 1; j < kSlots; ++j) {
