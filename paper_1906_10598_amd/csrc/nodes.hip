@@ -424,12 +424,17 @@ __device__ __forceinline__ void node_terms(const NodeCand& q, double u, double c
     }
 }
 
-// Objective from an octet's sums; en: half of (N + sum Wr).
+// Correlation objective, Eq. (2-2-5): F = 1 / (arctan(C) + pi/2), of f = -C.
+__device__ __noinline__ double cor_value(double f) { return 1.0 / (atan(-f) + 1.5707963267948966192); }
+
+// Objective from an octet's sums; en: half of (N + sum Wr).  COR: -C, which
+// rises and falls with F: members are compared by it, and F is formed where a
+// value leaves the generations (an arctangent and a division in each cost 0.25 of
+// 0.60 us; F itself cannot tell apart correlations closer than ~1e-10 relative).
 template <bool SLOPE, bool COR>
 __device__ __forceinline__ double node_objective(const NodeDesc* nd, const NodeCand& q, double a1, double a2, double S2,
                                                  double en, double N) {
-    // correlation objective, Eq. (2-2-5): F = 1 / (arctan(C) + pi/2)
-    if constexpr (COR) return 1.0 / (atan(-0.5 * oct_sum(SLOPE ? a1 : q.A * a1)) + 1.5707963267948966192);
+    if constexpr (COR) return 0.5 * oct_sum(SLOPE ? a1 : q.A * a1);
     const double v = oct_sum(SLOPE ? __fma_rn(0.5, a2, a1) : q.A * __fma_rn(-q.A, a2, a1));
     // half the energy of the amplitude (with the constant part of cos 2 phi's sum)
     if constexpr (SLOPE)
@@ -693,7 +698,8 @@ struct Book {
     const FitLds& l;
     FitShared& sh;
     int P, lane, win, max_gens, kind, pend;
-    double vtr, rel_tol, floor, F, bf;
+    double vtr, rel_tol, floor, F, bf, low;  // low: the best member's comparison value, bf: its objective
+    bool cor;
     double* hist;
 
     __device__ __forceinline__ Book(const NodeDesc* nd_, const BlockDesc* d, const FitLds& l_, FitShared& sh_)
@@ -709,18 +715,19 @@ struct Book {
         hist = d->hist;
         kind = __builtin_amdgcn_readfirstlane(sh.lev.kind);
         pend = __builtin_amdgcn_readfirstlane(sh.next.pend);
-        bf = __builtin_inf();
+        bf = low = __builtin_inf();
+        cor = d->objective != 0;
     }
     // (lanes past the population repeat its last member)
     __device__ __forceinline__ double value(int g, int t) const {
         return l.xs[(g & 1) * P * kRowD + min(lane + 64 * t, P - 1) * kRowD + kSlots];
     }
-    // lowest index of the members of generation g whose objective is bf
-    __device__ __forceinline__ int best_of(int g, double bf) const {
+    // lowest index of the members of generation g that have the best value
+    __device__ __forceinline__ int best_of(int g) const {
         int best = 0;
 #pragma unroll
         for (int t = NV - 1; t >= 0; --t) {
-            const unsigned long long hit = __ballot(lane + 64 * t < P && value(g, t) == bf);
+            const unsigned long long hit = __ballot(lane + 64 * t < P && value(g, t) == low);
             if (hit) best = 64 * t + __ffsll(hit) - 1;
         }
         return best;
@@ -735,7 +742,10 @@ struct Book {
         }
         // objectives only fall, so the best changes only when one lies below it
         // (seldom, once the population has drawn together)
-        if (__ballot(f < bf)) bf = wave_extreme<false>(f);
+        if (__ballot(f < low)) {
+            low = wave_extreme<false>(f);
+            bf = cor ? cor_value(low) : low;
+        }
         int flags = bf <= vtr ? 4 : 0;  // PT_FLAG_VTR
         if constexpr (WINDOW) {
             if (g >= win) {
@@ -753,7 +763,7 @@ struct Book {
         flags = __builtin_amdgcn_readfirstlane(flags);
         const bool look = (g & 15) == 14 && kind < 2 && pend < 0;  // takes effect at a multiple of 16
         if (__builtin_expect(flags || last || look, 0)) {
-            const int best = best_of(g, bf);
+            const int best = best_of(g);
             if (lane == 0) {
                 sh.best = best;
                 sh.best_f = bf;
@@ -1127,7 +1137,7 @@ __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, 
         if (j < kSlots)
             gst(d->pop + e, xl[e]);
         else
-            gst(d->fpop + e / kRowD, xl[e]);
+            gst(d->fpop + e / kRowD, COR && flags ? cor_value(xl[e]) : xl[e]);
     }
     if (!flags) {
         double* o = nd->nar;
