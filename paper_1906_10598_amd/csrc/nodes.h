@@ -58,6 +58,9 @@ constexpr double kNodeTurns16 = 1.0 / 8, kNodeTurns8 = 1.0 / 48;
 constexpr double kNodeCancel = 1e-3;
 enum { kFlagNodeAbort = 1 << 16 };  // DeState::flags of an abandoned fit
 
+struct DeState;
+struct FitRecord;
+
 // One block of a node-weight launch, beside its BlockDesc.
 struct NodeDesc {
     // reference phase in turns, a polynomial in m = n - ref: r1 (hi + lo), r2, r3, r4
@@ -82,6 +85,10 @@ struct NodeDesc {
     double* wts;       // K x 4 weights, then S2
     double* nar;       // the re-expanded set between launches
     uint64_t* draws;   // two halves of packed draws, node_draw_words each
+    // in host memory: the state after each launch, and the record of a fit that has
+    // ended (written by the fit: a kernel and two copies of ~4 us each otherwise)
+    DeState* state;
+    FitRecord* rec;
 };
 
 struct NodePlan {

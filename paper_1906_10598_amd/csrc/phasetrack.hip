@@ -1002,6 +1002,7 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
     NodeDesc* hn = static_cast<NodeDesc*>(ctx->hnode.p);
     BlockDesc* hb = reinterpret_cast<BlockDesc*>(static_cast<char*>(ctx->hnode.p) + ndb);
     double* ws = static_cast<double*>(ctx->node_ws.p);
+    DeState* hst = static_cast<DeState*>(ctx->hstate.p);
     for (int k = 0; k < nblk; ++k) {
         hb[k] = base_desc(blocks[idx[k]], de, 0, 0);
         set_state(ctx, idx[k], de->max_gens, &hb[k]);
@@ -1021,6 +1022,9 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
         n.pts = take(plans[k].pts_doubles);
         n.s2 = take(plans[k].s2_doubles);
         n.mom = take(plans[k].mom_doubles);
+        n.state = hst + idx[k];
+        n.state->done = 0;
+        n.rec = static_cast<FitRecord*>(ctx->hrec.p) + k;
         hn[k] = n;
     }
     HIPCHK(hipMemcpyAsync(ctx->node_desc.p, hn, ndb + bdb, hipMemcpyHostToDevice, s));
@@ -1028,10 +1032,9 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
     const BlockDesc* bd = reinterpret_cast<const BlockDesc*>(static_cast<const char*>(ctx->node_desc.p) + ndb);
     HIPCHK(node_project(nd, bd, nblk, proj, s));
     HIPCHK(node_moments(nd, bd, nblk, mom, P, std::min(chunk, iters), chunk, s));
-    DeState* hst = static_cast<DeState*>(ctx->hstate.p);
-    auto stopped = [&](const DeState* h) {
+    auto stopped = [&] {
         for (int b : idx)
-            if (!h[b].done) return false;
+            if (!*const_cast<volatile int*>(&hst[b].done)) return false;
         return true;
     };
     bool all = false;
@@ -1051,19 +1054,16 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
         }
         ++ctx->last_fit_launches;
         if (window && next && !ctx->timing) {
-            // as in the graph form: the state after chunk c - 1 is checked once
-            // chunk c is queued, so the device never idles for the check
-            HIPCHK(hipMemcpyAsync(hst + (c & 1) * nall, ctx->state.p, sizeof(DeState) * nall, hipMemcpyDeviceToHost, s));
+            // as in the graph form: the state after chunk c - 1 (or c, if that has
+            // ended too) is checked once chunk c is queued, so the device never
+            // idles for the check
             HIPCHK(hipEventRecord(ctx->ev_state[c & 1], s));
             if (c >= 1) {
                 HIPCHK(hipEventSynchronize(ctx->ev_state[(c - 1) & 1]));
-                all = stopped(hst + ((c - 1) & 1) * nall);
+                all = stopped();
             }
         }
     }
-    hipLaunchKernelGGL(k_finalize, dim3(nblk), dim3(64), 0, s, bd, static_cast<FitRecord*>(ctx->rec.p));
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(ctx->hrec.p, ctx->rec.p, sizeof(FitRecord) * nblk, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (ctx->timing && (rc = collect_timing(ctx))) return rc;
     const FitRecord* r = static_cast<const FitRecord*>(ctx->hrec.p);
@@ -1956,8 +1956,7 @@ struct pt_server {
     uint64_t next_ticket = 1;
     DevBuf desc, rec;
     PinBuf hdesc, hrec, hstate;
-    DevBuf node_desc, node_ws;
-    PinBuf hnode;
+    DevBuf node_ws;
     std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
     double clock() const {
         return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -2128,11 +2127,14 @@ int server_admit(pt_server* sv, hipStream_t s) {
     return PT_OK;
 }
 
-// One step of the node-weight blocks, act[0 .. nn) (the first nn_fresh new;
-// dd: the step's descriptors on the device): K generations, in launches of up
-// to kNodeGensWindow.
-int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, const BlockDesc* dd, int K,
-                 hipStream_t s, int* launches) {
+// One step of the node-weight blocks, act[0 .. nn) (the first nn_fresh new): K
+// generations, in launches of up to kNodeGensWindow.
+struct NodeStep {
+    int nn = 0, nn_fresh = 0, chunk = 0, maxK = 0, proj = 0, mom = 0;
+};
+
+// Its descriptors (hn: host copy, one per block).
+int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, int K, NodeDesc* hn, NodeStep* step) {
     const int P = sv->cfg.de.pop, chunk = std::min(kNodeGensWindow, K);
     const size_t draws = 2 * node_draw_words(P, chunk);  // (8 bytes each)
     size_t work = 0;
@@ -2142,10 +2144,7 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
         maxK = std::max(maxK, p.nd.K);
         if (q < nn_fresh) work += p.pts_doubles + p.s2_doubles + p.mom_doubles;
     }
-    if ((rc = sv->node_desc.ensure(sizeof(NodeDesc) * nn)) || (rc = sv->hnode.ensure(sizeof(NodeDesc) * nn)) ||
-        (rc = sv->node_ws.ensure(work * sizeof(double))))
-        return rc;
-    NodeDesc* hn = static_cast<NodeDesc*>(sv->hnode.p);
+    if ((rc = sv->node_ws.ensure(work * sizeof(double)))) return rc;
     double* ws = static_cast<double*>(sv->node_ws.p);
     for (int q = 0; q < nn; ++q) {
         pt_server::Slot& sl = sv->slots[act[q]];
@@ -2167,19 +2166,27 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
         n.draws = reinterpret_cast<uint64_t*>(n.nar + kNodeNarDoubles);
         n.g0 = sl.fresh ? 0 : sl.gen;
         n.parity = sl.parity;
+        n.state = static_cast<DeState*>(sv->hstate.p) + 2 * q;
+        n.rec = static_cast<FitRecord*>(sv->hrec.p) + q;
         hn[q] = n;
     }
-    HIPCHK(hipMemcpyAsync(sv->node_desc.p, hn, sizeof(NodeDesc) * nn, hipMemcpyHostToDevice, s));
-    const NodeDesc* nd = static_cast<const NodeDesc*>(sv->node_desc.p);
-    if (nn_fresh) {
-        HIPCHK(node_project(nd, dd, nn_fresh, proj, s));
-        HIPCHK(node_moments(nd, dd, nn_fresh, mom, P, chunk, chunk, s));
+    *step = NodeStep{nn, nn_fresh, chunk, maxK, proj, mom};
+    return PT_OK;
+}
+
+// Its launches (nd, dd: the step's descriptors on the device).
+int server_nodes_run(pt_server* sv, const NodeStep& st, const NodeDesc* nd, const BlockDesc* dd, int K, hipStream_t s,
+                     int* launches) {
+    const int P = sv->cfg.de.pop, chunk = st.chunk;
+    if (st.nn_fresh) {
+        HIPCHK(node_project(nd, dd, st.nn_fresh, st.proj, s));
+        HIPCHK(node_moments(nd, dd, st.nn_fresh, st.mom, P, chunk, chunk, s));
     }
     *launches = 0;
     for (int off = 0; off < K; off += chunk, ++*launches) {
         const int ngen = std::min(chunk, K - off), left = K - off - ngen;
         // the last launch of the step makes the draws of the next step's first
-        HIPCHK(node_fit(nd, dd, nn, P, maxK, off, ngen, left ? std::min(chunk, left) : chunk, chunk, *launches & 1,
+        HIPCHK(node_fit(nd, dd, st.nn, P, st.maxK, off, ngen, left ? std::min(chunk, left) : chunk, chunk, *launches & 1,
                         sv->cfg.de.objective != PT_OBJ_CHI2, s));
     }
     return PT_OK;
@@ -2282,9 +2289,7 @@ void pt_server_destroy(pt_server* sv) {
         DevBuf* b[] = {&sl.samples, &sl.pop, &sl.trial, &sl.fpop, &sl.partials, &sl.hist, &sl.state, &sl.node};
         for (DevBuf* x : b) x->release();
     }
-    sv->node_desc.release();
     sv->node_ws.release();
-    sv->hnode.release();
     sv->desc.release();
     sv->rec.release();
     sv->hdesc.release();
@@ -2355,7 +2360,9 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
     const pt_de_settings& de = sv->cfg.de;
     const int tile = kThreads * sv->geo.spl;
     const int groups = (P + sv->geo.cpg - 1) / sv->geo.cpg;
-    if ((rc = sv->desc.ensure(sizeof(BlockDesc) * nb)) || (rc = sv->hdesc.ensure(sizeof(BlockDesc) * nb)) ||
+    // (block descriptors, then those of the node weights: one copy)
+    const size_t bdb = (sizeof(BlockDesc) * nb + 255) & ~(size_t)255, ndb = sizeof(NodeDesc) * nb;
+    if ((rc = sv->desc.ensure(bdb + ndb)) || (rc = sv->hdesc.ensure(bdb + ndb)) ||
         (rc = sv->rec.ensure(sizeof(FitRecord) * nb)) || (rc = sv->hrec.ensure(sizeof(FitRecord) * nb)) ||
         (rc = sv->hstate.ensure(2 * sizeof(DeState) * nb)))
         return rc;
@@ -2451,14 +2458,18 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         any_fresh = any_fresh || sl.fresh;
         hd[q] = d;
     }
-    HIPCHK(hipMemcpyAsync(sv->desc.p, hd, sizeof(BlockDesc) * nb, hipMemcpyHostToDevice, s));
+    const int K = sv->cfg.gens_per_step;
+    NodeStep step;
+    if (nn && (rc = server_nodes(sv, act, nn, nn_fresh, K, reinterpret_cast<NodeDesc*>(static_cast<char*>(sv->hdesc.p) + bdb),
+                                 &step)))
+        return rc;
+    HIPCHK(hipMemcpyAsync(sv->desc.p, hd, bdb + sizeof(NodeDesc) * nn, hipMemcpyHostToDevice, s));
     const BlockDesc* dd = static_cast<const BlockDesc*>(sv->desc.p);
     const size_t de_lds = (size_t)P * kSlots * 8 + (size_t)de_threads * (8 + 8 + 4);
-    const int K = sv->cfg.gens_per_step;
     int node_launches = 0;
-    if (nn) {
-        if ((rc = server_nodes(sv, act, nn, nn_fresh, dd, K, s, &node_launches))) return rc;
-    }
+    if (nn && (rc = server_nodes_run(sv, step, reinterpret_cast<const NodeDesc*>(static_cast<const char*>(sv->desc.p) + bdb), dd,
+                                     K, s, &node_launches)))
+        return rc;
     const int nd = nb - nn;  // blocks whose samples are evaluated
     if (any_fresh) {
         hipLaunchKernelGGL(k_de_init_fresh, dim3(nd), dim3(de_threads), 0, s, dd + nn);
@@ -2480,13 +2491,17 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         hipLaunchKernelGGL(k_de_step, dim3(nd), dim3(de_threads), de_lds, s, dd + nn);
     }
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(64), 0, s, dd, static_cast<FitRecord*>(sv->rec.p));
-    HIPCHK(hipGetLastError());
+    // (states and records of node-weight blocks: from the fit itself)
     DeState* hst = static_cast<DeState*>(sv->hstate.p);
-    for (int q = 0; q < nb; ++q)
-        HIPCHK(hipMemcpyAsync(hst + 2 * q, sv->slots[act[q]].state.p, (lead && q >= nn ? 2 : 1) * sizeof(DeState),
+    if (nd) {
+        hipLaunchKernelGGL(k_finalize, dim3(nd), dim3(64), 0, s, dd + nn, static_cast<FitRecord*>(sv->rec.p));
+        HIPCHK(hipGetLastError());
+        for (int q = nn; q < nb; ++q)
+            HIPCHK(hipMemcpyAsync(hst + 2 * q, sv->slots[act[q]].state.p, (lead ? 2 : 1) * sizeof(DeState),
+                                  hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(static_cast<FitRecord*>(sv->hrec.p) + nn, sv->rec.p, sizeof(FitRecord) * nd,
                               hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(sv->hrec.p, sv->rec.p, sizeof(FitRecord) * nb, hipMemcpyDeviceToHost, s));
+    }
     HIPCHK(hipStreamSynchronize(s));
     const double now = sv->clock();
     const FitRecord* r = static_cast<const FitRecord*>(sv->hrec.p);
