@@ -430,7 +430,9 @@ int pt_server_create(pt_ctx* ctx, const pt_server_config* cfg, pt_server** out);
 /* Destroy a server (its queued and running blocks are dropped). */
 void pt_server_destroy(pt_server* srv);
 
-/* Queue a block of `track` (samples copied by the call, host or device).
+/* Queue a block of `track` (samples copied by the call, from host or device;
+ * the copy lies on the device if all waiting blocks fit the HBM budget beside
+ * the resident ones, for up to max_slots blocks, else in host memory).
  * PT_EBUSY when max_pending blocks are already queued; PT_EINVAL when the
  * block alone exceeds the HBM budget, or, with seed_first, when it is too
  * short for the three seeding snippets. */
