@@ -892,7 +892,8 @@ struct Members {
     __device__ __forceinline__ bool crossed(uint64_t w) const { return (uint32_t)(w >> 48) >> l8 & 1u; }
     // the bound rule (a mutant put half-way to one bound lies inside the other)
     __device__ __forceinline__ double bounded(double v, double x1) const {
-        const double vl = (lo + x1) * 0.5, vh = (hi + x1) * 0.5;
+        double vl = (lo + x1) * 0.5, vh = (hi + x1) * 0.5;
+        asm volatile("" : "+v"(vl), "+v"(vh));  // (selects, not branches around a sum and a product)
         return v < lo ? vl : (v > hi ? vh : v);
     }
     __device__ __forceinline__ double full(double y) const {
@@ -901,9 +902,8 @@ struct Members {
         lds_sums<SLOPE, QUART, COR>(q, l.zw, l.un, l8, K, a1, a2);
         return node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en_w, N);
     }
-    template <bool FIRST = false>
-    __device__ __forceinline__ void keep(int t, int g, char* x, double y, double ft) {
-        const bool take = (FIRST && g == 0) || ft <= fo[t];  // (generation 0 is accepted as it is)
+    __device__ __forceinline__ void keep(int t, char* x, double y, double ft) {
+        const bool take = ft <= fo[t];
         xi[t] = take ? y : xi[t];
         fo[t] = take ? ft : fo[t];
         // (octets that repeat the last member write the same values)
@@ -925,18 +925,38 @@ struct Members {
     }
 
     // generations on the full set, or a re-expanded one in LDS, until one of kind
-    // 1 or 2 is in effect
+    // 1 or 2 is in effect (in stretches, like register_loop's)
     __device__ __forceinline__ bool lds_loop(int& g) {
-        int n = sh.lev.K;
-        double mid = 0.0, nlo = 0.0, nhi = 0.0, en = 0.0;
+        // the set in use: the full one carries every trial
+        const double *zs, *us;
+        int n;
+        double mid, nlo, nhi, en;
         auto level = [&]() {
-            n = sh.lev.K;
-            if (!n) return;
+            const bool whole = sh.lev.K == 0;
+            zs = whole ? l.zw : l.lz;
+            us = whole ? l.un : l.lu;
+            n = whole ? K : sh.lev.K;
             limits(mid, nlo, nhi);
-            en = node_energy(l.lz, n, N);
+            mid = whole ? mid_w : mid;
+            nlo = whole ? -__builtin_inf() : nlo;
+            nhi = whole ? __builtin_inf() : nhi;
+            en = whole ? en_w : node_energy(l.lz, n, N);
         };
         level();
-        for (; g < g1; ++g) {
+        if (g == 0) {  // the initial population, accepted as it is
+            feed(0);
+#pragma unroll
+            for (int t = 0; t < NM; ++t) {
+                fo[t] = full(xi[t]);
+                *reinterpret_cast<double*>(place(t, 0)) = slot ? xi[t] : fo[t];
+            }
+            lds_barrier();
+            ++g;
+        }
+        uint64_t w[NM];
+#pragma unroll
+        for (int t = 0; t < NM; ++t) w[t] = draw(t, g);
+        while (g < g1) {
             if (!(g & 7)) {
                 if (!(g & 15) && sh.next.pend == g) {
                     relevel(nd, l, sh);
@@ -945,28 +965,35 @@ struct Members {
                 }
                 feed(g);
             }
-            if (stop_flag(g)) return true;
+            const char* xr = column(g);
+            char* xw[NM];
 #pragma unroll
-            for (int t = 0; t < NM; ++t) {
-                double y = xi[t];
-                if (g > 0) {
-                    const uint64_t w = draw(t, g);
+            for (int t = 0; t < NM; ++t) xw[t] = place(t, g);
+            int swap = (g & 1 ? 1 : -1) * P * kRowD * (int)sizeof(double);
+            const int end = min((g | 7) + 1, g1);
+            do {
+                const int stop = stop_flag(g);
+#pragma unroll
+                for (int t = 0; t < NM; ++t) {
                     double v, x1;
-                    mutant(column(g), w, v, x1);
-                    y = crossed(w) ? bounded(v, x1) : xi[t];
-                }
-                double ft;
-                if (n && __ballot(y >= nlo && y <= nhi) == ~0ull) {
+                    mutant(xr, w[t], v, x1);
+                    const double y = crossed(w[t]) ? bounded(v, x1) : xi[t];
+                    const unsigned long long inside = __ballot(y >= nlo) & __ballot(y <= nhi);
                     const NodeCand q = node_cand<SLOPE, QUART>((y - mid) * sc);
                     double a1 = 0.0, a2 = 0.0;
-                    lds_sums<SLOPE, QUART, COR>(q, l.lz, l.lu, l8, n, a1, a2);
-                    ft = node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
-                } else {
-                    ft = full(y);
+                    lds_sums<SLOPE, QUART, COR>(q, zs, us, l8, n, a1, a2);
+                    double ft = node_objective<SLOPE, COR>(nd, q, a1, a2, S2, en, N);
+                    asm volatile("" : "+v"(ft));
+                    if (__builtin_expect(inside != ~0ull, 0)) ft = full(y);
+                    w[t] = draw(t, g + 1);
+                    if (t == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(stop), 0)) return true;
+                    keep(t, xw[t], y, ft);
+                    xw[t] -= swap;
                 }
-                keep<true>(t, g, place(t, g), y, ft);
-            }
-            lds_barrier();
+                xr += swap;
+                swap = -swap;
+                lds_barrier();
+            } while (++g < end);
         }
         return false;
     }
@@ -1065,7 +1092,7 @@ struct Members {
                     }
                     w[t] = draw(t, g + 1);  // (not a draw after the last generation, and not used)
                     if (STOPS && t == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(stop), 0)) return true;
-                    keep(t, g, xw[t], y, ft);
+                    keep(t, xw[t], y, ft);
                     xw[t] -= swap;
                 }
                 xr += swap;
@@ -1088,9 +1115,13 @@ struct Members {
 
     __device__ __forceinline__ int run() {
         int g = g0;
-        bool often = true;
+        bool often = false;
         if (sh.lev.kind == 0 && lds_loop(g)) return g;
-        if (g < g1 && sh.lev.kind == 1 && register_loop<1, true, true>(g, often)) return g;
+        if (g < g1 && sh.lev.kind == 1) {
+            often = false;
+            if (register_loop<1, true, false>(g, often)) return g;
+            if (often && g < g1 && register_loop<1, true, true>(g, often)) return g;
+        }
         if (g < g1) {
             if (stops)
                 narrow<true>(g);
