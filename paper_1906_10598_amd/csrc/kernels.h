@@ -163,18 +163,26 @@ __device__ __forceinline__ void wave_sums(double (&v)[N]) {
 // compare and a select: fmin would first quieten its operands.  A NaN on the
 // left stays, one on the right is passed over.
 template <bool MAX>
-__device__ __forceinline__ double wave_extreme(double v) {
-    auto pick = [](double a, double b) { return (MAX ? b > a : b < a) ? b : a; };
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v = pick(v, dpp_move(v, s));
+__device__ __forceinline__ double pick_extreme(double a, double b) {
+    return (MAX ? b > a : b < a) ? b : a;
+}
+// over the four rows of 16 lanes, lane by lane
+template <bool MAX>
+__device__ __forceinline__ double rows_extreme(double v) {
     const int lo = __double2loint(v), hi = __double2hiint(v);
     const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
     const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    v = pick(__hiloint2double(h16[0], l16[0]), __hiloint2double(h16[1], l16[1]));
+    v = pick_extreme<MAX>(__hiloint2double(h16[0], l16[0]), __hiloint2double(h16[1], l16[1]));
     const int lo2 = __double2loint(v), hi2 = __double2hiint(v);
     const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
     const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
-    return pick(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
+    return pick_extreme<MAX>(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
+}
+template <bool MAX>
+__device__ __forceinline__ double wave_extreme(double v) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v = pick_extreme<MAX>(v, dpp_move(v, s));
+    return rows_extreme<MAX>(v);
 }
 
 __device__ __forceinline__ int find_block(const BlockDesc* __restrict__ descs, int nblk, int unit) {

@@ -615,67 +615,96 @@ __host__ __device__ inline double ellipse_growth(double b1, double b2, double b3
     return b1 * s1 + 0.5 * b2 * s2 + 0.25 * b3 * (s3 + 3.0 * s1) + 0.125 * b4 * (s4 + 4.0 * s2);
 }
 
-// Whether a smaller node set would carry the population after generation g,
-// whose best member is `best`; by one wave.
-__device__ __noinline__ void ask_level(const NodeDesc* nd, const FitLds& l, FitShared& sh, int P, double F, int g, int best) {
-    const int lane = threadIdx.x & 63;
-    const double* x = l.xs + (g & 1) * P * kRowD;
-    const double* xb = x + best * kRowD;
-    // largest distance of a member from the best one, per slot, with room for a
-    // mutant x1 + F (x2 - x3) of such members; in turns (half as much again makes
-    // the sets shrink later: 1 to 2.5 % of a fit)
-    const double room = 1.0 + 2.0 * F;
-    double rng[kSlots], q[5];
-#pragma unroll
-    for (int j = 1; j < kSlots; ++j) {
-        double a = 0.0;
-        for (int m = lane; m < P; m += 64) a = fmax(a, fabs(x[m * kRowD + j] - xb[j]));
-        rng[j] = room * wave_extreme<true>(a);
-        if (j != 5) q[j == 6 ? 4 : j - 1] = rng[j] * nd->sc[j];
-    }
-    // coefficients in x (u = x + c), of 2 delta, rad
-    const double c = fabs(nd->c), w = 1.0 + c, pi4 = 12.566370614359172;
-    const double b1 = pi4 * (q[1] + c * (2.0 * q[2] + c * (3.0 * q[3] + 4.0 * c * q[4])));
-    const double b2 = pi4 * (q[2] + c * (3.0 * q[3] + 6.0 * c * q[4])), b3 = pi4 * (q[3] + 4.0 * c * q[4]), b4 = pi4 * q[4];
-    const double sum = q[0] + w * (q[1] + w * (q[2] + w * (q[3] + w * q[4])));  // largest |delta|, turns
-    const int extra = nd->slope ? 2 : 0;
-    // the distances scaled up as far as 8 or 16 nodes allow (their bound is
-    // linear in the coefficients at a fixed ellipse: the best of the wave's
-    // ellipses) and delta stays within the polynomials' range
-    const double eta = 0.1 * (double)(lane + 1);
-    const double at0 = log(4e15 / (exp(eta) - 1.0)), slope = ellipse_growth(b1, b2, b3, b4, eta);
-    const double s8 = fmin(wave_extreme<true>(((8 - extra) * eta - at0) / slope), kNodeTurns8 / sum);
-    const double s16 = fmin(wave_extreme<true>(((16 - extra) * eta - at0) / slope), kNodeTurns16 / sum);
-    int K = 0, kind = 0;
-    double scale = 1.0;
-    if (s8 >= 1.0) {
-        K = 8;
-        kind = 2;
-        scale = s8;
-    } else if (s16 >= 1.0) {
-        K = 16;
-        kind = 1;
-        scale = s16;
-    } else {
-        const double need = wave_extreme<false>((at0 + slope) / eta + extra);
-        if (need <= (double)kNodeMaxK) K = ((int)ceil(need) + 7) & ~7;
-    }
-    // worth it for fewer than five eighths of the nodes
-    const int cur = sh.lev.K ? sh.lev.K : nd->K;
-    if (K == 0 || (kind ? kind <= sh.lev.kind : 8 * K > 5 * cur) || K > level_cap(nd->K)) return;
-    if (lane == 0) {
-        Level& n = sh.next;
-#pragma unroll
-        for (int j = 0; j < kSlots; ++j) {
-            const bool amp = j == 0 || j == 5;
-            n.mid[j] = amp ? 0.0 : xb[j];
-            n.lim[j] = amp ? __builtin_inf() : rng[j] * fmin(scale, 1e9);  // (finite: rng may be 0)
-        }
-        n.K = K;
-        n.kind = kind;
-        n.pend = g + 2;
-    }
+// 1 / v to a part in 1e15 (v normal): for limits and node counts only.
+__device__ __forceinline__ double near_rcp(double v) {
+    const double r = __builtin_amdgcn_rcp(v), e = __fma_rn(-v, r, 1.0);
+    const double s = __fma_rn(r, e, r);
+    return __fma_rn(s, __fma_rn(-v, s, 1.0), s);
 }
+
+// Whether a smaller node set would carry the population: by one wave, a lane per
+// ellipse.  What depends on neither population nor generation is worked out once
+// per launch and the eight slots are reduced side by side: all waves wait for a
+// look, every 16th generation until the smallest set is in use, and it took 1.4 us
+// longer with the exponentials, logarithms and one reduction after the other.
+struct LevelRule {
+    double eta, reta, at0, g[4];  // the lane's ellipse (nodes_needed)
+    double sc, c;                 // scale of the lane's slot (lane & 7); centre
+    int K, extra;
+
+    __device__ __forceinline__ void init(const NodeDesc* nd) {
+        const int lane = threadIdx.x & 63, j = lane & 7;
+        eta = 0.1 * (double)(lane + 1);
+        reta = 1.0 / eta;
+        at0 = log(4e15 / (exp(eta) - 1.0));
+        g[0] = ellipse_growth(1.0, 0.0, 0.0, 0.0, eta);
+        g[1] = ellipse_growth(0.0, 1.0, 0.0, 0.0, eta);
+        g[2] = ellipse_growth(0.0, 0.0, 1.0, 0.0, eta);
+        g[3] = ellipse_growth(0.0, 0.0, 0.0, 1.0, eta);
+        sc = j < kSlots ? gld(&nd->sc[j]) : 0.0;
+        c = fabs(nd->c);
+        K = nd->K;
+        extra = nd->slope ? 2 : 0;
+    }
+    // after generation gen, whose best member is `best`
+    __device__ __forceinline__ void look(const FitLds& l, FitShared& sh, int P, double F, int gen, int best) const {
+        const int lane = threadIdx.x & 63, j = lane & 7;
+        const double* x = l.xs + (gen & 1) * P * kRowD;
+        // largest distance of a member from the best one in the lane's slot (eight
+        // lanes share a slot's members), with room for a mutant x1 + F (x2 - x3) of
+        // such members (half as much again makes the sets shrink later: 1 to 2.5 % of
+        // a fit)
+        const double xb = x[best * kRowD + j];
+        double a = 0.0;
+        for (int m = lane >> 3; m < P; m += 8) a = fmax(a, fabs(x[m * kRowD + j] - xb));
+        a = fmax(a, lane_move<0x128>(a));  // row_ror:8
+        a = rows_extreme<true>(a);
+        const double rng = (1.0 + 2.0 * F) * a, turns = rng * sc;
+        auto of = [&](int slot) {
+            return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(turns), slot),
+                                    __builtin_amdgcn_readlane(__double2loint(turns), slot));
+        };
+        const double q0 = of(1), q1 = of(2), q2 = of(3), q3 = of(4), q4 = of(6);
+        // coefficients in x (u = x + c), of 2 delta, rad
+        const double w = 1.0 + c, pi4 = 12.566370614359172;
+        const double b1 = pi4 * (q1 + c * (2.0 * q2 + c * (3.0 * q3 + 4.0 * c * q4)));
+        const double b2 = pi4 * (q2 + c * (3.0 * q3 + 6.0 * c * q4)), b3 = pi4 * (q3 + 4.0 * c * q4), b4 = pi4 * q4;
+        const double rsum = near_rcp(q0 + w * (q1 + w * (q2 + w * (q3 + w * q4))) + 1e-300);  // 1 / largest |delta|
+        // the distances scaled up as far as 8 or 16 nodes allow (their bound is
+        // linear in the coefficients at a fixed ellipse: the best of the wave's
+        // ellipses) and delta stays within the polynomials' range
+        const double slope = (b1 * g[0] + b2 * g[1]) + (b3 * g[2] + b4 * g[3]), rs = near_rcp(slope + 1e-300);
+        const double s8 = fmin(wave_extreme<true>(((8 - extra) * eta - at0) * rs), kNodeTurns8 * rsum);
+        const double s16 = fmin(wave_extreme<true>(((16 - extra) * eta - at0) * rs), kNodeTurns16 * rsum);
+        const double need = wave_extreme<false>((at0 + slope) * reta + extra);
+        int n = 0, kind = 0;
+        double scale = 1.0;
+        if (s8 >= 1.0) {
+            n = 8;
+            kind = 2;
+            scale = s8;
+        } else if (s16 >= 1.0) {
+            n = 16;
+            kind = 1;
+            scale = s16;
+        } else if (need <= (double)kNodeMaxK) {
+            n = ((int)ceil(need) + 7) & ~7;
+        }
+        // worth it for fewer than five eighths of the nodes
+        const int cur = sh.lev.K ? sh.lev.K : K;
+        if (n == 0 || (kind ? kind <= sh.lev.kind : 8 * n > 5 * cur) || n > level_cap(K)) return;
+        if (lane < kSlots) {
+            const bool amp = j == 0 || j == 5;
+            sh.next.mid[j] = amp ? 0.0 : xb;
+            sh.next.lim[j] = amp ? __builtin_inf() : rng * fmin(scale, 1e9);  // (finite: rng may be 0)
+        }
+        if (lane == 0) {
+            sh.next.K = n;
+            sh.next.kind = kind;
+            sh.next.pend = gen + 2;
+        }
+    }
+};
 
 // The bookkeeping of each generation, by one wave: best objective, history, stop
 // rule, and every 16th generation a look at the node set.  It runs one
@@ -694,6 +723,7 @@ struct Book {
     double vtr, rel_tol, floor, F, bf, low;  // low: the best member's comparison value, bf: its objective
     bool cor;
     double* hist;
+    LevelRule rule;
 
     __device__ __forceinline__ Book(const NodeDesc* nd_, const BlockDesc* d, const FitLds& l_, FitShared& sh_)
         : nd(nd_), l(l_), sh(sh_) {
@@ -710,6 +740,7 @@ struct Book {
         pend = __builtin_amdgcn_readfirstlane(sh.next.pend);
         bf = low = __builtin_inf();
         cor = d->objective != 0;
+        if (kind < 2) rule.init(nd);
     }
     // (lanes past the population repeat its last member)
     __device__ __forceinline__ double value(int g, int t) const {
@@ -763,7 +794,7 @@ struct Book {
                 sh.stop_gen = g;
             }
             if (look && !flags) {
-                ask_level(nd, l, sh, P, F, g, best);
+                rule.look(l, sh, P, F, g, best);
                 pend = __builtin_amdgcn_readfirstlane(sh.next.pend);
             }
         }
