@@ -76,7 +76,7 @@ struct NodeDesc {
     int runs;          // kNodeRun-sample runs per projection workgroup
     int ntile;         // tiles
     int proj_begin, nproj;  // projection workgroups
-    int mom_begin, nmom;    // moments workgroups
+    int mom_begin, nmom;    // moments workgroups before it; groups of points
     int g0;            // next generation of the block when the descriptors were uploaded
     int parity;        // which half of `draws` the next launch reads
     double* pts;       // ntile x 16 x (Re s e, Im s e, Re e^2, Im e^2)
@@ -118,6 +118,7 @@ __host__ __device__ inline size_t node_draw_words(int P, int gens) {
 
 // Launches (nd / bd: device tables of nblk blocks; chunk: generations per
 // half of `draws`).  `off`: generations run since the tables were uploaded.
+inline int node_mom_wgs(const NodeDesc& n) { return n.nmom * ((n.K + 63) / 64); }
 hipError_t node_project(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_proj, hipStream_t s);
 hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int total_mom, int P, int ngen, int chunk,
                         hipStream_t s);

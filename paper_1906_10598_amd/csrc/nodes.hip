@@ -240,8 +240,9 @@ __global__ __launch_bounds__(256) void k_node_project(const NodeDesc* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Moments: sum over 128 points of value x T_j(x_point) for j < K; a lane holds
-// one j, the waves share the points.  Workgroups past `total` make the draws of
+// Moments: sum over 128 points of value x T_j(x_point) for 64 of the K values of
+// j; a lane holds one j, the waves share the points (all K values in one workgroup
+// took 8 to 13 us for 144 to 256 nodes, 5 apart).  Workgroups past `total` make the draws of
 // the fit's first launch (here rather than beside the projection, whose registers
 // allow two waves on a SIMD: 64 blocks' draws of 1500 generations, 3.8e6 of them,
 // 58 us there, 41 here).
@@ -256,7 +257,8 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
     const int b = node_block_of(nds, nblk, blockIdx.x, true);
     const NodeDesc* nd = nds + b;
     const BlockDesc* d = bds + b;
-    const int wg = blockIdx.x - nd->mom_begin, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int K = nd->K, parts = (K + 63) >> 6, at = blockIdx.x - nd->mom_begin, wg = at / parts, j0 = (at - wg * parts) * 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t N = d->n;
     const int64_t B = (int64_t)16 * nd->runs << nd->lanes_log, Be = B < N ? B : N;
     const int npt = nd->ntile * kNodePts, p0 = wg * kNodeGroup, np = min(kNodeGroup, npt - p0);
@@ -273,27 +275,22 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
         for (int q = 0; q < 4; ++q) v[tid][q] = gld(nd->pts + (size_t)pt * 4 + q);
     }
     __syncthreads();
-    const int K = nd->K;
-    for (int j0 = 0; j0 < K; j0 += 64) {
-        const double j = (double)(j0 + lane);
-        double a[4] = {0.0, 0.0, 0.0, 0.0};
+    const double j = (double)(j0 + lane);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
-        for (int p = wave; p < np; p += 4) {
-            const double t = th[p], y = j * t, e = __fma_rn(j, t, -y);
-            const double r = (y - rint(y)) + e;
-            const double c = cos_turns64(r * r);
+    for (int p = wave; p < np; p += 4) {
+        const double t = th[p], y = j * t, e = __fma_rn(j, t, -y);
+        const double r = (y - rint(y)) + e;
+        const double c = cos_turns64(r * r);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) a[q] = __fma_rn(c, v[p][q], a[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) red[wave][lane][q] = a[q];
-        __syncthreads();
-        const int jl = tid >> 2, q = tid & 3;
-        if (j0 + jl < K)
-            gst(nd->mom + ((size_t)wg * K + j0 + jl) * 4 + q,
-                (red[0][jl][q] + red[1][jl][q]) + (red[2][jl][q] + red[3][jl][q]));
-        __syncthreads();
+        for (int q = 0; q < 4; ++q) a[q] = __fma_rn(c, v[p][q], a[q]);
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[wave][lane][q] = a[q];
+    __syncthreads();
+    const int jl = tid >> 2, q = tid & 3;
+    if (j0 + jl < K)
+        gst(nd->mom + ((size_t)wg * K + j0 + jl) * 4 + q, (red[0][jl][q] + red[1][jl][q]) + (red[2][jl][q] + red[3][jl][q]));
 }
 
 // ---------------------------------------------------------------------------

@@ -1010,7 +1010,7 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
         n.proj_begin = proj;
         n.mom_begin = mom;
         proj += n.nproj;
-        mom += n.nmom;
+        mom += node_mom_wgs(n);
         auto take = [&](size_t doubles) {
             double* p = ws;
             ws += doubles;
@@ -2263,7 +2263,7 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
             n.proj_begin = proj;
             n.mom_begin = mom;
             proj += n.nproj;
-            mom += n.nmom;
+            mom += node_mom_wgs(n);
             n.pts = ws;
             n.s2 = n.pts + sl.plan.pts_doubles;
             n.mom = n.s2 + sl.plan.s2_doubles;
