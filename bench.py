@@ -9,8 +9,11 @@ the fitted record (coefficients + derived observables) on the host.
 Printed (one JSON line): candidate*sample evaluations per second of the
 plain FP64 path, fit latency p50 / p99 of the plain and mixed-precision
 paths, the mixed path's speedup and error against the FP64 oracle, the
-objective kernel's roofline figures (HIP-event timing of its launches inside
-a fit) and the CPU oracle's rate on a bounded sample of the same workload.
+roofline figures of the fit's kernels (HIP events around the timed fits) and of
+the objective over the samples, and the CPU oracle's rate on a bounded sample of
+the same workload.  The fits run through node weights (sums over the samples as
+sums over about a hundred nodes, the same to FP64 rounding), so a candidate
+evaluation is credited with all the samples it stands for.
 """
 import argparse
 import json
@@ -36,8 +39,10 @@ VALU_ISSUE_SLOTS_PER_S = 1024 * 2.4e9 / 4.0  # wave64 VALU instructions: 1024 SI
 # square-accumulate FMA -- about 40 FP64 FLOP.  Every arithmetic computes
 # that objective and is credited the same work (the phasor path executes 12
 # to 15 FP64 operations per candidate*sample, an FMA counted as two, so its
-# algorithmic rate is an equivalent rate and can exceed the hardware peak);
-# `executed` gives the counter-measured FP64 operations of the same launches.
+# algorithmic rate is an equivalent rate and can exceed the hardware peak; a fit
+# through node weights evaluates 8 to a few hundred nodes instead of the samples,
+# so its rate exceeds the peak many times); `executed` gives the counter-measured
+# FP64 operations of the same launches.
 ALG_FLOP = 40
 ARITH_NAME = {0: "fp64-per-sample", 1: "mixed", 2: "fp64-phasor"}
 
@@ -325,20 +330,18 @@ def batch_fits(ctx, ptk, synth, np, torch, P, seed, crlb_f0_block, tiles):
                        "roofline": {"bound": "alu", "unit": "TFLOP/s", "peak": PEAK_FP64_TFLOPS,
                                     "achieved": ach, "frac": ach / PEAK_FP64_TFLOPS,
                                     "flop_per_candidate_sample": ALG_FLOP,
-                                    "note": "whole-batch algorithmic rate (40 FLOP per candidate*sample over the "
-                                            "wall time of the batch, DE steps and launch gaps included); above 1 "
-                                            "because the FP64 phasor arithmetic executes ~12 FP64 operations per "
-                                            "candidate*sample for the same result (`executed` gives the counter "
-                                            "rate); the mixed path's per-sample FP32 cosine executes ~27 FP32 and ~2 FP64"}}
+                                    "note": "whole-batch equivalent rate (40 FLOP per candidate*sample over the "
+                                            "wall time of the batch, host work and DE steps included); far above "
+                                            "1 because the fits evaluate their candidates at the nodes of the "
+                                            "blocks' weights, not at the samples (`executed` gives the counter "
+                                            "rate of the fit kernel)"}}
     batch["workload"] = ("64 blocks, N log-uniform in [5e4, 4e5] at 50 kHz (total %d samples), own "
-                         "populations P=40, 1500 generations, one launch per generation" % sum(x.n for x in blocks))
-    g = batch["fp64"]["geometry"]
-    prof = profile_of("batch_last_64blocks_%dx%d.md" % tuple(g), "batch-64", g, "batch-last")
+                         "populations P=40, 1500 generations" % sum(x.n for x in blocks))
+    prof = profile_of("batch_nodes_64blocks.md", "batch-64", (0, 0), "batch-nodes")
     if prof.get("avg_us"):
         ex = executed_roofline(prof, prof["avg_us"] * 1e-3)
         if ex:
-            ex["kernel"] = ("k_objective (FP64 phasor, last-workgroup DE step) as the 64-block batch launches it, "
-                            "per dispatch, profile time")
+            ex["kernel"] = "k_node_fit as the 64-block batch launches it (one workgroup per block), profile time"
             ex["avg_launch_ms"] = prof["avg_us"] * 1e-3
         batch["fp64"]["roofline"]["executed"] = ex
         batch["fp64"]["roofline"]["traffic"] = prof.get("bytes_per_launch")
@@ -487,8 +490,8 @@ def main():
     extra = max(0, args.latency_fits - args.steps)
     _, lat_more, _ = run_fits(ctx, blk, lambda k: de(ptk.PT_PREC_FP64)(args.steps + k), extra, "fp64-lat")
     lat64 = lat_steps + lat_more
-    # first fits of a fresh context at the same geometry: the first one captures
-    # and instantiates the fit's launch graphs, the second replays them
+    # first fits of a fresh context at the same geometry: the first one allocates
+    # its buffers, the second has them
     with ptk.Context(0) as cold:
         ptk.pt_ctx_set_tile(cold.handle, *tiles["fp64"])
         _, lat_cold, _ = run_fits(cold, blk, de(ptk.PT_PREC_FP64), 2, "fp64-cold")
@@ -536,12 +539,11 @@ def main():
                           tiles["fp64"], "objective")
     mx_prof = profile_of("k_objective_mixed_paper400k_%dx%d.md" % tuple(tiles["mixed"]), "paper-400000-fp32",
                          tiles["mixed"], "objective")
-    fit_prof = profile_of("fit_lead_paper400k_%dx%d.md" % tuple(tiles["fp64"]), "paper-400000-fp32",
-                          tiles["fp64"], "fit-lead")
+    fit_prof = profile_of("fit_nodes_paper400k.md", "paper-400000-fp32", (0, 0), "fit-nodes")
 
-    # the kernel as the timed fits launch it: HIP events around the timed region
-    # on the fits' stream, divided by the launches it held (every launch but each
-    # fit's last one evaluates the population: ALG_FLOP * P * N)
+    # the fit's generations as the timed fits launch them: HIP events around the
+    # timed region on the fits' stream, divided by the launches of generations it
+    # held (one per fit; the projection and moments kernels' ~20 us are in it)
     fit_launch_ms = ev[0] / (args.steps * launches_per_fit)
     fit_ach = ALG_FLOP * pairs_per_fit * args.steps / (ev[0] * 1e-3) / 1e12
 
@@ -558,14 +560,14 @@ def main():
         serving["roofline"] = {"bound": "arrivals", "unit": "TFLOP/s", "peak": PEAK_FP64_TFLOPS, "achieved": ach,
                                "frac": ach / PEAK_FP64_TFLOPS, "flop_per_candidate_sample": ALG_FLOP,
                                "note": "algorithmic work of the served fits over the run's wall time: the offered "
-                                       "load (20 blocks/s) sets it, not the kernels; `step_kernel` is the objective "
-                                       "launch the server makes, per dispatch"}
-        sprof = profile_of("server_step_16tracks_16x4.md", "serving-16", (16, 4), "server")
+                                       "load (20 blocks/s) sets it, not the kernels; `step_kernel` is the fit "
+                                       "launch of a server step, per dispatch"}
+        sprof = profile_of("server_nodes_16tracks.md", "serving-16", (0, 0), "server-nodes")
         if sprof.get("avg_us"):
             ex = executed_roofline(sprof, sprof["avg_us"] * 1e-3)
             if ex:
                 ex["avg_launch_ms"] = sprof["avg_us"] * 1e-3
-                ex["kernel"] = "k_objective (16 x 4, objective alone) as the server launches it, profile time"
+                ex["kernel"] = "k_node_fit as a server step launches it (32 generations), profile time"
             serving["roofline"]["step_kernel"] = ex
         print(f"# serving: p50 {serving['latency_ms']['p50']:.1f} ms p99 {serving['latency_ms']['p99']:.1f} ms",
               file=sys.stderr, flush=True)
@@ -643,8 +645,9 @@ def main():
                                "traffic": mx_prof.get("bytes_per_launch"), "executed": ex_mx}},
         "roofline": {"bound": "alu", "achieved": fit_ach, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": fit_ach / PEAK_FP64_TFLOPS, "traffic": fit_prof.get("bytes_per_launch"),
-                     "kernel": "k_objective (FP64, %s) as launched in the timed fits: one launch per "
-                               "generation with the leading DE step" % arith64,
+                     "kernel": "k_node_fit (FP64, node weights) as launched in the timed fits: one launch "
+                               "of one workgroup for all generations; an equivalent rate, bound by the chain of "
+                               "dependent operations of a generation, not by arithmetic or bandwidth",
                      "avg_launch_ms": fit_launch_ms, "launches_per_fit": launches_per_fit,
                      "event_ms_timed_region": ev[0],
                      "flop_per_candidate_sample": ALG_FLOP, "kernel_hash": kernel_hash(),

@@ -312,9 +312,9 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
 // each.  So the fewest instructions a wave needs and the fewest waves a SIMD
 // holds pull against each other; measured for P = 40: 16 lanes a member (ten
 // waves) 0.99 us a generation, 8 lanes (five) 0.45, 4 lanes (three) 0.54; 8 lanes
-// with the bound rule and the stop flag off the chain where they can be 0.41, with what
-// waits for a multiple of 8 out of the loop 0.365 (P = 64 0.38, 120 0.58, 240
-// 1.17).  The draws pass through LDS 16 generations at a time, so a launch runs
+// with the bound rule and the stop flag off the chain where they can be 0.41, with
+// what waits for a multiple of 8 out of the loop 0.365, now 0.35 (P = 64 0.38,
+// 120 0.58, 240 1.17).  The draws pass through LDS 16 generations at a time, so a launch runs
 // as many generations as there are; while all of a launch's lay there, a fit of
 // 2000 generations took five launches, each ~14 us for its start.
 //
@@ -1077,7 +1077,7 @@ struct Members {
         // In stretches to the next multiple of 8: what can wait is done between
         // them (draws, a pending set, the count of side paths), and the two copies'
         // places are held and swapped instead of worked out (P = 40: 115
-        // instructions and 0.44 us a generation with these inside, 91 and 0.365
+        // instructions and 0.44 us a generation with these inside, 90 and 0.35
         // without).
         while (g < g1) {
             if (!(g & 7)) {

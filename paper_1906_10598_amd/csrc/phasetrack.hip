@@ -3,7 +3,8 @@
 // The runtime owns device buffers per context, plans the objective grid of
 // a launch (units of (block, sample tile, candidate group)), captures chunks
 // of DE generations into HIP graphs and replays them, and turns the final
-// device records into the per-block output of the paper's Appendix 1.
+// device records into the per-block output of the paper's Appendix 1.  Fits
+// go through node weights (nodes.h) where those apply.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,8 +28,8 @@
 
 using namespace pt;
 
-// Device memory of pt_objective_noalloc: the block descriptor, the packed
-// population rows and the tile partial sums of one call.  Each device the
+// Device memory of pt_objective_noalloc: the tile partial sums of one call (past
+// room once taken by a descriptor and packed rows).  Each device the
 // library runs on holds its own copy for the life of the process; host code
 // reaches it only through the address hipGetSymbolAddress gives for the
 // current device (pt_ctx::noalloc), never through this name.

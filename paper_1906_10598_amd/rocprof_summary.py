@@ -152,7 +152,7 @@ def summarise(root, kernel, command, form, workload):
         out.append(f"Executed operations per launch (counters x 64 lanes, FMA x 2): FP64 {f64:.4g}, FP32 {f32:.4g}; "
                    f"at the average duration: FP64 {f64 / (avg_ns * 1e-9) / 1e12:.2f} TFLOP/s "
                    f"({f64 / (avg_ns * 1e-9) / 78.6e12:.1%} of 78.6), FP32 {f32 / (avg_ns * 1e-9) / 1e12:.2f} TFLOP/s.\n")
-    geo = ""
+    geo = " geometry=0,0"  # (kernels without the objective's tile shape)
     m = re.search(r"k_objective<\w+, (\d+), (\d+)", kernel)
     if m:
         geo = f" geometry={m.group(1)},{m.group(2)}"
