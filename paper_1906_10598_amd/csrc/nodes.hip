@@ -854,8 +854,8 @@ struct Members {
         sc = slot ? gld(&nd->sc[j]) : 0.0;
         en_w = node_energy(l.zw, K, N);
         // (fits of a fixed number of generations are stopped by nothing but their
-        // abandonment, which may come late)
-        stops = (d->rel_tol > 0.0 && d->window > 0) || d->vtr > -__builtin_inf();
+        // abandonment, which may come late, unless the launch reaches past their end)
+        stops = (d->rel_tol > 0.0 && d->window > 0) || d->vtr > -__builtin_inf() || g1 - 1 > d->max_gens;
         const double* x = l.xs + ((g0 + 1) & 1) * P * kRowD;
 #pragma unroll
         for (int t = 0; t < NM; ++t) {
