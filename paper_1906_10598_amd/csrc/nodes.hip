@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
 // holds pull against each other; measured for P = 40: 16 lanes a member (ten
 // waves) 0.99 us a generation, 8 lanes (five) 0.45, 4 lanes (three) 0.54; 8 lanes
 // with the bound rule and the stop flag off the chain where they can be 0.41, with
-// what waits for a multiple of 8 out of the loop 0.365, now 0.35 (P = 64 0.38,
+// what waits for a multiple of 8 out of the loop 0.35, two a turn of it 0.34 (P = 64 0.38,
 // 120 0.58, 240 1.17).  The draws pass through LDS 16 generations at a time, so a launch runs
 // as many generations as there are; while all of a launch's lay there, a fit of
 // 2000 generations took five launches, each ~14 us for its start.
@@ -332,6 +332,10 @@ __global__ __launch_bounds__(256) void k_node_moments(const NodeDesc* __restrict
 // ---------------------------------------------------------------------------
 constexpr int kRowD = kStride;  // doubles of a member's row in LDS: seven slots, then its objective
 
+// draws of a wave and member of its octets in LDS: 32 generations of eight, then
+// the first again (a stretch of eight reads one past its end without a wrap)
+constexpr int kDrawRing = 33 * 8;
+
 struct FitLds {
     double *xs;        // two generations of P rows
     double *zw, *un;   // full node set: -2 Z and W (4 doubles a node), u
@@ -347,7 +351,7 @@ __host__ __device__ inline int level_cap(int K) { return K <= 2 * kNodePts ? kNo
 
 __host__ __device__ inline size_t fit_lds_doubles(int P, int maxK) {
     return (size_t)2 * P * kRowD + 11 * (size_t)maxK + 7 * (size_t)level_cap(maxK) + 2 + kNodeRing +
-           (size_t)256 * node_nm(P) * node_waves(P);
+           (size_t)kDrawRing * node_nm(P) * node_waves(P);
 }
 
 __device__ __forceinline__ FitLds fit_lds(double* base, int P, int maxK) {
@@ -801,6 +805,7 @@ struct Book {
     // generation's books
     __device__ __forceinline__ int run(int g0, int g1) {
         int f2 = 0, f1 = 0;  // flags of generations g - 2 and g - 1
+        asm volatile(".p2align 6, , 60");  // (as the members' loop)
         for (int g = g0; g < g1; ++g) {
             if (pend == g) {
                 relevel(nd, l, sh);
@@ -865,7 +870,7 @@ struct Members {
         }
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
         src = draws + wave * NM * 128 + 2 * lane;
-        ring = l.dr + wave * NM * 256;
+        ring = l.dr + wave * NM * kDrawRing;
         fetch();
         put(g0 >> 4);
         if (g0 & 15) {
@@ -889,9 +894,14 @@ struct Members {
     __device__ __forceinline__ void put(int block) {
 #pragma unroll
         for (int t = 0; t < NM; ++t) {
-            uint64_t* o = ring + t * 256 + (block & 1) * 128 + 2 * (threadIdx.x & 63);
+            const int lane = threadIdx.x & 63;
+            uint64_t* o = ring + t * kDrawRing + (block & 1) * 128 + 2 * lane;
             o[0] = pre[t][0];
             o[1] = pre[t][1];
+            if (!(block & 1) && lane < 4) {
+                o[256] = pre[t][0];
+                o[257] = pre[t][1];
+            }
         }
     }
     // at multiples of 8
@@ -902,7 +912,10 @@ struct Members {
             fetch();
     }
     __device__ __forceinline__ uint64_t draw(int t, int g) const {
-        return ring[t * 256 + (g & 31) * 8 + ((threadIdx.x >> 3) & 7)];
+        return draws(g)[t * kDrawRing];
+    }
+    __device__ __forceinline__ const uint64_t* draws(int g) const {
+        return ring + (g & 31) * 8 + ((threadIdx.x >> 3) & 7);
     }
 
     // this lane's column of the rows that generation g reads
@@ -1078,7 +1091,7 @@ struct Members {
         // them (draws, a pending set, the count of side paths), and the two copies'
         // places are held and swapped instead of worked out (P = 40: 115
         // instructions and 0.44 us a generation with these inside, 90 and 0.35
-        // without).
+        // without; 85 and 0.34 two generations at a time).
         while (g < g1) {
             if (!(g & 7)) {
                 if (KIND == 1 && !(g & 15) && sh.next.pend == g) {
@@ -1087,18 +1100,10 @@ struct Members {
                 }
                 feed(g);
             }
-            const char* xr = column(g);
-            char* xw[NM];
-#pragma unroll
-            for (int t = 0; t < NM; ++t) xw[t] = place(t, g);
-            int swap = (g & 1 ? 1 : -1) * P * kRowD * (int)sizeof(double);  // from the copy read to the one written
             int side = 0;
-            const int end = min((g | 7) + 1, g1);
-            // (the loop at a multiple of 64 bytes: 1.3 % of a fit between the best and the
-            // worst place for its 600 bytes)
-            asm volatile(".p2align 6, , 60");
-            do {
-                const int stop = STOPS ? stop_flag(g) : 0;
+            // one generation: rows read from xr, written to xw; next: the draws of the one
+            // after it (not made after the last generation, and not used)
+            auto one = [&](const char* xr, char* const (&xw)[NM], const uint64_t* next, int stop) {
 #pragma unroll
                 for (int t = 0; t < NM; ++t) {
                     double v, x1;
@@ -1118,15 +1123,47 @@ struct Members {
                             ++side;
                         }
                     }
-                    w[t] = draw(t, g + 1);  // (not a draw after the last generation, and not used)
+                    w[t] = next[t * kDrawRing];
                     if (STOPS && t == 0 && __builtin_expect(__builtin_amdgcn_readfirstlane(stop), 0)) return true;
                     keep(t, xw[t], y, ft);
-                    xw[t] -= swap;
                 }
-                xr += swap;
-                swap = -swap;
                 lds_barrier();
-            } while (++g < end);
+                return false;
+            };
+            if (!STOPS && !(g & 7) && g + 8 <= g1) {
+                // a whole stretch, two generations at a time: places and draws at fixed offsets
+                const char *even = column(g), *odd = column(g + 1);
+                char *to_even[NM], *to_odd[NM];
+#pragma unroll
+                for (int t = 0; t < NM; ++t) {
+                    to_even[t] = place(t, g);
+                    to_odd[t] = place(t, g + 1);
+                }
+                const uint64_t *next = draws(g) + 8, *last = next + 64;
+                // (the loop at a multiple of 64 bytes: 1.3 % of a fit between the best and the
+                // worst place for it)
+                asm volatile(".p2align 6, , 60");
+                do {
+                    one(even, to_even, next, 0);
+                    one(odd, to_odd, next + 8, 0);
+                } while ((next += 16) != last);
+                g += 8;
+            } else {
+                const char* xr = column(g);
+                char* xw[NM];
+#pragma unroll
+                for (int t = 0; t < NM; ++t) xw[t] = place(t, g);
+                int swap = (g & 1 ? 1 : -1) * P * kRowD * (int)sizeof(double);  // from the copy read to the one written
+                const int end = min((g | 7) + 1, g1);
+                asm volatile(".p2align 6, , 60");
+                do {
+                    if (one(xr, xw, draws(g + 1), STOPS ? stop_flag(g) : 0)) return true;
+#pragma unroll
+                    for (int t = 0; t < NM; ++t) xw[t] -= swap;
+                    xr += swap;
+                    swap = -swap;
+                } while (++g < end);
+            }
             if (!BOUNDS && side > 2 * NM) {
                 often = true;
                 return false;
