@@ -34,8 +34,9 @@ namespace pt {
 // Variant 0: plain accesses, agent-scope acquire / release fences (L2
 // invalidate / write-back).  Variant 1: coherent (agent-scope atomic) loads,
 // so readers need no L2 invalidate.  Variant 2 (built): coherent loads and
-// stores, so neither side needs cache maintenance; fences only order the
-// wave.  All three give bit-identical fits; on the paper-scale block the fit
+// stores, so neither side needs cache maintenance; every wave waits for its
+// stores to arrive before one thread publishes them (stores_done), and fences
+// order the wave's own accesses.  All three give bit-identical fits; on the paper-scale block the fit
 // takes 70, 52 and 48 ms with them.
 // ---------------------------------------------------------------------------
 #ifndef PT_SYNC_VARIANT
@@ -98,6 +99,14 @@ __device__ __forceinline__ void xsti(int* p, int v) {
     gst(p, v);
 #endif
 }
+
+// Waits until the wave's own stores have arrived where every XCD reads them (xst
+// writes through to there).  A workgroup barrier does not: at that scope a release
+// leaves global stores in flight, as the waves of a workgroup share their caches.
+// So every wave that has stored something another workgroup will read waits here
+// before the barrier behind which one thread counts or publishes it; without, that
+// count could be seen before the stores of the other three waves.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---------------------------------------------------------------------------
 // helpers
@@ -1680,7 +1689,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))
     if (!rule.tail) return;
 
     // arrivals, counted per XCD range first as in k_objective
-    __syncthreads();  // every wave's partial stores are issued
+    stores_done();
+    __syncthreads();  // every wave's partial stores have arrived
     if (tid == 0) {
         const int xcd = bid & 7, nx = min(total_units, (xcd + 1) * Ux) - xcd * Ux;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, PT_REL_SCOPE);
@@ -1770,7 +1780,8 @@ __device__ __forceinline__ int units_in_range(const BlockDesc* d, int x, int Ux,
 // count and reduction order as k_de_step, so fits are bit-identical to the
 // two-launch form) and clears the counters for the next launch.  No
 // workgroup waits for another.  Partial sums are coherent stores and loads
-// (xst / xld), so the fences only order each wave's accesses around its
+// (xst / xld): every wave waits for its stores (stores_done) before the
+// workgroup is counted, and the fences order a wave's own accesses around its
 // counter update.
 //
 // fused = 2 + k (fits with P <= 256): the leading-step form (de_lead), launch
@@ -1872,7 +1883,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))
 
         int* sync = d->sync;
         const int xcd = bid & 7;
-        __syncthreads();  // every wave's partial stores are issued
+        stores_done();
+        __syncthreads();  // every wave's partial stores have arrived
         // (one counter per block instead of per XCD range: fits 30 % slower on MI355X,
         // the same-address atomics from all XCDs serialise)
         if (threadIdx.x == 0) {
@@ -1956,10 +1968,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))
             if (!resident) load_lane<V, T, S>(d, tile, sv, full, valid);
             unit_setup<S, CPG, MODE, SLOPE, true>(d, tile, group, cs, rc, d->trial);
             objective_unit<S, CPG, MODE, SLOPE>(d, tile, group, sv, full, valid, cs, rc, red, d->partials);
-            // The workgroup barrier makes every wave's partial stores visible
-            // at the XCD's L2; one release fence then publishes them device-wide
+            // Every wave's partial stores have arrived before the barrier, hence
             // before the arrival is counted.  Arrivals are counted per XCD
             // range first, so no counter sees more than one XCD's workgroups.
+            stores_done();
             __syncthreads();
             if (threadIdx.x == 0) {
                 // counters restart at every launch (k_de_init / k_sync_reset)
@@ -1984,6 +1996,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))
             __syncthreads();
             if (s_last) {
                 de_step_body<true, true>(d, lds);
+                stores_done();  // (the next trials, by every wave)
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, PT_REL_SCOPE);
