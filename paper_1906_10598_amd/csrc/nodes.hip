@@ -382,7 +382,17 @@ struct FitShared {
     double S2, best_f;
     int stop[2];      // DeState flags of a stop, by generation parity
     int best, stop_gen;
+    int abandoned;    // generation after which the fit was abandoned, kNeverGen: not
 };
+constexpr int kNeverGen = 0x7fffffff;
+
+// Whether waves on the smallest set (kind 2) look for a stop in every generation.
+// A fit of a fixed number of generations is stopped there by nothing but its
+// abandonment, unless the launch (its last generation g1 - 1) reaches past its end;
+// its waves look for that every 8th generation, and leave together there.
+__device__ __forceinline__ bool stops_anywhere(const BlockDesc* d, int g1) {
+    return (d->rel_tol > 0.0 && d->window > 0) || d->vtr > -__builtin_inf() || g1 - 1 > d->max_gens;
+}
 
 // Coefficients of one candidate's phase difference (turns, in u) and its
 // amplitude A + B u.
@@ -718,6 +728,7 @@ struct LevelRule {
 template <int NV, bool WINDOW>
 struct Book {
     const NodeDesc* nd;
+    const BlockDesc* blk;
     const FitLds& l;
     FitShared& sh;
     int P, lane, win, max_gens, kind, pend;
@@ -727,7 +738,7 @@ struct Book {
     LevelRule rule;
 
     __device__ __forceinline__ Book(const NodeDesc* nd_, const BlockDesc* d, const FitLds& l_, FitShared& sh_)
-        : nd(nd_), l(l_), sh(sh_) {
+        : nd(nd_), blk(d), l(l_), sh(sh_) {
         P = d->P;
         lane = threadIdx.x & 63;
         win = d->window;
@@ -784,6 +795,7 @@ struct Book {
         if (lane == 0) {
             gst(hist + g, bf);
             sh.stop[g & 1] = flags;
+            if (flags == kFlagNodeAbort) sh.abandoned = g;
         }
         flags = __builtin_amdgcn_readfirstlane(flags);
         const bool look = (g & 15) == 14 && kind < 2 && pend < 0;  // takes effect at a multiple of 16
@@ -802,9 +814,11 @@ struct Book {
         return flags;
     }
     // the members' barriers, one generation behind them, and the last
-    // generation's books
+    // generation's books.  This wave leaves where the members do: two generations
+    // after a stop, or at the next multiple of 8 where they look no more often.
     __device__ __forceinline__ int run(int g0, int g1) {
-        int f2 = 0, f1 = 0;  // flags of generations g - 2 and g - 1
+        const bool stops = stops_anywhere(blk, g1);
+        int f2 = 0, f1 = 0;  // flags of generations g - 2 and g - 1; kept after a stop
         asm volatile(".p2align 6, , 60");  // (as the members' loop)
         for (int g = g0; g < g1; ++g) {
             if (pend == g) {
@@ -812,8 +826,11 @@ struct Book {
                 pend = -1;
                 kind = __builtin_amdgcn_readfirstlane(sh.lev.kind);
             }
-            if (f2) return g;
-            f1 = g > g0 ? step(g - 1, false) : 0;
+            if (f2) {
+                if (stops || kind < 2 || !(g & 7)) return g;
+            } else if (g > g0) {
+                f1 = step(g - 1, false);
+            }
             lds_barrier();
             f2 = f1;
         }
@@ -825,7 +842,8 @@ struct Book {
 // The generations of the members' waves.  A stop after generation g is found
 // while g + 1 runs and seen by every wave while it works on g + 2, before it
 // writes anything (where the flag's LDS read costs nothing): g + 2 is returned.
-// g1: the launch's generations are done.
+// g1: the launch's generations are done.  On the smallest set of a fit that only
+// its abandonment can stop, that is looked for at multiples of 8 (stops_anywhere).
 template <int NM, bool SLOPE, bool QUART, bool COR>
 struct Members {
     const NodeDesc* nd;
@@ -858,9 +876,7 @@ struct Members {
         mid_w = slot ? gld(&nd->mid[j]) : 0.0;
         sc = slot ? gld(&nd->sc[j]) : 0.0;
         en_w = node_energy(l.zw, K, N);
-        // (fits of a fixed number of generations are stopped by nothing but their
-        // abandonment, which may come late, unless the launch reaches past their end)
-        stops = (d->rel_tol > 0.0 && d->window > 0) || d->vtr > -__builtin_inf() || g1 - 1 > d->max_gens;
+        stops = stops_anywhere(d, g1);
         const double* x = l.xs + ((g0 + 1) & 1) * P * kRowD;
 #pragma unroll
         for (int t = 0; t < NM; ++t) {
@@ -1098,6 +1114,9 @@ struct Members {
                     relevel(nd, l, sh);
                     return false;
                 }
+                // (an abandonment after generation g - 1 may be on its way: not before the
+                // next look, for any wave)
+                if (!STOPS && __builtin_expect(__builtin_amdgcn_readfirstlane(sh.abandoned) <= g - 2, 0)) return true;
                 feed(g);
             }
             int side = 0;
@@ -1238,6 +1257,7 @@ __device__ __forceinline__ void fit_run(const NodeDesc* nd, const BlockDesc* d, 
     // a stop of the last generation but one, or of the last; otherwise the last is kept
     int flags = sh.stop[g & 1];
     if (g == g1 && !(ngen > 1 && flags)) flags = sh.stop[(g1 - 1) & 1];
+    if (sh.abandoned != kNeverGen) flags = kFlagNodeAbort;
 
     // state for the next launch: the population after the last kept generation
     const int gl = flags ? sh.stop_gen : g1 - 1;
@@ -1351,6 +1371,7 @@ __global__ __launch_bounds__(MAXT) void k_node_fit(const NodeDesc* __restrict__ 
             l.ring[g & (kNodeRing - 1)] = gld(d->hist + g);
     }
     if (tid < 2) sh.stop[tid] = 0;
+    if (tid == 0) sh.abandoned = kNeverGen;
     if (!fresh) __syncthreads();  // tab complete
     for (int k = tid; k < K; k += NT) l.un[k] = l.tab[2 * k + 1] + nd->c;
     __syncthreads();
