@@ -113,7 +113,7 @@ bool node_fits(int P, int maxK, int lds_max);
 __host__ __device__ inline int node_nm(int P) { return P <= 120 ? 1 : 2; }
 __host__ __device__ inline int node_waves(int P) { return (P + 8 * node_nm(P) - 1) / (8 * node_nm(P)); }
 __host__ __device__ inline size_t node_draw_words(int P, int gens) {
-    return (size_t)((gens + 30) / 16) * 128 * node_nm(P) * node_waves(P);
+    return gens ? (size_t)((gens + 30) / 16) * 128 * node_nm(P) * node_waves(P) : 0;
 }
 
 // Launches (nd / bd: device tables of nblk blocks; chunk: generations per

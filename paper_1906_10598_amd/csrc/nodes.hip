@@ -1525,6 +1525,8 @@ hipError_t node_moments(const NodeDesc* nd, const BlockDesc* bd, int nblk, int t
 hipError_t node_fit(const NodeDesc* nd, const BlockDesc* bd, int nblk, int P, int maxK, int off, int ngen, int next_ngen,
                     int chunk, int flip, bool cor, hipStream_t s) {
     const int nt = 64 * fit_waves(P);
+    // workgroups that make the next launch's draws: none without one (each would
+    // take the fit's LDS, the place of a fit in a batch larger than the chip)
     const int slices = (int)((node_draw_words(P, next_ngen) + nt - 1) / nt);
     const FitKernel k = fit_kernel(P, cor);
     hipLaunchKernelGGL(k, dim3((unsigned)(nblk + nblk * slices)), dim3((unsigned)nt),
