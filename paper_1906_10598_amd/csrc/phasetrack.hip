@@ -255,6 +255,7 @@ struct pt_ctx {
     // node-weight fits: descriptor tables, and weights, draws and the projection's working space
     DevBuf node_desc, node_ws;
     PinBuf hnode;
+    size_t node_bytes = SIZE_MAX;  // device bytes they may take at a time (pt_ctx_node_bytes_)
     int lds_max = 65536;  // LDS bytes one workgroup may hold
     // last fit (for pt_last_population / pt_last_history)
     int last_nblk = 0, last_P = 0, last_maxg = 0;
@@ -978,8 +979,15 @@ int run_direct(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<
 constexpr int kNodeGens = 2048, kNodeGensWindow = 512;
 constexpr size_t kNodeDrawBytes = (size_t)256 << 20;
 
+// Room for node weights.  Without it nothing is lost: PT_ENOMEM here sends the
+// fit over its samples.
+int node_room(const pt_ctx* ctx, DevBuf* buf, size_t bytes) {
+    if (bytes > ctx->node_bytes) return fail(PT_ENOMEM, "node weights: %zu bytes", bytes);
+    return buf->ensure(bytes);
+}
+
 // Fits of the blocks `idx` through node weights (plans[k] for idx[k]); rec[b]:
-// block b's record.
+// block b's record.  PT_ENOMEM: no room, nothing was launched.
 int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<int>& idx,
               const std::vector<NodePlan>& plans, const pt_de_settings* de, hipStream_t s,
               std::vector<FitRecord>* rec) {
@@ -993,12 +1001,16 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
     }
     int chunk = ctx->timing ? 1 : std::min(window ? kNodeGensWindow : kNodeGens, iters);
     chunk = std::min<int64_t>(chunk, std::max<int64_t>(16, kNodeDrawBytes / (node_draw_words(P, 1) * nblk)));
-    const size_t draws = (chunk < iters ? 2 : 1) * node_draw_words(P, chunk);  // (8 bytes each)
-    const size_t fixed = kNodeWtsDoubles + kNodeNarDoubles + draws;
+    size_t draws, fixed;
+    for (;; chunk = std::max(16, chunk / 4)) {
+        draws = (chunk < iters ? 2 : 1) * node_draw_words(P, chunk);  // (8 bytes each)
+        fixed = kNodeWtsDoubles + kNodeNarDoubles + draws;
+        rc = node_room(ctx, &ctx->node_ws, (work + fixed * nblk) * sizeof(double));
+        if (rc != PT_ENOMEM || chunk <= 16) break;  // (else more launches, each with fewer draws)
+    }
     const size_t ndb = (sizeof(NodeDesc) * nblk + 255) & ~(size_t)255, bdb = sizeof(BlockDesc) * nblk;
-    if ((rc = ensure_state(ctx, nall, de)) || (rc = ctx->node_ws.ensure((work + fixed * nblk) * sizeof(double))) ||
-        (rc = ctx->node_desc.ensure(ndb + bdb)) || (rc = ctx->hnode.ensure(ndb + bdb)) ||
-        (rc = ctx->errflag.ensure(sizeof(int))))
+    if (rc || (rc = node_room(ctx, &ctx->node_desc, ndb + bdb)) || (rc = ctx->hnode.ensure(ndb + bdb)) ||
+        (rc = ensure_state(ctx, nall, de)))
         return rc;
     NodeDesc* hn = static_cast<NodeDesc*>(ctx->hnode.p);
     BlockDesc* hb = reinterpret_cast<BlockDesc*>(static_cast<char*>(ctx->hnode.p) + ndb);
@@ -1111,10 +1123,16 @@ int run_fit(pt_ctx* ctx, const pt_block* given, int nblk, const pt_de_settings* 
     std::vector<FitRecord> rec(nblk);
     ctx->last_fit_launches = 0;
     if (!by_nodes.empty()) {
-        if ((rc = run_nodes(ctx, blocks.data(), nblk, by_nodes, plans, de, s, &rec))) return rc;
+        rc = run_nodes(ctx, blocks.data(), nblk, by_nodes, plans, de, s, &rec);
+        const bool room = rc != PT_ENOMEM;
+        if (rc && room) return rc;
         for (int b : by_nodes)  // abandoned: more signal to noise than the weights carry
-            if (rec[b].flags & kFlagNodeAbort) by_samples.push_back(b);
+            if (!room || rec[b].flags & kFlagNodeAbort) by_samples.push_back(b);
         std::sort(by_samples.begin(), by_samples.end());
+        if (!room) {
+            by_nodes.clear();
+            (void)hipGetLastError();  // (the allocation's, not for a later launch to report)
+        }
     }
     if (!by_samples.empty()) {
         const int64_t node_launches = ctx->last_fit_launches;
@@ -1727,6 +1745,10 @@ int pt_seed_box(const pt_seed* sd, int rule, double nsig, double T, int slope, p
 }
 
 // ------------------------------------------------------------ instrumentation
+// Device bytes one buffer of node weights may take in this context.  Not part of the
+// interface: tests have a fit find no room with it, without filling the device.
+void pt_ctx_node_bytes_(pt_ctx* ctx, uint64_t bytes) { ctx->node_bytes = bytes; }
+
 int pt_ctx_set_launch_mode(pt_ctx* ctx, int mode) {
     if (!ctx) return fail(PT_EINVAL, "ctx is null");
     if (mode != PT_LAUNCH_AUTO && mode != PT_LAUNCH_GRAPH && mode != PT_LAUNCH_PERSISTENT)
