@@ -2157,6 +2157,17 @@ int early_withdraw(pt_server* sv, pt_server::Pending& p) {
     return PT_OK;
 }
 
+// The device is full: everything held for blocks that wait goes first (but `keep`'s).
+int server_make_room(pt_server* sv, const pt_server::Pending* keep) {
+    (void)hipGetLastError();  // (the failed allocation's)
+    int rc;
+    for (auto& w : sv->pending)
+        if (&w != keep && w.dev.p && (rc = early_withdraw(sv, w))) return rc;
+    for (DevBuf& b : sv->spare) b.release();
+    sv->spare.clear();
+    return PT_OK;
+}
+
 int server_admit(pt_server* sv, hipStream_t s) {
     const int P = sv->cfg.de.pop;
     const int tile = kThreads * sv->geo.spl;
@@ -2197,12 +2208,7 @@ int server_admit(pt_server* sv, hipStream_t s) {
             return PT_OK;
         };
         if ((rc = ensure()) == PT_ENOMEM) {
-            // the device is full: everything held for blocks that wait goes first
-            (void)hipGetLastError();
-            for (auto& w : sv->pending)
-                if (&w != &*it && w.dev.p && (rc = early_withdraw(sv, w))) return rc;
-            for (DevBuf& b : sv->spare) b.release();
-            sv->spare.clear();
+            if ((rc = server_make_room(sv, &*it))) return rc;
             rc = ensure();
         }
         if (rc) return rc;
@@ -2258,30 +2264,50 @@ int server_admit(pt_server* sv, hipStream_t s) {
     return PT_OK;
 }
 
+// Room for the weights and draws of the blocks that start in this step, and for
+// working them out.  A block that finds none is fitted over its samples.
+int server_node_room(pt_server* sv, int K) {
+    const size_t draws = 2 * node_draw_words(sv->cfg.de.pop, std::min(kNodeGensWindow, K));  // (8 bytes each)
+    size_t work = 0;
+    bool tried = false;
+    int rc = PT_OK;
+    auto room = [&](DevBuf* b, size_t doubles) -> int {
+        int e = node_room(sv->ctx, b, doubles * sizeof(double));
+        if (e == PT_ENOMEM && !tried) {
+            tried = true;
+            if ((rc = server_make_room(sv, nullptr))) return e;
+            e = node_room(sv->ctx, b, doubles * sizeof(double));
+        }
+        if (e) (void)hipGetLastError();
+        return e;
+    };
+    for (auto& sl : sv->slots) {
+        if (!sl.active || !sl.fresh || !sl.nodes) continue;
+        sl.nodes = room(&sl.node, kNodeWtsDoubles + kNodeNarDoubles + draws) == PT_OK;
+        if (sl.nodes) work += sl.plan.pts_doubles + sl.plan.s2_doubles + sl.plan.mom_doubles;
+    }
+    if (room(&sv->node_ws, work) != PT_OK)
+        for (auto& sl : sv->slots)
+            if (sl.active && sl.fresh) sl.nodes = false;
+    return rc;
+}
+
 // One step of the node-weight blocks, act[0 .. nn) (the first nn_fresh new): K
 // generations, in launches of up to kNodeGensWindow.
 struct NodeStep {
     int nn = 0, nn_fresh = 0, chunk = 0, maxK = 0, proj = 0, mom = 0;
 };
 
-// Its descriptors (hn: host copy, one per block).
-int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, int K, NodeDesc* hn, NodeStep* step) {
-    const int P = sv->cfg.de.pop, chunk = std::min(kNodeGensWindow, K);
-    const size_t draws = 2 * node_draw_words(P, chunk);  // (8 bytes each)
-    size_t work = 0;
-    int maxK = 0, proj = 0, mom = 0, rc;
-    for (int q = 0; q < nn; ++q) {
-        const NodePlan& p = sv->slots[act[q]].plan;
-        maxK = std::max(maxK, p.nd.K);
-        if (q < nn_fresh) work += p.pts_doubles + p.s2_doubles + p.mom_doubles;
-    }
-    if ((rc = sv->node_ws.ensure(work * sizeof(double)))) return rc;
+// Its descriptors (hn: host copy, one per block; server_node_room has made the room).
+NodeStep server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fresh, int K, NodeDesc* hn) {
+    const int chunk = std::min(kNodeGensWindow, K);
+    int maxK = 0, proj = 0, mom = 0;
     double* ws = static_cast<double*>(sv->node_ws.p);
     for (int q = 0; q < nn; ++q) {
         pt_server::Slot& sl = sv->slots[act[q]];
         NodeDesc n = sl.plan.nd;
+        maxK = std::max(maxK, n.K);
         if (q < nn_fresh) {
-            if ((rc = sl.node.ensure((kNodeWtsDoubles + kNodeNarDoubles + draws) * sizeof(double)))) return rc;
             sl.parity = 0;
             n.proj_begin = proj;
             n.mom_begin = mom;
@@ -2301,8 +2327,7 @@ int server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn_fres
         n.rec = static_cast<FitRecord*>(sv->hrec.p) + q;
         hn[q] = n;
     }
-    *step = NodeStep{nn, nn_fresh, chunk, maxK, proj, mom};
-    return PT_OK;
+    return NodeStep{nn, nn_fresh, chunk, maxK, proj, mom};
 }
 
 // Its launches (nd, dd: the step's descriptors on the device).
@@ -2473,7 +2498,7 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
     HIPCHK(hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     int rc = server_admit(sv, s);
-    if (rc) return rc;
+    if (rc || (rc = server_node_room(sv, sv->cfg.gens_per_step))) return rc;
     // active slots: those fitted through node weights first (new ones leading),
     // then the others grouped by objective kernel (arithmetic, dtype, slope)
     auto kernel_key = [&](int k) {
@@ -2596,9 +2621,8 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
     }
     const int K = sv->cfg.gens_per_step;
     NodeStep step;
-    if (nn && (rc = server_nodes(sv, act, nn, nn_fresh, K, reinterpret_cast<NodeDesc*>(static_cast<char*>(sv->hdesc.p) + bdb),
-                                 &step)))
-        return rc;
+    if (nn)
+        step = server_nodes(sv, act, nn, nn_fresh, K, reinterpret_cast<NodeDesc*>(static_cast<char*>(sv->hdesc.p) + bdb));
     HIPCHK(hipMemcpyAsync(sv->desc.p, hd, bdb + sizeof(NodeDesc) * nn, hipMemcpyHostToDevice, s));
     const BlockDesc* dd = static_cast<const BlockDesc*>(sv->desc.p);
     const size_t de_lds = (size_t)P * kSlots * 8 + (size_t)de_threads * (8 + 8 + 4);

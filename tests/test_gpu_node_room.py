@@ -52,3 +52,38 @@ def test_little_room_takes_more_launches(room):
     room(300_000)
     _same([_fit([pb], de)[0]], want)
     assert ptk.pt_ctx_fit_launches(ctx().handle) > 3
+
+
+@pytest.mark.parametrize("lead", [False, True])
+@pytest.mark.parametrize("room_bytes", [0, 100_000])
+def test_served_blocks_without_room_run_over_their_samples(room, lead, room_bytes):
+    """No room at all, and room for a block's weights (50 KB with the draws of 2 x 8
+    generations) but not for working three blocks' out at once (74 tiles or more of 16
+    points and 10 groups of 96 moments, 32 bytes each: 68 KB a block)."""
+    bs = [synth.config1(k, n=300_000 + 1111 * k) for k in range(3)]
+    devs = [to_dev(b.samples) for b in bs]
+    pbs = [block_of(b, d) for b, d in zip(bs, devs)]
+    de = settings_of(bs[0], gens=70)
+    c = ctx()
+    ptk.pt_ctx_set_tile(c.handle, 16, 4)  # the server's geometry
+    try:
+        want = [_fit([pb], de, ptk.PT_LAUNCH_GRAPH)[0][0] for pb in pbs]
+    finally:
+        ptk.pt_ctx_set_tile(c.handle, 0, 0)
+    ptk.pt_ctx_set_step_fusion(c.handle, ptk.PT_FUSION_LEAD if lead else ptk.PT_FUSION_AUTO)
+    srv = ptk.pt_server_create(c.handle, ptk.make_server_config(de, max_slots=4, gens_per_step=8))
+    ptk.pt_ctx_set_step_fusion(c.handle, ptk.PT_FUSION_AUTO)
+    try:
+        room(room_bytes)
+        order = {ptk.pt_server_submit(srv, k, pb): k for k, pb in enumerate(pbs)}
+        got = {}
+        for _ in range(30):
+            ptk.pt_server_step(srv, ptk.current_stream())
+            for r in ptk.pt_server_poll(srv):
+                got[order[r.ticket]] = r.fit
+        for k, w in enumerate(want):
+            f = got[k]
+            assert list(f.coef) == list(w.coef), k
+            assert (f.objective, f.generations, f.flags) == (w.objective, w.generations, w.flags), k
+    finally:
+        ptk.pt_server_destroy(srv)
