@@ -1950,6 +1950,7 @@ struct pt_server {
         // node-weight fits: the block's plan, its weights and draws (two chunks),
         // and the half of the draws the next launch reads
         bool nodes = false;
+        bool over = false;  // more signal to noise than node weights carry (a fit was abandoned)
         NodePlan plan{};
         DevBuf node;
         int parity = 0;
@@ -1965,6 +1966,7 @@ struct pt_server {
     };
     struct Track {
         bool busy = false, has_fit = false;
+        bool over = false;        // the last block's signal to noise: no node weights for the next
         bool contiguous = false;  // the most recent block was accepted (it is `last`)
         pt_fit last{};            // last accepted fit
         double t_since = 0.0;     // seconds from last's reference sample to the end of the latest block
@@ -2029,11 +2031,12 @@ int slot_mode(const pt_server* sv, const pt_block& b) {
                : kModePoly;
 }
 
-// How a block's fit runs, from its own box only: through node weights, or by
-// evaluating its samples in the arithmetic of slot_mode.
+// How a block's fit runs, from its own box (and what is known of its signal to
+// noise): through node weights, or by evaluating its samples in the arithmetic of
+// slot_mode.
 void slot_form(const pt_server* sv, pt_server::Slot& sl) {
     sl.mode = slot_mode(sv, sl.blk);
-    sl.nodes = nodes_allowed(sv->ctx) && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan) &&
+    sl.nodes = !sl.over && nodes_allowed(sv->ctx) && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan) &&
                node_fits(sv->cfg.de.pop, sl.plan.nd.K, sv->ctx->lds_max);
 }
 
@@ -2239,6 +2242,7 @@ int server_admit(pt_server* sv, hipStream_t s) {
                 }
             sl.warm = 2;
         }
+        sl.over = tr.over;
         slot_form(sv, sl);
         sl.attempts = 1;
         sl.active = true;
@@ -2687,8 +2691,10 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         }
         if (sl.nodes && (cur.flags & kFlagNodeAbort)) {
             // more signal to noise than node weights carry: the same fit again
-            // over the samples
+            // over the samples, as any retry of this block and the track's next
+            // blocks (an attempt that is abandoned costs a step)
             sl.nodes = false;
+            sl.over = true;
             sl.fresh = true;
             sl.gen = 0;
             ++still;
@@ -2754,6 +2760,9 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         sv->done.push_back(res);
         pt_server::Track& tr = sv->tracks[sl.track];
         tr.busy = false;
+        // (back to node weights once the fitted signal lies 3 dB below the limit)
+        tr.over = sl.over && de.objective == PT_OBJ_CHI2 &&
+                  f.objective < 2.0 * kNodeCancel * (f.objective + 0.5 * (double)sl.blk.n * f.coef[0] * f.coef[0]);
         if (!failed) {
             tr.has_fit = true;
             tr.contiguous = true;
