@@ -420,11 +420,13 @@ typedef struct {
     double border_dfreq;
 } pt_server_result;
 
-/* Create a server on ctx.  Its generations run as objective + DE step
- * launches, or, when the context's step fusion is PT_FUSION_LEAD at this
- * call (and pop <= 256), as one leading-step launch per generation for every
- * resident block; the choice holds for the server's lifetime.  Both give
- * bit-identical fits. */
+/* Create a server on ctx.  Blocks are fitted through node weights where those
+ * apply when the context's launch mode is PT_LAUNCH_AUTO at this call (an FP64
+ * method of PT_FP64_POLY set later still holds for blocks that start after
+ * it).  The generations of the others run as objective + DE step launches, or,
+ * when the context's step fusion is PT_FUSION_LEAD at this call (and pop <=
+ * 256), as one leading-step launch per generation for every resident block;
+ * both give bit-identical fits.  The choices hold for the server's lifetime. */
 int pt_server_create(pt_ctx* ctx, const pt_server_config* cfg, pt_server** out);
 
 /* Destroy a server (its queued and running blocks are dropped). */

@@ -1932,6 +1932,7 @@ int pt_ctx_autotune(pt_ctx* ctx, int64_t n, int P, int precision, void* hip_stre
 // fit (warm start).
 struct pt_server {
     bool lead = false;  // leading-step launches (the context's step fusion was PT_FUSION_LEAD at creation)
+    bool nodes = false;  // node weights where they apply (its launch mode was PT_LAUNCH_AUTO)
     struct Slot {
         bool active = false, fresh = false;
         int track = -1;
@@ -2036,7 +2037,7 @@ int slot_mode(const pt_server* sv, const pt_block& b) {
 // slot_mode.
 void slot_form(const pt_server* sv, pt_server::Slot& sl) {
     sl.mode = slot_mode(sv, sl.blk);
-    sl.nodes = !sl.over && nodes_allowed(sv->ctx) && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan) &&
+    sl.nodes = !sl.over && sv->nodes && sv->ctx->fp64_method == PT_FP64_AUTO && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan) &&
                node_fits(sv->cfg.de.pop, sl.plan.nd.K, sv->ctx->lds_max);
 }
 
@@ -2436,6 +2437,7 @@ int pt_server_create(pt_ctx* ctx, const pt_server_config* cfg, pt_server** out) 
     if (sv->cfg.max_attempts == 0) sv->cfg.max_attempts = 1;
     sv->geo = cfg->spl ? Geometry{cfg->spl, cfg->cpg} : default_geometry(400000, cfg->de.pop);
     sv->lead = ctx->step_fusion == PT_FUSION_LEAD;
+    sv->nodes = ctx->launch_mode == PT_LAUNCH_AUTO;
     sv->slots.resize(cfg->max_slots);
     *out = sv.release();
     return PT_OK;

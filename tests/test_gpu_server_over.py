@@ -1,6 +1,7 @@
-"""Served blocks with more signal to noise than node weights carry: their fit is
-run again over the samples, and retries and the track's next blocks go there
-at once.
+"""The route of served blocks.  Those with more signal to noise than node weights
+carry: their fit is run again over the samples, and retries and the track's next
+blocks go there at once.  Otherwise the launch mode that a server was created
+with decides.
 """
 import numpy as np
 import pytest
@@ -80,3 +81,26 @@ def test_retries_of_a_block_past_the_limit(lead):
     assert r.attempts == 2 and abs(r.fit.coef[0] - b.truth[0]) < 1e-3
     # tried through nodes once, then over the samples in the first box and the second
     assert steps == 3
+
+
+@pytest.mark.parametrize("created,later", [(ptk.PT_LAUNCH_AUTO, ptk.PT_LAUNCH_GRAPH),
+                                           (ptk.PT_LAUNCH_GRAPH, ptk.PT_LAUNCH_AUTO)])
+def test_the_launch_mode_at_creation_holds(created, later):
+    b = _block(20_000, dtype=np.float64)
+    pb = block_of(b, to_dev(b.samples))
+    de = settings_of(b, gens=150)
+    c = ctx()
+    ptk.pt_ctx_set_tile(c.handle, 16, 4)  # the server's geometry
+    try:
+        want = {m: _key(_fit([pb], de, m)[0][0]) for m in (created, later)}
+    finally:
+        ptk.pt_ctx_set_tile(c.handle, 0, 0)
+    assert want[created] != want[later]
+    ptk.pt_ctx_set_launch_mode(c.handle, created)
+    srv = _server(de, False)
+    try:
+        ptk.pt_ctx_set_launch_mode(c.handle, later)
+        assert _key(_serve(srv, 0, pb)[0].fit) == want[created]
+    finally:
+        ptk.pt_ctx_set_launch_mode(c.handle, ptk.PT_LAUNCH_AUTO)
+        ptk.pt_server_destroy(srv)
