@@ -467,11 +467,11 @@ double pt_server_clock(pt_server* srv);
  *     n of 64 to 2^26, P <= 240, K <= 512 and an FP64 method of
  *     PT_FP64_AUTO; the choice depends on the block and P only.  The chi-square
  *     comes as a difference from the samples' energy, so a fit whose best
- *     falls below 1/1000 of it (30 dB of signal to noise), or whose samples are
- *     not finite, is run again over its samples (a server takes that block's
- *     retries, and the track's next blocks until one's fit lies 3 dB below,
- *     over their samples at once); so is one that finds no device memory for
- *     its weights.
+ *     falls below 1/16 of it (12 dB of signal to noise; mixed precision 1/1000,
+ *     30 dB), or whose samples are not finite, is run again over its samples (a
+ *     server takes that block's retries, and the track's next blocks until one's
+ *     fit lies 3 dB below, over their samples at once); so is one that finds no
+ *     device memory for its weights.
  *   PT_LAUNCH_PERSISTENT: one cooperative grid runs every generation of
  *     every block; workgroups keep their sample chunks in registers, and the
  *     workgroup that completes a block's generation runs its DE step (no

@@ -52,10 +52,16 @@ constexpr int kNodeLevelHead = 48;  // doubles before a saved re-expanded set's 
 // largest |delta| (turns) of the sets of 16 and 8 nodes: the range of their
 // sine and cosine polynomials
 constexpr double kNodeTurns16 = 1.0 / 8, kNodeTurns8 = 1.0 / 48;
-// chi-square is taken as S2 - ..., so it carries rounding of ~1e-16 S2: a fit
-// whose best falls below kNodeCancel * S2 (30 dB of signal to noise) is
-// abandoned and run through the per-sample objective
-constexpr double kNodeCancel = 1e-3;
+// Chi-square is taken as a difference from S2, so its error is a few ulp of S2 and
+// its relative error grows with the signal to noise: a fit whose best falls below
+// this share of S2 is abandoned and run over its samples.  FP64: 12 dB.  Rms error
+// relative to chi-square, nodes / samples: up to 10 dB 6e-15 or less / 7e-15 to
+// 1e-13 (carriers of tens of Hz and more, n = 256 to 1e5); at 13 dB 1.9e-14 / 4e-15
+// for 256 samples whose phase covers 30 turns, 1.4e-14 / 2.2e-14 for 20 000; at 28 dB
+// 3.7e-13 / 1.2e-13 for those.  (Where the phase stays within a few turns, a carrier
+// near zero, the samples' sums are exact to 2e-16 at any signal to noise.)  Mixed: 30
+// dB, its sums over the samples are off by 1e-9 and more.
+__host__ __device__ constexpr double node_cancel(bool mixed) { return mixed ? 1e-3 : 1.0 / 16; }
 enum { kFlagNodeAbort = 1 << 16 };  // DeState::flags of an abandoned fit
 
 struct DeState;
@@ -70,6 +76,7 @@ struct NodeDesc {
     // slot -> coefficient of u = m / h: (value - mid) * sc (turns; amplitude units for slots 0 and 5)
     double mid[kSlots], sc[kSlots];
     double su1, su2;   // sum over samples of u and u^2 (energy of a sloping amplitude)
+    double cancel;     // node_cancel of the fit's precision
     int K;             // nodes, a multiple of 16
     int slope;         // the amplitude slope is active
     int lanes_log;     // log2 of the lanes (16 samples each) sharing a tile
@@ -92,7 +99,7 @@ struct NodeDesc {
 };
 
 struct NodePlan {
-    NodeDesc nd;       // everything but the pointers, prefixes, g0 and parity
+    NodeDesc nd;       // everything but the pointers, prefixes, limit, g0 and parity
     size_t pts_doubles, s2_doubles, mom_doubles;  // working space of the projection
 };
 constexpr size_t kNodeWtsDoubles = 4 * kNodeMaxK + 2;

@@ -745,7 +745,7 @@ struct Book {
         max_gens = d->max_gens;
         vtr = d->vtr;
         rel_tol = d->rel_tol;
-        floor = d->objective == 0 ? kNodeCancel * sh.S2 : -__builtin_inf();
+        floor = d->objective == 0 ? nd_->cancel * sh.S2 : -__builtin_inf();
         F = d->F;
         hist = d->hist;
         kind = __builtin_amdgcn_readfirstlane(sh.lev.kind);

@@ -1020,6 +1020,7 @@ int run_nodes(pt_ctx* ctx, const pt_block* blocks, int nall, const std::vector<i
         hb[k] = base_desc(blocks[idx[k]], de, 0, 0);
         set_state(ctx, idx[k], de->max_gens, &hb[k]);
         NodeDesc n = plans[k].nd;
+        n.cancel = node_cancel(de->precision == PT_PREC_MIXED);
         n.proj_begin = proj;
         n.mom_begin = mom;
         proj += n.nproj;
@@ -2311,6 +2312,7 @@ NodeStep server_nodes(pt_server* sv, const std::vector<int>& act, int nn, int nn
     for (int q = 0; q < nn; ++q) {
         pt_server::Slot& sl = sv->slots[act[q]];
         NodeDesc n = sl.plan.nd;
+        n.cancel = node_cancel(sv->cfg.de.precision == PT_PREC_MIXED);
         maxK = std::max(maxK, n.K);
         if (q < nn_fresh) {
             sl.parity = 0;
@@ -2764,7 +2766,8 @@ int pt_server_step(pt_server* sv, void* hip_stream, int32_t* n_active, int32_t* 
         tr.busy = false;
         // (back to node weights once the fitted signal lies 3 dB below the limit)
         tr.over = sl.over && de.objective == PT_OBJ_CHI2 &&
-                  f.objective < 2.0 * kNodeCancel * (f.objective + 0.5 * (double)sl.blk.n * f.coef[0] * f.coef[0]);
+                  f.objective < 2.0 * node_cancel(de.precision == PT_PREC_MIXED) *
+                                    (f.objective + 0.5 * (double)sl.blk.n * f.coef[0] * f.coef[0]);
         if (!failed) {
             tr.has_fit = true;
             tr.contiguous = true;
