@@ -392,7 +392,8 @@ typedef struct {
     uint64_t hbm_budget_bytes;  /* device bytes resident blocks may hold; a block of n samples
                                    holds n * sizeof(sample) + (max_gens + 1) * 8 + 2 * (P * 136 +
                                    P * ntiles * 8 + 48), ntiles = ceil(n / (256 * spl)): samples,
-                                   history and two slots of rows, objectives, partials and state;
+                                   history and two slots of rows, objectives, partials and state
+                                   (sample buffers kept for blocks to come stay within it, too);
                                    node weights and draws (30 KB + 16 P, P rounded up to 8 or above
                                    120 to 16, per generation of a step, at most 512, and 30 more)
                                    and the working space of one step's new blocks are not counted */

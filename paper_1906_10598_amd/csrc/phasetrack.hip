@@ -2085,6 +2085,26 @@ int seed_fits(const pt_block* b, int M) {
     return PT_OK;
 }
 
+// Sample buffers that no block holds (spare, or a free slot's) go, the smallest
+// first, until `bytes` more fit the budget beside them and the blocks' own (keep:
+// one that is among those bytes).
+void trim_idle(pt_server* sv, size_t bytes, const DevBuf* keep) {
+    std::vector<DevBuf*> idle;
+    for (DevBuf& b : sv->spare) idle.push_back(&b);
+    for (auto& sl : sv->slots)
+        if (!sl.active && sl.samples.p && &sl.samples != keep) idle.push_back(&sl.samples);
+    std::sort(idle.begin(), idle.end(), [](const DevBuf* x, const DevBuf* y) { return x->cap < y->cap; });
+    size_t held = sv->used_bytes + sv->early_bytes + bytes;
+    for (const DevBuf* b : idle) held += b->cap;
+    for (DevBuf* b : idle) {
+        if (held <= sv->cfg.hbm_budget_bytes) break;
+        held -= b->cap;
+        b->release();
+    }
+    sv->spare.erase(std::remove_if(sv->spare.begin(), sv->spare.end(), [](const DevBuf& b) { return !b.p; }),
+                    sv->spare.end());
+}
+
 // A buffer for a waiting block's samples: a spare one or a free slot's, the
 // smallest that holds them, else a new one (and then a spare one too small goes,
 // so there are never more than blocks have been on the device at a time).
@@ -2099,11 +2119,8 @@ bool early_buffer(pt_server* sv, size_t bytes, DevBuf* out) {
     if (best) {
         std::swap(*out, *best);
     } else {
-        for (DevBuf& b : sv->spare)
-            if (b.p) {
-                b.release();
-                break;
-            }
+        if (!sv->spare.empty()) sv->spare.front().release();
+        trim_idle(sv, bytes, nullptr);
         if (hipMalloc(&out->p, std::max(bytes, (size_t)256)) != hipSuccess) {
             out->p = nullptr;
             (void)hipGetLastError();
@@ -2202,6 +2219,7 @@ int server_admit(pt_server* sv, hipStream_t s) {
             --w;
             if (w != it && w->dev.p && (rc = early_withdraw(sv, *w))) return rc;
         }
+        trim_idle(sv, early ? need - sbytes : need, early ? nullptr : &sl.samples);
         // two slots of the DE buffers (the leading-step form alternates between them)
         auto ensure = [&]() -> int {
             int e;
