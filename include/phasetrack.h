@@ -559,8 +559,10 @@ int pt_ctx_last_geometry(pt_ctx* ctx, int* samples_per_lane, int* cand_per_group
 
 /* Objective-kernel launches of the context's most recent fit (all blocks of
  * a batch share them): one per generation including generation 0, plus one
- * for the last DE step in the leading-step form; 1 for a persistent launch; one
- * per up to 500 generations through node weights.
+ * for the last DE step in the leading-step form; 1 for a persistent launch;
+ * through node weights one per up to 2048 generations, 512 with the window rule
+ * (more with little device memory, and those of the run over the samples if
+ * that follows).
  * A fit that stopped early by the window rule may have run fewer. */
 int pt_ctx_last_fit_launches(pt_ctx* ctx, int64_t* launches);
 

@@ -1209,9 +1209,9 @@ int pt_ctx_create(int device, pt_ctx** out) {
         lds_max = 65536;
     c->lds_max = lds_max;
     HIPCHK(node_setup(lds_max));
-    // 16 bytes of LDS per snippet sample plus the kernel's 1 KiB of reduction space
+    // 8 bytes of LDS per snippet sample, and up to 1 KiB of fixed size
     for (int lg = kSeedMaxLog; lg >= 6; --lg)
-        if ((16 << lg) + 1024 <= lds_max) {
+        if ((8 << lg) + 1024 <= lds_max) {
             c->seed_max_log = lg;
             break;
         }
@@ -1397,7 +1397,7 @@ static EvalPlan eval_plan(pt_ctx* ctx, const pt_block& blk, int P, int precision
     // places) rounds, each of the candidates, about one more per group for its
     // reduction and four for the set-up.  The group size is chosen along with it
     // unless it was set or tuned (it changes no sum).
-    const int64_t places = 256 * (e.geo.spl == 32 ? 2 : e.geo.spl == 16 ? 3 : 4);
+    const int64_t places = ctx->ncu * (e.geo.spl == 32 ? 2 : e.geo.spl == 16 ? 3 : 4);
     const bool given = ctx->forced.spl || ctx->tuned.count(std::make_tuple(size_class(blk.n), P, (int)mixed));
     const int cpg0 = e.geo.cpg;
     int64_t best = INT64_MAX;

@@ -25,7 +25,7 @@
 namespace pt {
 
 constexpr int kSeedThreads = 1024;
-constexpr int kSeedMaxLog = 13;  // M <= 8192 (128 KiB of FP64 complex LDS)
+constexpr int kSeedMaxLog = 13;  // M <= 8192 (64 KiB of LDS: M / 2 complex numbers)
 
 struct SeedSnippet {
     double f;      // Hz
