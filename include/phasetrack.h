@@ -466,7 +466,8 @@ double pt_server_clock(pt_server* srv);
  *     at its start and then runs its generations, one workgroup per block,
  *     without touching the samples again.  Taken for every block it carries:
  *     n of 64 to 2^26, P <= 240, K <= 512 and an FP64 method of
- *     PT_FP64_AUTO; the choice depends on the block and P only.  The chi-square
+ *     PT_FP64_AUTO, unless the fit is so short that its many nodes do not pay;
+ *     the choice depends on the block, P and max_gens only.  The chi-square
  *     comes as a difference from the samples' energy, so a fit whose best
  *     falls below 1/16 of it (12 dB of signal to noise; mixed precision 1/1000,
  *     30 dB), or whose samples are not finite, is run again over its samples (a

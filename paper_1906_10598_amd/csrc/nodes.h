@@ -106,8 +106,9 @@ constexpr size_t kNodeWtsDoubles = 4 * kNodeMaxK + 2;
 constexpr size_t kNodeNarDoubles = kNodeLevelHead + 5 * (kNodeMaxK / 8 * 5);
 
 // Whether a block's fits go through node weights, and its plan: depends on
-// the block (length, rate, reference, box) and the population size only.
-bool node_plan(const pt_block& b, double ref, int P, NodePlan* out);
+// the block (length, rate, reference, box), the population size and the
+// generations only.
+bool node_plan(const pt_block& b, double ref, int P, int max_gens, NodePlan* out);
 
 // Dynamic LDS bytes of k_node_fit for population P and nodes up to maxK, and
 // whether the device has them.
@@ -121,6 +122,22 @@ __host__ __device__ inline int node_nm(int P) { return P <= 120 ? 1 : 2; }
 __host__ __device__ inline int node_waves(int P) { return (P + 8 * node_nm(P) - 1) / (8 * node_nm(P)); }
 __host__ __device__ inline size_t node_draw_words(int P, int gens) {
     return gens ? (size_t)((gens + 30) / 16) * 128 * node_nm(P) * node_waves(P) : 0;
+}
+
+// Whether a fit is shorter through K nodes than over n samples, both without what
+// they share.  Only a few generations on many nodes are not: sets shrink after some
+// 40, while a generation over the samples of a small block has the whole chip.  In
+// microseconds, fitted to single fits of 2 to 501 generations, 8 to 240 members, 512
+// to 4e5 samples and 48 to 464 nodes (nodes / samples: 464 nodes, P = 40, 5e4 samples
+// 101 / 56 for 2 generations, 266 / 191 for 21, 536 / 784 for 101; 256 nodes, P = 240,
+// 4096 samples 482 / 203 for 21, 1415 / 3692 for 501; 112 nodes, P = 40 52 / 49 for 2,
+// 97 / 147 for 21): of 480 fits the rule leaves five slower, by 7 to 22.
+inline bool node_pays(int K, int64_t n, int P, int max_gens) {
+    const double G = max_gens + 1.0, W = node_waves(P);
+    const double per_simd = W * node_nm(P) / 4;  // members of an octet, on the fullest SIMD
+    const double gen = 0.0093 * K * (per_simd > 1 ? (double)(int64_t)(per_simd + 0.75) : 1.3);
+    const double nodes = 0.06 * P + 1e-3 * K * K / (W + 1) + (G < 40 ? G : 40) * gen;
+    return nodes <= 2.4 + G * (5.1 + 7e-7 * P * (double)n);
 }
 
 // Launches (nd / bd: device tables of nblk blocks; chunk: generations per

@@ -1420,7 +1420,7 @@ double nodes_needed(const double* b, int extra) {
 
 }  // namespace
 
-bool node_plan(const pt_block& B, double ref, int P, NodePlan* out) {
+bool node_plan(const pt_block& B, double ref, int P, int max_gens, NodePlan* out) {
     if (P > kNodeMaxP || B.n < 64 || B.n > (int64_t)1 << 26) return false;
     const double N = (double)B.n, h = 0.5 * (N - 1.0), c = (h - ref) / h, fs = B.fs;
     NodeDesc nd{};
@@ -1455,6 +1455,7 @@ bool node_plan(const pt_block& B, double ref, int P, NodePlan* out) {
     if (!(k <= (double)kNodeMaxK)) return false;
     nd.K = ((int)std::ceil(k) + 15) & ~15;
     if (nd.K < 16) nd.K = 16;
+    if (!node_pays(nd.K, B.n, P, max_gens)) return false;
 
     // tiles: the longest (up to a workgroup's 4096 samples, or more of them for
     // long blocks, so that a block takes at most 1024 projection workgroups) in

@@ -1113,7 +1113,7 @@ int run_fit(pt_ctx* ctx, const pt_block* given, int nblk, const pt_de_settings* 
     std::vector<NodePlan> plans;
     for (int b = 0; b < nblk; ++b) {
         NodePlan p;
-        if (!direct && nodes_allowed(ctx) && node_plan(blocks[b], block_ref(&blocks[b]), de->pop, &p) &&
+        if (!direct && nodes_allowed(ctx) && node_plan(blocks[b], block_ref(&blocks[b]), de->pop, de->max_gens, &p) &&
             node_fits(de->pop, p.nd.K, ctx->lds_max)) {
             by_nodes.push_back(b);
             plans.push_back(p);
@@ -2038,7 +2038,8 @@ int slot_mode(const pt_server* sv, const pt_block& b) {
 // slot_mode.
 void slot_form(const pt_server* sv, pt_server::Slot& sl) {
     sl.mode = slot_mode(sv, sl.blk);
-    sl.nodes = !sl.over && sv->nodes && sv->ctx->fp64_method == PT_FP64_AUTO && node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, &sl.plan) &&
+    sl.nodes = !sl.over && sv->nodes && sv->ctx->fp64_method == PT_FP64_AUTO &&
+               node_plan(sl.blk, sl.blk.ref, sv->cfg.de.pop, sv->cfg.de.max_gens, &sl.plan) &&
                node_fits(sv->cfg.de.pop, sl.plan.nd.K, sv->ctx->lds_max);
 }
 
