@@ -389,7 +389,9 @@ constexpr int kNeverGen = 0x7fffffff;
 // Whether waves on the smallest set (kind 2) look for a stop in every generation.
 // A fit of a fixed number of generations is stopped there by nothing but its
 // abandonment, unless the launch (its last generation g1 - 1) reaches past its end;
-// its waves look for that every 8th generation, and leave together there.
+// its waves look for that every kAbandonLook generations, and leave together there
+// (every 8th cost 0.7 % of a fit of 2000: an LDS read on the chain).
+constexpr int kAbandonLook = 64;
 __device__ __forceinline__ bool stops_anywhere(const BlockDesc* d, int g1) {
     return (d->rel_tol > 0.0 && d->window > 0) || d->vtr > -__builtin_inf() || g1 - 1 > d->max_gens;
 }
@@ -815,7 +817,7 @@ struct Book {
     }
     // the members' barriers, one generation behind them, and the last
     // generation's books.  This wave leaves where the members do: two generations
-    // after a stop, or at the next multiple of 8 where they look no more often.
+    // after a stop, or at the next multiple of kAbandonLook where they look no more often.
     __device__ __forceinline__ int run(int g0, int g1) {
         const bool stops = stops_anywhere(blk, g1);
         int f2 = 0, f1 = 0;  // flags of generations g - 2 and g - 1; kept after a stop
@@ -827,7 +829,7 @@ struct Book {
                 kind = __builtin_amdgcn_readfirstlane(sh.lev.kind);
             }
             if (f2) {
-                if (stops || kind < 2 || !(g & 7)) return g;
+                if (stops || kind < 2 || !(g & (kAbandonLook - 1))) return g;
             } else if (g > g0) {
                 f1 = step(g - 1, false);
             }
@@ -843,7 +845,7 @@ struct Book {
 // while g + 1 runs and seen by every wave while it works on g + 2, before it
 // writes anything (where the flag's LDS read costs nothing): g + 2 is returned.
 // g1: the launch's generations are done.  On the smallest set of a fit that only
-// its abandonment can stop, that is looked for at multiples of 8 (stops_anywhere).
+// its abandonment can stop, that is looked for seldom (stops_anywhere).
 template <int NM, bool SLOPE, bool QUART, bool COR>
 struct Members {
     const NodeDesc* nd;
@@ -1116,7 +1118,9 @@ struct Members {
                 }
                 // (an abandonment after generation g - 1 may be on its way: not before the
                 // next look, for any wave)
-                if (!STOPS && __builtin_expect(__builtin_amdgcn_readfirstlane(sh.abandoned) <= g - 2, 0)) return true;
+                if (!STOPS && !(g & (kAbandonLook - 1)) &&
+                    __builtin_expect(__builtin_amdgcn_readfirstlane(sh.abandoned) <= g - 2, 0))
+                    return true;
                 feed(g);
             }
             int side = 0;

@@ -8,9 +8,14 @@ The waves run in lockstep from barrier to barrier; what the books write during a
 generation is seen by a member either before or after, so both are tried.
 """
 import itertools
+import os
+import re
 
 import pytest
 
+from paper_1906_10598_amd import build
+
+LOOK = int(re.search(r"kAbandonLook = (\d+);", open(os.path.join(build.CSRC, "nodes.hip")).read()).group(1))
 NEVER = 1 << 30
 STOP, ABANDONED = 4, 1 << 16
 
@@ -38,7 +43,7 @@ def leaves(g0, g1, first2, stops, stop_at, flag, early):
         # the books
         writes, new_abandoned, book_leaves = [], NEVER, False
         if f2:
-            book_leaves = stops or kind < 2 or not g & 7
+            book_leaves = stops or kind < 2 or not g & (LOOK - 1)
         elif g > g0:
             f1, writes, new_abandoned = step(g - 1)
         # the members: on what is written before this generation, or also during it
@@ -48,7 +53,7 @@ def leaves(g0, g1, first2, stops, stop_at, flag, early):
                 seen[k] = v
             seen_ab = min(seen_ab, new_abandoned)
         if kind == 2 and not stops:
-            member_leaves = not g & 7 and seen_ab <= g - 2
+            member_leaves = not g & (LOOK - 1) and seen_ab <= g - 2
         else:
             member_leaves = g > g0 + 1 and seen[g & 1] != 0
         for k, v in writes:
@@ -79,7 +84,8 @@ def leaves(g0, g1, first2, stops, stop_at, flag, early):
 @pytest.mark.parametrize("stops", [False, True])
 @pytest.mark.parametrize("early", [False, True])
 def test_all_waves_leave_together(stops, early):
-    for g0, ngen, first2 in itertools.product(range(0, 34), (1, 2, 3, 7, 8, 9, 16, 17, 40), (0, 16, 32, 48, NEVER)):
+    for g0, ngen, first2 in itertools.product((*range(0, 34), LOOK - 1, LOOK, LOOK + 1), (1, 2, 3, 7, 8, 9, 16, 17, 40, LOOK + 1, 2 * LOOK),
+                                            (0, 16, 32, 48, NEVER)):
         g1 = g0 + ngen
         for stop_at in list(range(g0, g1)) + [NEVER]:
             # without a stop rule nothing but the abandonment stops a fit
@@ -89,4 +95,4 @@ def test_all_waves_leave_together(stops, early):
                 assert left["books"] == left["members"]
                 assert flags == (flag if stop_at < g1 else 0), (g0, g1, first2, stop_at, flag)
                 if stop_at < g1:
-                    assert left["books"] <= max(stop_at + 10, g1 if stop_at + 2 >= g1 else 0)
+                    assert left["books"] <= max(stop_at + 2 + LOOK, g1 if stop_at + 2 >= g1 else 0)
