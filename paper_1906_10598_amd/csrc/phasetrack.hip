@@ -28,8 +28,8 @@
 
 using namespace pt;
 
-// Device memory of pt_objective_noalloc: the tile partial sums of one call (past
-// room once taken by a descriptor and packed rows).  Each device the
+// Device memory of pt_objective_noalloc: the block descriptor and the packed rows
+// (of the larger evaluations) and the tile partial sums of one call.  Each device the
 // library runs on holds its own copy for the life of the process; host code
 // reaches it only through the address hipGetSymbolAddress gives for the
 // current device (pt_ctx::noalloc), never through this name.
@@ -240,6 +240,8 @@ void launch_objective(ObjKernel k, unsigned grid, size_t lds, hipStream_t s, con
 }  // namespace
 
 // ------------------------------------------------------------------ context
+constexpr size_t kEvalRowsAt = 64;  // bytes of pt_ctx::eval_host ahead of the rows
+
 struct pt_ctx {
     int device = 0;
     int ncu = 0;
@@ -285,10 +287,10 @@ struct pt_ctx {
     std::map<std::tuple<int, int, int>, Geometry> tuned;  // (size class, P, mixed)
     // this device's copy of the allocation-free entry point's array
     unsigned char* noalloc = nullptr;
-    // bare objective evaluations: arrival counters (zero between calls), and the
-    // arithmetic the device chose (pinned host memory)
+    // bare objective evaluations: arrival counters (zero between calls); and in pinned
+    // host memory the arithmetic the device chose, and room for the rows
     DevBuf eval_sync;
-    PinBuf eval_arith;
+    PinBuf eval_host;
     // graph cache
     struct GraphKey {
         void* desc;
@@ -555,22 +557,22 @@ int get_graph(pt_ctx* ctx, const Plan& pl, int iters, int base, hipGraphExec_t* 
 }
 
 // Everything up to (and including) copying descriptors for nblk blocks.
+// Workgroups of kernel k that a compute unit holds at a time (0: not known).
+int resident_wgs(pt_ctx* ctx, const void* k, size_t lds) {
+    auto key = std::make_pair(k, lds);
+    auto it = ctx->resident.find(key);
+    if (it != ctx->resident.end()) return it->second;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kThreads, lds) != hipSuccess) per_cu = 0;
+    ctx->resident[key] = per_cu;
+    return per_cu;
+}
+
 // Whether a leading-step launch of `units` work units (bookkeeping units
 // included) of kernel k fits in two rounds of resident workgroups; larger
 // launches are throughput-bound and run the DE step elsewhere.
 bool lead_fits(pt_ctx* ctx, ObjKernel k, size_t lds, int64_t units) {
-    auto key = std::make_pair(reinterpret_cast<const void*>(k), lds);
-    auto it = ctx->resident.find(key);
-    int per_cu = 0;
-    if (it != ctx->resident.end()) {
-        per_cu = it->second;
-    } else {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k), kThreads, lds) !=
-            hipSuccess)
-            per_cu = 0;
-        ctx->resident[key] = per_cu;
-    }
-    return units <= 2LL * per_cu * ctx->ncu;
+    return units <= 2LL * resident_wgs(ctx, reinterpret_cast<const void*>(k), lds) * ctx->ncu;
 }
 
 // Descriptor fields of one block that do not depend on where its buffers
@@ -1195,7 +1197,7 @@ int pt_ctx_create(int device, pt_ctx** out) {
     HIPCHK(hipGetSymbolAddress(&na, HIP_SYMBOL(scratch)));
     c->noalloc = static_cast<unsigned char*>(na);
     int rc = c->eval_sync.ensure(kSyncInts * sizeof(int));
-    if (rc || (rc = c->eval_arith.ensure(sizeof(int)))) {
+    if (rc || (rc = c->eval_host.ensure(kEvalRowsAt + PT_MAX_POP * PT_NSLOT * sizeof(double)))) {
         c->eval_sync.release();
         return rc;
     }
@@ -1243,7 +1245,7 @@ void pt_ctx_destroy(pt_ctx* ctx) {
     ctx->hrec.release();
     ctx->hseed.release();
     ctx->hnode.release();
-    ctx->eval_arith.release();
+    ctx->eval_host.release();
     ctx->hstate.release();
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
@@ -1392,12 +1394,14 @@ static EvalPlan eval_plan(pt_ctx* ctx, const pt_block& blk, int P, int precision
     const int64_t tile = (int64_t)kThreads * e.geo.spl, ntiles = (blk.n + tile - 1) / tile;
     // Candidate groups per workgroup: the samples, the rows' extents and the tile
     // constants are then fetched once for all of them, but a launch of few
-    // workgroups leaves places idle.  With 2 (32 samples per lane), 3 (16) or 4
-    // workgroups resident per compute unit a launch takes ceil(workgroups /
-    // places) rounds, each of the candidates, about one more per group for its
-    // reduction and four for the set-up.  The group size is chosen along with it
-    // unless it was set or tuned (it changes no sum).
-    const int64_t places = ctx->ncu * (e.geo.spl == 32 ? 2 : e.geo.spl == 16 ? 3 : 4);
+    // workgroups leaves places idle.  With the places of the workgroups resident
+    // at a time (two to four per compute unit, fewest for FP64 and 32 samples per
+    // lane) a launch takes ceil(workgroups / places) rounds, each of the
+    // candidates, about one more per group for its reduction and four for the
+    // set-up.  The group size is chosen along with it unless it was set or tuned
+    // (it changes no sum).
+    const void* k0 = reinterpret_cast<const void*>(eval_kernel(blk.dtype, e.geo, mixed));
+    const int64_t places = (int64_t)ctx->ncu * std::max(1, resident_wgs(ctx, k0, 0));
     const bool given = ctx->forced.spl || ctx->tuned.count(std::make_tuple(size_class(blk.n), P, (int)mixed));
     const int cpg0 = e.geo.cpg;
     int64_t best = INT64_MAX;
@@ -1422,7 +1426,7 @@ static EvalPlan eval_plan(pt_ctx* ctx, const pt_block& blk, int P, int precision
 
 // Enqueue the evaluation, wait for it, and note what it used.
 static int eval_run(pt_ctx* ctx, const EvalPlan& e, const double* pop, double* out, int* sync, hipStream_t s) {
-    int* arith = static_cast<int*>(ctx->eval_arith.p);
+    int* arith = static_cast<int*>(ctx->eval_host.p);
     hipLaunchKernelGGL(e.kernel, dim3((unsigned)((e.units + 7) / 8 * 8)), dim3(kThreads), 0, s, e.d, pop, out, sync, arith,
                        e.rule, (int)e.units);
     HIPCHK(hipGetLastError());
@@ -1434,6 +1438,70 @@ static int eval_run(pt_ctx* ctx, const EvalPlan& e, const double* pop, double* o
     HIPCHK(hipStreamSynchronize(s));
     ctx->last_arith = *arith;
     ctx->last_geo = e.geo;
+    return PT_OK;
+}
+
+// One descriptor into device memory, passed by value (no host staging).
+__global__ void k_put_desc(BlockDesc d, BlockDesc* dst) {
+    if (threadIdx.x == 0) *dst = d;
+}
+
+// Evaluations of so many candidate-samples run faster in the objective kernels of
+// the fits: the host reads the rows and names the arithmetic, so a kernel holds one
+// variant's registers (FP64, 32 samples per lane: three workgroups per compute unit
+// instead of two) and a workgroup one group of candidates.  That is three launches
+// and a copy more, some 20 us.  P n, k_eval / these, us: FP64 1.6e8 90 / 97, 2.8e8
+// 130 / 131, 3.2e8 147 / 143, 4e8 184 / 172, 1.6e9 633 / 507; mixed 1.8e8 124 / 131, 2.6e8
+// 168 / 161, 4e8 231 / 204, 1.6e9 751 / 627.
+static bool eval_large(const BlockDesc& d, int precision) {
+    return d.n * d.P >= (precision == PT_PREC_MIXED ? 190000000 : 300000000) &&
+           (int64_t)d.ntiles * d.P <= (int64_t)1 << 30;  // (work units, however many rows in each)
+}
+
+// Such an evaluation (samples on the device).  head: device memory of
+// eval_head_bytes(P).
+constexpr size_t kEvalDescBytes = 1024;
+static size_t eval_head_bytes(int P) {
+    return kEvalDescBytes + (((size_t)P * kStride * sizeof(double) + 255) & ~(size_t)255);
+}
+static int eval_by_fit_kernels(pt_ctx* ctx, const pt_block& block, const double* pop, int P, int precision, int objective,
+                               unsigned char* head, double* partials, double* out, hipStream_t s) {
+    // (pinned memory, one copy: 20 us for each of several, or into other memory)
+    double* rows_h = reinterpret_cast<double*>(static_cast<char*>(ctx->eval_host.p) + kEvalRowsAt);
+    PopExtents ext;
+    HIPCHK(hipMemcpyAsync(rows_h, pop, sizeof(double) * PT_NSLOT * P, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    ext.add(rows_h, P);
+    pt_block blk = block;
+    ext.apply(blk);
+    Plan pl;
+    pl.mixed = precision == PT_PREC_MIXED;
+    pl.geo = choose_geometry(ctx, blk.n, P, pl.mixed);
+    pl.mode = pl.mixed ? kModeMixed : kModePoly;
+    pl.mode = ext.mode(pl, ctx, &block);
+    const int64_t tile = (int64_t)kThreads * pl.geo.spl, ntiles = (blk.n + tile - 1) / tile;
+    const int groups = (P + pl.geo.cpg - 1) / pl.geo.cpg;
+    const int64_t units = ntiles * groups;
+    const pt_de_settings de = eval_settings(P, precision, objective);
+    BlockDesc d = base_desc(blk, &de, (int)ntiles, groups);
+    static_assert(sizeof(BlockDesc) <= kEvalDescBytes, "descriptor slot too small");
+    BlockDesc* dd = reinterpret_cast<BlockDesc*>(head);
+    d.trial = d.pop = reinterpret_cast<double*>(head + kEvalDescBytes);
+    d.partials = partials;
+    const bool slope = blk.box.lo[5] != 0.0 || blk.box.hi[5] != 0.0;
+    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, d, dd);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(k_pack_rows, dim3(1), dim3(256), 0, s, pop, d.trial, P);
+    HIPCHK(hipGetLastError());
+    launch_objective(objective_kernel(blk.dtype, pl.geo, pl.mode, slope), (unsigned)((units + 7) / 8 * 8), 0, s,
+                     (const BlockDesc*)dd, 1, (int)units, 0);
+    HIPCHK(hipGetLastError());
+    const unsigned nt = pow2_at_least(P);
+    hipLaunchKernelGGL(k_reduce_eval, dim3(1), dim3(nt), nt * sizeof(double), s, d, out);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(s));
+    ctx->last_arith = pl.mode;
+    ctx->last_geo = pl.geo;
     return PT_OK;
 }
 
@@ -1451,6 +1519,11 @@ int pt_objective(pt_ctx* ctx, const pt_block* block, const double* pop, int P, i
     if (e.units > (int64_t)1 << 30) return fail(PT_EINVAL, "batch too large (%lld work units)", (long long)e.units);
     if ((rc = ctx->partials.ensure((size_t)P * e.d.ntiles * sizeof(double)))) return rc;
     e.d.partials = static_cast<double*>(ctx->partials.p);
+    if (eval_large(e.d, precision)) {
+        if ((rc = ctx->eval_pop.ensure(eval_head_bytes(P)))) return rc;
+        return eval_by_fit_kernels(ctx, staged[0], pop, P, precision, objective,
+                                   static_cast<unsigned char*>(ctx->eval_pop.p), e.d.partials, out, s);
+    }
     return eval_run(ctx, e, pop, out, static_cast<int*>(ctx->eval_sync.p), s);
 }
 
@@ -1464,18 +1537,19 @@ int pt_objective_noalloc(pt_ctx* ctx, const pt_block* block, const double* pop, 
     if (!ctx->noalloc) return fail(PT_EDEVICE, "pt_objective_noalloc: no device array on this context");
     HIPCHK(hipSetDevice(ctx->device));
     EvalPlan e = eval_plan(ctx, *block, P, precision, objective);
-    // the partial sums (P x ntiles) lie in the array past the places of a
-    // descriptor and of packed rows, which count towards its size as stated
-    constexpr size_t kDescBytes = 1024;
-    const size_t row_bytes = ((size_t)P * kStride * sizeof(double) + 255) & ~(size_t)255;
-    const size_t need = kDescBytes + row_bytes + (size_t)P * (size_t)e.d.ntiles * sizeof(double);
+    // layout in the array: descriptor | rows (of the larger evaluations) | partial
+    // sums (P x ntiles)
+    const size_t head = eval_head_bytes(P), need = head + (size_t)P * (size_t)e.d.ntiles * sizeof(double);
     if (need > (size_t)PT_NOALLOC_SCRATCH_BYTES)
         return fail(PT_EINVAL,
                     "pt_objective_noalloc: P = %d and n = %lld need %zu bytes of device memory, more than the "
                     "%zu-byte array (P x ceil(n / %lld) partial sums must fit)",
                     P, (long long)block->n, need, (size_t)PT_NOALLOC_SCRATCH_BYTES,
                     (long long)((int64_t)kThreads * e.geo.spl));
-    e.d.partials = reinterpret_cast<double*>(ctx->noalloc + kDescBytes + row_bytes);
+    e.d.partials = reinterpret_cast<double*>(ctx->noalloc + head);
+    if (eval_large(e.d, precision))
+        return eval_by_fit_kernels(ctx, *block, pop, P, precision, objective, ctx->noalloc, e.d.partials, out,
+                                   static_cast<hipStream_t>(hip_stream));
     // (no counters in that array: calls that raced on it would leave them wrong)
     e.rule.tail = 0;
     return eval_run(ctx, e, pop, out, nullptr, static_cast<hipStream_t>(hip_stream));
