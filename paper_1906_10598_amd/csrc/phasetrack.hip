@@ -667,6 +667,12 @@ int plan_arithmetic(pt_ctx* ctx, const pt_block* blocks, int nblk, const pt_de_s
                      ((P + pl->geo.cpg - 1) / pl->geo.cpg);
         if (units > 4LL * ctx->ncu) pl->geo = throughput_geometry(P);
     }
+    // (whatever form a block then takes: the work units of the forms over the samples)
+    int64_t units = 0;
+    for (int b = 0; b < nblk; ++b)
+        units += (blocks[b].n + (int64_t)kThreads * pl->geo.spl - 1) / ((int64_t)kThreads * pl->geo.spl) *
+                 ((P + pl->geo.cpg - 1) / pl->geo.cpg);
+    if (units > (int64_t)1 << 30) return fail(PT_EINVAL, "batch too large (%lld work units)", (long long)units);
     pl->mode = pl->mixed ? kModeMixed : kModePoly;
     phasor->assign(nblk, 0);
     *n_phasor = 0;
@@ -1455,7 +1461,7 @@ __global__ void k_put_desc(BlockDesc d, BlockDesc* dst) {
 // 168 / 161, 4e8 231 / 204, 1.6e9 751 / 627.
 static bool eval_large(const BlockDesc& d, int precision) {
     return d.n * d.P >= (precision == PT_PREC_MIXED ? 190000000 : 300000000) &&
-           (int64_t)d.ntiles * d.P <= (int64_t)1 << 30;  // (work units, however many rows in each)
+           (int64_t)d.ntiles * d.P <= (int64_t)1 << 30;  // (work units, with one row in each)
 }
 
 // Such an evaluation (samples on the device).  head: device memory of
@@ -1516,7 +1522,9 @@ int pt_objective(pt_ctx* ctx, const pt_block* block, const double* pop, int P, i
     std::vector<pt_block> staged;
     if ((rc = stage_blocks(ctx, block, 1, s, &staged))) return rc;
     EvalPlan e = eval_plan(ctx, staged[0], P, precision, objective);
-    if (e.units > (int64_t)1 << 30) return fail(PT_EINVAL, "batch too large (%lld work units)", (long long)e.units);
+    const Geometry geo = choose_geometry(ctx, block->n, P, precision == PT_PREC_MIXED);
+    const int64_t units = (int64_t)e.d.ntiles * ((P + geo.cpg - 1) / geo.cpg);  // one group each
+    if (units > (int64_t)1 << 30) return fail(PT_EINVAL, "batch too large (%lld work units)", (long long)units);
     if ((rc = ctx->partials.ensure((size_t)P * e.d.ntiles * sizeof(double)))) return rc;
     e.d.partials = static_cast<double*>(ctx->partials.p);
     if (eval_large(e.d, precision)) {
