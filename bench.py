@@ -7,8 +7,9 @@ all samples), starting from samples already resident in HBM and ending with
 the fitted record (coefficients + derived observables) on the host.
 
 Printed (one JSON line): candidate*sample evaluations per second of the
-plain FP64 path, fit latency p50 / p99 of the plain and mixed-precision
-paths, the mixed path's speedup and error against the FP64 oracle, the
+plain FP64 path, fit latency p50 / p99 with either precision asked for (both run
+through FP64 node weights), the plain and mixed sums over the samples against each
+other, errors against the FP64 oracle, the
 roofline figures of the fit's kernels (HIP events around the timed fits) and of
 the objective over the samples, and the CPU oracle's rate on a bounded sample of
 the same workload.  The fits run through node weights (sums over the samples as
@@ -45,6 +46,15 @@ VALU_ISSUE_SLOTS_PER_S = 1024 * 2.4e9 / 4.0  # wave64 VALU instructions: 1024 SI
 # FP64 operations of the same launches.
 ALG_FLOP = 40
 ARITH_NAME = {0: "fp64-per-sample", 1: "mixed", 2: "fp64-phasor"}
+
+
+def fit_arithmetic(ptk, ctx, gens):
+    """Arithmetic of the context's last fit of a fixed number of generations: the
+    forms over the samples take a launch a generation (or one persistent grid)."""
+    if (ptk.pt_ctx_last_launch(ctx.handle) != ptk.PT_LAUNCH_PERSISTENT
+            and ptk.pt_ctx_fit_launches(ctx.handle) <= gens):
+        return "fp64-nodes"
+    return ARITH_NAME[ptk.pt_ctx_last_arithmetic(ctx.handle)]
 
 from paper_1906_10598_amd.rocprof_summary import executed_flop, kernel_hash, read_profile  # noqa: E402
 
@@ -255,7 +265,7 @@ def quartic_fit(ctx, ptk, synth, np, torch):
     t0 = time.perf_counter()
     q = ctx.fit_block(blk, de)
     dt = time.perf_counter() - t0
-    arith = ARITH_NAME[ptk.pt_ctx_last_arithmetic(ctx.handle)]
+    arith = fit_arithmetic(ptk, ctx, b.de.max_gens)
     lo, hi = b.lo.copy(), b.hi.copy()
     lo[6] = hi[6] = 0.0
     lo[4], hi[4] = b.truth[4] - 0.05, b.truth[4] + 0.05
@@ -410,8 +420,9 @@ def main():
         return 2 * src.numel() * 4
 
     # launch form of the fits (the autotuner times fits in this form)
-    ptk.pt_ctx_set_launch_mode(ctx.handle, {"auto": ptk.PT_LAUNCH_AUTO, "graph": ptk.PT_LAUNCH_GRAPH,
-                                            "persistent": ptk.PT_LAUNCH_PERSISTENT}[args.launch])
+    launch_mode = {"auto": ptk.PT_LAUNCH_AUTO, "graph": ptk.PT_LAUNCH_GRAPH,
+                   "persistent": ptk.PT_LAUNCH_PERSISTENT}[args.launch]
+    ptk.pt_ctx_set_launch_mode(ctx.handle, launch_mode)
     ptk.pt_ctx_set_step_fusion(ctx.handle, {"auto": ptk.PT_FUSION_AUTO, "lead": ptk.PT_FUSION_LEAD,
                                             "last": ptk.PT_FUSION_LAST, "off": ptk.PT_FUSION_OFF}[args.fusion])
     tiles = {}
@@ -456,7 +467,7 @@ def main():
         print(json.dumps({"fit_only": True, "launch": args.launch, "fusion": args.fusion, "fits": args.steps,
                           "ms_per_fit": el / args.steps * 1e3,
                           "p50_ms": pct(lat, 50), "geometry": tiles["fp64"],
-                          "arithmetic": ARITH_NAME[ptk.pt_ctx_last_arithmetic(ctx.handle)],
+                          "arithmetic": fit_arithmetic(ptk, ctx, G),
                           "kernel_hash": kernel_hash()}), flush=True)
         ctx.close()
         return
@@ -483,7 +494,7 @@ def main():
     elapsed, lat_steps, fits64 = run_fits(ctx, blk, de(ptk.PT_PREC_FP64), args.steps, "fp64", events=ev)
     launches_per_fit = ptk.pt_ctx_fit_launches(ctx.handle)
     value = pairs_per_fit * args.steps / elapsed
-    arith64 = ARITH_NAME[ptk.pt_ctx_last_arithmetic(ctx.handle)]
+    arith64 = fit_arithmetic(ptk, ctx, G)
     print(f"# fp64: {args.steps} fits in {elapsed:.3f} s", file=sys.stderr, flush=True)
 
     # ---- latency percentiles (distinct seeds), both paths
@@ -498,6 +509,15 @@ def main():
     run_fits(ctx, blk, de(ptk.PT_PREC_MIXED), max(1, args.warmup), "mixed-warm")
     el_mx, lat_mx, fits_mx = run_fits(ctx, blk, de(ptk.PT_PREC_MIXED), max(args.latency_fits, 1), "mixed")
     value_mx = pairs_per_fit * len(lat_mx) / el_mx
+    arith_mx = fit_arithmetic(ptk, ctx, G)
+    # the mixed arithmetic itself, which those fits do not use: both over the samples
+    over = {}
+    ptk.pt_ctx_set_launch_mode(ctx.handle, ptk.PT_LAUNCH_GRAPH)
+    for name, prec in (("fp64", ptk.PT_PREC_FP64), ("mixed", ptk.PT_PREC_MIXED)):
+        run_fits(ctx, blk, de(prec), 1, "over-samples-warm")
+        _, lat_over, _ = run_fits(ctx, blk, de(prec), 5, "over-samples")
+        over[name] = {"p50_ms": pct(lat_over, 50), "arithmetic": fit_arithmetic(ptk, ctx, G)}
+    ptk.pt_ctx_set_launch_mode(ctx.handle, launch_mode)
     print(f"# mixed: {len(lat_mx)} fits in {el_mx:.3f} s", file=sys.stderr, flush=True)
 
     # ---- accuracy of both paths against the FP64 oracle (same seed as fit 0)
@@ -634,7 +654,9 @@ def main():
             "mixed": {"p50": pct(lat_mx, 50), "p99": pct(lat_mx, 99), "fits": len(lat_mx)},
         },
         "block_fits_per_s": {"fp64": args.steps / elapsed, "mixed": len(lat_mx) / el_mx},
-        "mixed": {"value": value_mx, "speedup_vs_fp64": value_mx / value, **mixed_err,
+        "mixed": {"value": value_mx, "arithmetic": arith_mx, "speedup_vs_fp64": value_mx / value,
+                  "over_samples": {**over, "speedup_vs_fp64": over["fp64"]["p50_ms"] / over["mixed"]["p50_ms"]},
+                  **mixed_err,
                   "geometry": {"samples_per_lane": tiles["mixed"][0], "cand_per_group": tiles["mixed"][1]},
                   "roofline": {"bound": "alu", "achieved": roof["mixed"]["achieved"],
                                "peak": PEAK_FP32_UNPACKED_TFLOPS, "unit": "TFLOP/s",

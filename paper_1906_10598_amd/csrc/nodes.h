@@ -18,7 +18,7 @@
 //
 // Measured against one launch per generation over all samples (each generation
 // a chain of ~9 us in its leading-step form; same machine): the 400 000-sample
-// block, P = 40, 2000 generations 18.2 -> 0.89 ms; the quartic 1e6-sample block
+// block, P = 40, 2000 generations 18.2 -> 0.90 ms; the quartic 1e6-sample block
 // 39.5 -> 1.19 ms; 64 uneven blocks, 1500 generations 183 -> 0.97 ms (the
 // blocks' generations then run on 64 compute units at once instead of sharing
 // the chip's issue slots sample by sample).
