@@ -73,6 +73,7 @@ struct DevBuf {
         size_t want = std::max(bytes, (size_t)256);
         if (hipMalloc(&p, want) != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();  // (reported here, not by the next launch)
             return fail(PT_ENOMEM, "hipMalloc(%zu bytes) failed", want);
         }
         cap = want;
@@ -96,6 +97,7 @@ struct PinBuf {
         size_t want = std::max(bytes, (size_t)4096);
         if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();
             return fail(PT_ENOMEM, "hipHostMalloc(%zu bytes) failed", want);
         }
         cap = want;
@@ -1138,10 +1140,7 @@ int run_fit(pt_ctx* ctx, const pt_block* given, int nblk, const pt_de_settings* 
         for (int b : by_nodes)  // abandoned: more signal to noise than the weights carry
             if (!room || rec[b].flags & kFlagNodeAbort) by_samples.push_back(b);
         std::sort(by_samples.begin(), by_samples.end());
-        if (!room) {
-            by_nodes.clear();
-            (void)hipGetLastError();  // (the allocation's, not for a later launch to report)
-        }
+        if (!room) by_nodes.clear();
     }
     if (!by_samples.empty()) {
         const int64_t node_launches = ctx->last_fit_launches;
@@ -2264,7 +2263,6 @@ int early_withdraw(pt_server* sv, pt_server::Pending& p) {
 
 // The device is full: everything held for blocks that wait goes first (but `keep`'s).
 int server_make_room(pt_server* sv, const pt_server::Pending* keep) {
-    (void)hipGetLastError();  // (the failed allocation's)
     int rc;
     for (auto& w : sv->pending)
         if (&w != keep && w.dev.p && (rc = early_withdraw(sv, w))) return rc;
@@ -2385,7 +2383,6 @@ int server_node_room(pt_server* sv, int K) {
             if ((rc = server_make_room(sv, nullptr))) return e;
             e = node_room(sv->ctx, b, doubles * sizeof(double));
         }
-        if (e) (void)hipGetLastError();
         return e;
     };
     for (auto& sl : sv->slots) {

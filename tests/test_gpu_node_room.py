@@ -87,3 +87,19 @@ def test_served_blocks_without_room_run_over_their_samples(room, lead, room_byte
             assert (f.objective, f.generations, f.flags) == (w.objective, w.generations, w.flags), k
     finally:
         ptk.pt_server_destroy(srv)
+
+
+@pytest.mark.parametrize("mode", [ptk.PT_LAUNCH_AUTO, ptk.PT_LAUNCH_GRAPH])
+def test_a_refused_allocation_leaves_no_error_behind(mode):
+    """The history of 4096 blocks of 1e7 generations is 328 GB, more than the device has:
+    the call says so, and the next one runs."""
+    b = synth.config0(5)
+    pb = block_of(b, to_dev(b.samples))
+    with ptk.Context(0) as c:
+        ptk.pt_ctx_set_launch_mode(c.handle, mode)
+        with pytest.raises(ptk.PtError, match=r"hipMalloc\(\d+ bytes\) failed"):
+            c.fit_batch([pb] * 4096, settings_of(b, gens=10_000_000, pop=4))
+        de = settings_of(b, gens=20)
+        want = _fit([pb], de, mode)[0][0]
+        f = c.fit_block(pb, de)
+        assert list(f.coef) == list(want.coef) and f.objective == want.objective
